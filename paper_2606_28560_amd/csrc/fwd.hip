@@ -1,4 +1,6 @@
-// Forward kernel: window band + shared rung offsets, softmax, weighted values, lse.
+// Forward kernel for every storage type, head size and window outside the bfloat16,
+// d_head 64, W <= 16 path (fwd_mfma.hip): window band + shared rung offsets, softmax,
+// weighted values, lse.
 //
 // Section 2 "Attended set": every query i of a (b, h) attends to distances 0..W and to
 // the rung distances d_k = alpha f_k, each rung read as the blend of rows
@@ -6,123 +8,260 @@
 // offsets are shared, a block of consecutive queries reads, for each rung, one
 // contiguous shifted block of key/value rows.
 //
-// Layout: a group of LPQ = D / VN lanes owns one query; lane `sub` holds dims
-// [sub*VN, sub*VN + VN) (16 bytes of the row), so a row load by a group is one
-// coalesced 64- or 128-byte access and consecutive groups read consecutive rows.
-// Pass 1 computes the scaled logits (blend done in score space: the logit of a rung
-// is (1-w) <q, k[r0]> + w <q, k[r1]>) into LDS and their maximum; pass 2 forms the
-// probabilities and the weighted sum of values.  The whole softmax runs in base 2.
+// A wave owns 16 consecutive queries (lane layouts in tile.h):
+//   - window band: the keys i - W .. i lie in 32-row chunks that end at the wave's last
+//     query (one for W <= 16, five for W = 128).  The workgroup's chunks are copied to LDS
+//     a few at a time; per chunk, S = K.Q^T on the matrix cores, masked to 0 <= i - j <= W,
+//     and V^T.P^T accumulated there, with the running maximum of an online softmax;
+//   - rungs: per-row dot products on the VALU (four lanes per row), blended in score
+//     space, their probabilities' weighted values added in the same registers.
+// The whole softmax runs in base 2.
+//
+// What bounds it: the latency of the rung gathers (L2) and their VALU work; the band, on
+// the matrix cores, is a fraction of it at any window.  Against a kernel with one lane
+// group per query, every row read from global memory by every query and no matrix cores
+// (us a launch, interpolating unless noted): bf16 d 64 B4 H8 T1500 W128, integer offsets,
+// 115.8 -> 15.6; bf16 d 64 B4 H8 T2048 W64 76.3 -> 17.2; bf16 d 128 B2 H16 on 4 T2000 W8
+// 62.0 -> 28.3; bf16 d 32 B8 H8 T1024 W10 25.5 -> 11.1; fp32 d 64 B4 H8 T1024 W12 33.4 -> 16.9.
 #include "launch.h"
+#include "tile.h"
 
 namespace fibattn {
 
-// DEV: the rung table is the one at rtp, built on the device (rt_arg unused).
-template <typename S, int D, bool DEV>
-__global__ __launch_bounds__(256) void fwd_kernel(const S *__restrict__ q, const S *__restrict__ k,
-                                                  const S *__restrict__ v, S *__restrict__ o,
-                                                  float *__restrict__ lse, int T, int W,
-                                                  RungTable rt_arg, const RungTable *__restrict__ rtp,
-                                                  float scale_log2, Heads hd, Layouts lay) {
-    const RungTable &rt = DEV ? *rtp : rt_arg;
-    constexpr int VN = Vec<S>::N;
-    constexpr int LPQ = D / VN;
-    constexpr int QPB = 256 / LPQ;
-    extern __shared__ float smem[];
+constexpr float kFwdSlack = 8.f;  // log2 units a rung's logit may exceed the running reference
 
-    const int cap = W + 1 + (DEV ? kMaxRungs : rt.n);  // LDS logits per query
-    const int g = threadIdx.x / LPQ;
-    const int sub = threadIdx.x % LPQ;
-    const int i = blockIdx.x * QPB + g;
-    const int bk = hd.kv_of(blockIdx.y);
-    const S *Q = q + lay.q.head(blockIdx.y, hd.H);
+// Waves per SIMD the registers are budgeted for: a slice is NC 16-byte pieces, and a rung
+// holds four of them in flight (rows r0, r1 of K and V) next to q's slice and D / 4 sums.
+template <typename S, int D>
+constexpr int fwd_waves = Tile<S, D>::NC <= 2 ? 4 : Tile<S, D>::NC == 4 ? 3 : 2;
+
+// INTERP: some rung has w != 0, so the second row r1 is read; otherwise two rungs are
+// taken together.  DEV: the rung table is the one at rtp, built on the device (rt_arg
+// unused).
+template <typename S, int D, bool INTERP, bool DEV>
+__global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
+    const S *__restrict__ q, const S *__restrict__ k, const S *__restrict__ v, S *__restrict__ o,
+    float *__restrict__ lse, int T, int W, RungTable rt_arg, const RungTable *__restrict__ rtp, float sl2,
+    TileShape ts, Heads hd, Layouts lay) {
+    using TL = Tile<S, D>;
+    using Slice = typename TL::Slice;
+    const RungTable &rt = DEV ? *rtp : rt_arg;
+    constexpr int RB = INTERP ? 1 : 2;          // rungs per batch: two rows of K and of V
+    constexpr int NBUF = TL::NC <= 2 ? 2 : 1;   // batches in flight
+    extern __shared__ __align__(16) char smem[];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nw = blockDim.x >> 6;
+    const int nm = lane & 15, gm = lane >> 4;  // MFMA layout
+    const int nq = lane >> 2, gq = lane & 3;   // quad layout
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int runs = nw / ts.hs, wv = wave / ts.hs;
+    const int bh = (blk / ts.tiles) * ts.hs + wave % ts.hs;  // this wave's query head
+    const int T0 = (blk % ts.tiles) * 16 * runs;
+    const int bk = hd.kv_of(bh);
+    const S *Q = q + lay.q.head(bh, hd.H);
     const S *K = k + lay.k.head(bk, hd.kv_heads());
     const S *V = v + lay.v.head(bk, hd.kv_heads());
-    const long long sq = lay.q.st, sk = lay.k.st, sv = lay.v.st;  // row strides
-    float *sc = smem + g * cap;
-    const int col = sub * VN;
+    const uint32_t sk = (uint32_t)(lay.k.st * (int)sizeof(S)), sv = (uint32_t)(lay.v.st * (int)sizeof(S));
 
-    float m = -INFINITY;
-    if (i < T) {
-        float qv[VN], kv[VN];
-        Vec<S>::load(Q + i * sq + col, qv);
-        int e = 0;
-        const int wmax = min(W, i);
-        for (int d = 0; d <= wmax; ++d, ++e) {
-            Vec<S>::load(K + (i - d) * sk + col, kv);
-            const float s = group_sum<LPQ>(dot<VN>(qv, kv)) * scale_log2;
-            if (sub == 0) sc[e] = s;
-            m = fmaxf(m, s);
+    const int t0 = T0 + 16 * wv;
+    const int im = t0 + nm;                        // MFMA layout query
+    const int i = t0 + nq, ic = min(i, T - 1);     // quad layout query
+    const Slice qq = TL::load(Q, ic, gq, (uint32_t)(lay.q.st * (int)sizeof(S)));
+
+    // rungs some query of this wave includes: a prefix of the table (sorted by d)
+    int nact = 0;
+#pragma unroll
+    for (int r = 0; r < kMaxRungs; ++r) nact += ((r < rt.n) & (rt.d0[r] <= min(t0 + 15, T - 1))) ? 1 : 0;
+    nact = t0 < T ? __builtin_amdgcn_readfirstlane(nact) : 0;
+
+    // the two rows of a batch: r0 and r1 of a rung, or r0 of two rungs (the second clamped
+    // to an active one and masked)
+    auto load_batch = [&](int rb, const void *X, uint32_t st, Slice *x) {
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            const int d = INTERP ? rt.d0[rb] + y : rt.d0[min(rb + y, nact - 1)];
+            x[y] = TL::load(X, max(ic - d, 0), gq, st);
         }
-        for (int r = 0; r < rt.n; ++r, ++e) {
-            const int d0 = rt.d0[r];
-            const float w = rt.w[r];
-            if (!(d0 < i || (d0 == i && w == 0.f))) break;  // d_k > i: before position 0
-            const int r0 = i - d0;
-            Vec<S>::load(K + r0 * sk + col, kv);
-            float part = (1.f - w) * dot<VN>(qv, kv);
-            if (w != 0.f) {
-                Vec<S>::load(K + (r0 - 1) * sk + col, kv);
-                part = fmaf(w, dot<VN>(qv, kv), part);
+    };
+    Slice kx[NBUF][2], vx[NBUF][2];
+    // in flight during the band phase, as far as the registers go
+    if (TL::NC <= 4 && nact > 0) load_batch(0, K, sk, kx[0]);
+    if (TL::NC <= 2 && nact > 0) load_batch(0, V, sv, vx[0]);
+
+    // ---- window band (MFMA layout) ----
+    const Slice qm = TL::from_quad(qq, lane);
+    float m = 0.f, l = 0.f;
+    typename TL::Acc acc;
+    TL::zero(acc);
+    const unsigned reach = (unsigned)min(W, im);  // 0 <= im - key <= W and key >= 0
+    for (int c0 = 0; c0 < ts.nc; c0 += ts.cps) {
+        // chunks c0 .. c0 + n - 1 of every run: chunk c of run wv is the rows
+        // [T0 + 16 wv + 16 - 32 (c + 1), T0 + 16 wv + 16 - 32 c)
+        const int n = min(ts.cps, ts.nc - c0);
+        const int rbeg = T0 + 16 - 32 * (c0 + n), rows = 16 * (runs - 1) + 32 * n;
+        char *kr = smem, *vr = smem + rows * TL::kRow;
+        if (c0 > 0) __syncthreads();  // every wave is done with the rows staged before
+        TL::stage(kr, K, rbeg, rows, T, lay.k.st, wave, nw);
+        TL::stage(vr, V, rbeg, rows, T, lay.v.st, wave, nw);
+        wait_vmem();
+        __syncthreads();
+        for (int c = 0; c < n; ++c) {
+            const int base = 16 * wv + 32 * (n - 1 - c);  // the chunk's first staged row
+            float p[8], mx = -INFINITY;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const f32x4 s = TL::scores(TL::staged(kr, base + 16 * b + nm, gm), qm);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int key = rbeg + base + 16 * b + 4 * gm + e;
+                    p[4 * b + e] = (unsigned)(im - key) <= reach ? s[e] * sl2 : -INFINITY;
+                    mx = fmaxf(mx, p[4 * b + e]);
+                }
             }
-            const float s = group_sum<LPQ>(part) * scale_log2;
-            if (sub == 0) sc[e] = s;
-            m = fmaxf(m, s);
+            mx = max4(mx);
+            if (c0 + c == 0) {
+                m = mx;  // finite: the first chunk holds key im itself
+            } else if (__builtin_amdgcn_ballot_w64(mx > m)) {
+                const float mn = fmaxf(m, mx), f = fast_exp2(m - mn);
+                m = mn;
+                l *= f;
+                TL::scale(acc, f);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                p[e] = fast_exp2(p[e] - m);
+                l += p[e];
+            }
+            TL::accumulate(acc, vr, base, TL::weights(p), gm);
         }
     }
-    __syncthreads();
-    if (i < T) {
-        float acc[VN], vv[VN];
+    if (TL::NC > 4 && nact > 0) load_batch(0, K, sk, kx[0]);
+    if (TL::NC > 2 && nact > 0) load_batch(0, V, sv, vx[0]);
+    l = sum4(l);
+    // hand the band results to the quad layout
+    TL::to_quad_acc(acc, lane);
+    m = to_quad(m, lane);
+    l = to_quad(l, lane);
+
+    // ---- rungs (quad layout) ----
+    float p[RB];
+    auto logits = [&](int rb, const Slice *x) {
+        float s[RB], mb = m;
+        if constexpr (INTERP) {
+            const int d0 = rt.d0[rb];
+            const float w = rt.w[rb];
+            const bool in = d0 < i || (d0 == i && w == 0.f);
+            const float part = quad_sum((1.f - w) * TL::dot(qq, x[0]) + w * TL::dot(qq, x[1]));
+            s[0] = in ? part * sl2 : -INFINITY;
+            mb = fmaxf(mb, s[0]);
+        } else {
 #pragma unroll
-        for (int c = 0; c < VN; ++c) acc[c] = 0.f;
-        float l = 0.f;
-        int e = 0;
-        const int wmax = min(W, i);
-        for (int d = 0; d <= wmax; ++d, ++e) {
-            const float p = exp2f(sc[e] - m);
-            l += p;
-            Vec<S>::load(V + (i - d) * sv + col, vv);
-#pragma unroll
-            for (int c = 0; c < VN; ++c) acc[c] = fmaf(p, vv[c], acc[c]);
-        }
-        for (int r = 0; r < rt.n; ++r, ++e) {
-            const int d0 = rt.d0[r];
-            const float w = rt.w[r];
-            if (!(d0 < i || (d0 == i && w == 0.f))) break;
-            const float p = exp2f(sc[e] - m);
-            l += p;
-            const int r0 = i - d0;
-            const float p0 = p * (1.f - w);
-            Vec<S>::load(V + r0 * sv + col, vv);
-#pragma unroll
-            for (int c = 0; c < VN; ++c) acc[c] = fmaf(p0, vv[c], acc[c]);
-            if (w != 0.f) {
-                const float p1 = p * w;
-                Vec<S>::load(V + (r0 - 1) * sv + col, vv);
-#pragma unroll
-                for (int c = 0; c < VN; ++c) acc[c] = fmaf(p1, vv[c], acc[c]);
+            for (int y = 0; y < 2; ++y) {
+                const float part = quad_sum(TL::dot(qq, x[y]));
+                const bool in = rb + y < nact && rt.d0[rb + y < nact ? rb + y : nact - 1] <= i;
+                s[y] = in ? part * sl2 : -INFINITY;
+                mb = fmaxf(mb, s[y]);
             }
         }
+        // The running reference moves only when a logit exceeds it by more than kFwdSlack
+        // log2 units (exp2(s - m) <= 2^kFwdSlack; o = acc / l and lse = m + log2(l) hold
+        // for any reference).
+        const bool grow = mb > m + kFwdSlack;
+        if (__builtin_amdgcn_ballot_w64(grow)) {
+            const float mn = grow ? mb : m, f = fast_exp2(m - mn);
+            m = mn;
+            l *= f;
+            TL::scale(acc, f);
+        }
+#pragma unroll
+        for (int y = 0; y < RB; ++y) {
+            p[y] = fast_exp2(s[y] - m);
+            l += p[y];
+        }
+    };
+    auto values = [&](int rb, const Slice *x) {
+        if constexpr (INTERP) {
+            const float w = rt.w[rb];
+            TL::axpy2(acc, p[0] * (1.f - w), x[0], p[0] * w, x[1]);
+        } else {
+            TL::axpy2(acc, p[0], x[0], p[1], x[1]);
+        }
+    };
+    if constexpr (NBUF == 2) {
+        for (int rb = 0; rb < nact; rb += 2 * RB) {
+            if (rb + RB < nact) {
+                load_batch(rb + RB, K, sk, kx[1]);
+                load_batch(rb + RB, V, sv, vx[1]);
+            }
+            logits(rb, kx[0]);
+            values(rb, vx[0]);
+            if (rb + RB < nact) {
+                if (rb + 2 * RB < nact) {
+                    load_batch(rb + 2 * RB, K, sk, kx[0]);
+                    load_batch(rb + 2 * RB, V, sv, vx[0]);
+                }
+                logits(rb + RB, kx[1]);
+                values(rb + RB, vx[1]);
+            }
+        }
+    } else {
+        // one buffer each for K and V: the next batch's keys load while this one's values
+        // are added, its values while the next logits are taken
+        for (int rb = 0; rb < nact; rb += RB) {
+            const int nx = min(rb + RB, nact - 1);
+            logits(rb, kx[0]);
+            load_batch(nx, K, sk, kx[0]);
+            values(rb, vx[0]);
+            load_batch(nx, V, sv, vx[0]);
+        }
+    }
+
+    if (i < T) {
         const bool bad = DEV && table_unusable(rt, W);  // bad device alpha, or another W
-        const float inv = bad ? NAN : 1.f / l;
-#pragma unroll
-        for (int c = 0; c < VN; ++c) acc[c] *= inv;
-        Vec<S>::store(o + lay.o.head(blockIdx.y, hd.H) + i * lay.o.st + col, acc);
-        if (sub == 0) lse[(size_t)blockIdx.y * T + i] = bad ? NAN : (m + log2f(l)) * kLn2;
+        TL::store(o + lay.o.head(bh, hd.H) + i * lay.o.st, gq, acc, bad ? NAN : 1.f / l);
+        if (gq == 0) __builtin_nontemporal_store(bad ? NAN : (m + log2f(l)) * kLn2, lse + (size_t)bh * T + i);
     }
+}
+
+// Query heads side by side in a workgroup of nw waves, for G heads per key/value head:
+// they read the same key/value rows, so the staged rows serve all of them.
+int tile_heads(int G, int nw) {
+    for (int h = nw; h > 1; h >>= 1)
+        if (G % h == 0) return h;
+    return 1;
+}
+
+// Chunks staged at a time: as many as keep `fixed` + `per` bytes a chunk within the LDS of
+// a workgroup when four (slices of up to 32 bytes) or three workgroups share a CU.
+int tile_chunks(int nc, size_t fixed, size_t per, int slice_pieces) {
+    const size_t budget = slice_pieces <= 2 ? 40 * 1024 : 53 * 1024;
+    int c = 1;
+    while (c < nc && fixed + (size_t)(c + 1) * per <= budget) ++c;
+    return c;
 }
 
 template <typename S, int D>
 static hipError_t launch_fwd_t(const void *q, const void *k, const void *v, void *o, float *lse,
                                int BH, const Heads &hd, int T, int W, const RungTable &rt,
                                const RungTable *rtp, const Layouts &lay, hipStream_t s) {
-    constexpr int LPQ = D / Vec<S>::N;
-    constexpr int QPB = 256 / LPQ;
-    dim3 grid((T + QPB - 1) / QPB, BH);
-    const size_t lds = sizeof(float) * QPB * (size_t)(W + 1 + (rtp ? kMaxRungs : rt.n));
-    const float scale_log2 = kLog2e / sqrtf((float)D);
-    return launch(kForward, rtp ? fwd_kernel<S, D, true> : fwd_kernel<S, D, false>, grid, dim3(256),
-                  (unsigned)lds, s, (const S *)q, (const S *)k, (const S *)v, (S *)o, lse, T, W, rt,
-                  rtp, scale_log2, hd, lay);
+    using TL = Tile<S, D>;
+    constexpr int nw = TL::kRow == 512 ? 2 : 4;  // rows of 512 bytes: 32 queries' band in 48 KB
+    TileShape ts;
+    ts.hs = tile_heads(hd.G, nw);
+    const int runs = nw / ts.hs;
+    ts.tiles = (T + 16 * runs - 1) / (16 * runs);
+    ts.nc = band_chunks(W);
+    const size_t fixed = 2 * (size_t)16 * (runs - 1) * TL::kRow, per = 2 * (size_t)32 * TL::kRow;
+    ts.cps = tile_chunks(ts.nc, fixed, per, TL::NC);
+    bool interp = false;
+    for (int r = 0; r < rt.n && !interp; ++r) interp = rt.w[r] != 0.f;
+    const float sl2 = kLog2e / sqrtf((float)D);
+    auto kern = rtp ? fwd_tile_kernel<S, D, true, true>
+                    : interp ? fwd_tile_kernel<S, D, true, false> : fwd_tile_kernel<S, D, false, false>;
+    return launch(kForward, kern, dim3(ts.tiles * (BH / ts.hs)), dim3(64 * nw), (unsigned)(fixed + per * ts.cps), s,
+                  (const S *)q, (const S *)k, (const S *)v, (S *)o, lse, T, W, rt, rtp, sl2, ts, hd, lay);
 }
 
 hipError_t launch_forward(int dtype, int D, const void *q, const void *k, const void *v, void *o,

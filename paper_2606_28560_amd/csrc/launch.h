@@ -37,6 +37,11 @@ hipError_t launch_forward(int dtype, int D, const void *q, const void *k, const 
                           float *lse, int BH, const Heads &hd, int T, int W, const RungTable &rt,
                           const RungTable *rtp, const Layouts &lay, hipStream_t s);
 
+// Tile kernels (fwd.hip, bwd.hip): query heads side by side in a workgroup of nw waves, and
+// band chunks staged at a time (tile.h).
+int tile_heads(int G, int nw);
+int tile_chunks(int nc, size_t fixed, size_t per, int slice_pieces);
+
 // Number of dalpha partials the dq kernel writes (one per workgroup).
 size_t bwd_num_partials(int dtype, int D, int BH, int T);
 

@@ -152,7 +152,7 @@ __global__ __launch_bounds__(256) void rope_bf16_d64_kernel(const uint16_t *x0, 
 RopeFreq make_rope_freq(double rope_base, int D) {
     RopeFreq rf;
     rf.on = rope_base > 0.0;
-    for (int j = 0; j < 32; ++j) rf.inv[j] = (j < D / 2 && rf.on) ? pow(rope_base, -2.0 * (double)j / (double)D) : 0.0;
+    for (int j = 0; j < 64; ++j) rf.inv[j] = (j < D / 2 && rf.on) ? pow(rope_base, -2.0 * (double)j / (double)D) : 0.0;
     return rf;
 }
 

@@ -1,0 +1,306 @@
+// Helpers of the tile kernels (fwd.hip, bwd.hip): every storage type and head size, any
+// window, on gfx950 matrix cores.
+//
+// Lane layout: a wave owns 16 consecutive rows (queries in the forward and dq kernels,
+// keys in the dk/dv kernel).  A row of D values is spread over four lanes; piece s of lane
+// g is the row's 16-byte chunk 4s + g, so each 16-byte load instruction reads 64
+// contiguous bytes of each of 16 rows.  The lane's values are its "slice", slice position
+// 4b + i being element i of accumulator block b:
+//   bfloat16: chunk 4s + g holds dims 32s + 8g + j: position 8s + j;
+//   float32:  chunk 4s + g holds dims 16s + 4g + e: position 4s + e.
+// In the MFMA layout row n is on lanes n + 16g, in the quad layout on lanes 4n + g (where
+// rows are read from global memory: neighbouring lanes read neighbouring chunks).
+// Products over the head dims take the slices as they are: v_mfma_f32_16x16x32_bf16 has
+// k index 8g + j on lane group g, v_mfma_f32_16x16x4_f32 k index g.  Products over rows
+// (P.V and the gradients) leave lane (n, g) with exactly its own slice of the output row.
+//
+// Precision: float32 rows are multiplied in float32.  bfloat16 rows are multiplied
+// exactly (bf16 products in float32 accumulators); the float32 weights they are scaled by
+// (probabilities, tau dS) are split into two bfloat16 parts, high and low (17 bits of the
+// weight), each with its own product, so no weight is rounded to 16 bits.
+#pragma once
+
+#include "mfma.h"
+
+namespace fibattn {
+
+template <typename S, int D>
+struct Tile {
+    static constexpr int kRow = D * (int)sizeof(S);  // bytes of a row
+    static constexpr int NC = kRow / 64;             // 16-byte pieces of a slice
+    static constexpr int NB = D / 16;                // accumulator blocks of a slice
+    static constexpr bool kF32 = sizeof(S) == 4;
+
+    struct Slice {
+        u32x4 c[NC];
+    };
+    struct Acc {
+        f32x4 c[NB];
+    };
+
+    __device__ static __forceinline__ void zero(Acc &a) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) a.c[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ static __forceinline__ void scale(Acc &a, float s) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) a.c[b] *= s;
+    }
+
+    // Slice g of row `row`, rows `st` bytes apart from a uniform base (the host keeps
+    // every row offset below 2^31 bytes).
+    __device__ static __forceinline__ Slice load(const void *base, int row, int g, uint32_t st) {
+        const char *p = reinterpret_cast<const char *>(base);
+        const uint32_t off = (uint32_t)row * st + (uint32_t)g * 16u;
+        Slice s;
+#pragma unroll
+        for (int x = 0; x < NC; ++x) s.c[x] = *reinterpret_cast<const u32x4 *>(p + off + 64 * x);
+        return s;
+    }
+    // The lane's slice of an output row: a.c times `scale`, rounded to S.
+    __device__ static __forceinline__ void store(void *row, int g, const Acc &a, float scale) {
+        char *p = reinterpret_cast<char *>(row) + 16 * g;
+#pragma unroll
+        for (int x = 0; x < NC; ++x) {
+            u32x4 v;
+            if constexpr (kF32) {
+                v = __builtin_bit_cast(u32x4, a.c[x] * scale);
+            } else {
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const f32x4 &h = a.c[2 * x + (w >> 1)];
+                    v[w] = pack_bf16(h[2 * (w & 1)] * scale, h[2 * (w & 1) + 1] * scale);
+                }
+            }
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(p + 64 * x));
+        }
+    }
+
+    // <x, y> over the slice, in two chains.
+    __device__ static __forceinline__ float dot(const Slice &x, const Slice &y) {
+        float s[2] = {0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float &t = s[e & 1];
+                if constexpr (kF32)
+                    t = fmaf(__uint_as_float(x.c[c][e]), __uint_as_float(y.c[c][e]), t);
+                else
+                    t = __builtin_amdgcn_fdot2_f32_bf16(as_bf2(x.c[c][e]), as_bf2(y.c[c][e]), t, false);
+            }
+        return s[0] + s[1];
+    }
+
+    // acc += a x + b y with float32 weights.
+    __device__ static __forceinline__ void axpy2(Acc &acc, float a, const Slice &x, float b, const Slice &y) {
+        if constexpr (kF32) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc.c[c][e] = fmaf(a, __uint_as_float(x.c[c][e]),
+                                       fmaf(b, __uint_as_float(y.c[c][e]), acc.c[c][e]));
+        } else {
+            const uint32_t h = pack_bf16(a, b);
+            const uint32_t l = pack_bf16(a - bf16_lo(h), b - bf16_hi(h));
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    // pairs (x_d, y_d) of the word's two dims
+                    const uint32_t lo = __builtin_amdgcn_perm(y.c[c][w], x.c[c][w], 0x05040100u);
+                    const uint32_t hi = __builtin_amdgcn_perm(y.c[c][w], x.c[c][w], 0x07060302u);
+                    f32x4 &d = acc.c[2 * c + (w >> 1)];
+                    const int e = 2 * (w & 1);
+                    d[e] = __builtin_amdgcn_fdot2_f32_bf16(as_bf2(lo), as_bf2(l), d[e], false);
+                    d[e + 1] = __builtin_amdgcn_fdot2_f32_bf16(as_bf2(hi), as_bf2(l), d[e + 1], false);
+                    d[e] = __builtin_amdgcn_fdot2_f32_bf16(as_bf2(lo), as_bf2(h), d[e], false);
+                    d[e + 1] = __builtin_amdgcn_fdot2_f32_bf16(as_bf2(hi), as_bf2(h), d[e + 1], false);
+                }
+        }
+    }
+    // acc += a x.
+    __device__ static __forceinline__ void axpy(Acc &acc, float a, const Slice &x) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                if constexpr (kF32) {
+                    acc.c[c][w] = fmaf(a, __uint_as_float(x.c[c][w]), acc.c[c][w]);
+                } else {
+                    f32x4 &d = acc.c[2 * c + (w >> 1)];
+                    const int e = 2 * (w & 1);
+                    d[e] = fmaf(a, bf16_lo(x.c[c][w]), d[e]);
+                    d[e + 1] = fmaf(a, bf16_hi(x.c[c][w]), d[e + 1]);
+                }
+            }
+    }
+
+    // A quad-layout slice moved to the MFMA layout, and an accumulator or a value moved
+    // from the MFMA to the quad layout.
+    __device__ static __forceinline__ Slice from_quad(const Slice &x, int lane) {
+        const int src = 4 * (lane & 15) + (lane >> 4);
+        Slice y;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y.c[c][e] = __shfl(x.c[c][e], src, 64);
+        return y;
+    }
+    __device__ static __forceinline__ void to_quad_acc(Acc &a, int lane) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a.c[b][e] = to_quad(a.c[b][e], lane);
+    }
+
+    // ---- rows staged in LDS -----------------------------------------------------------
+    // Row-major, 16-byte chunk c of staged row r in slot c ^ swz(r), so that eight lanes
+    // reading one chunk of consecutive rows cover the banks.
+    __device__ static __forceinline__ int swz(int r) { return kRow == 64 ? (r >> 1) & 3 : r & 7; }
+    __device__ static __forceinline__ const char *chunk(const char *buf, int r, int c) {
+        return buf + r * kRow + 16 * (c ^ swz(r));
+    }
+    __device__ static __forceinline__ Slice staged(const char *buf, int r, int g) {
+        Slice s;
+#pragma unroll
+        for (int x = 0; x < NC; ++x) s.c[x] = *reinterpret_cast<const u32x4 *>(chunk(buf, r, 4 * x + g));
+        return s;
+    }
+    // Rows [r_begin, r_begin + nrows) of rows `st` elements apart, copied by direct-to-LDS
+    // loads (1 KB per wave and instruction; nrows is a multiple of 16).  Rows outside [0, T)
+    // are clamped copies of real rows: callers mask them.
+    __device__ static __forceinline__ void stage(char *buf, const S *X, int r_begin, int nrows, int T, long long st,
+                                                 int wave, int nwaves) {
+        const int lane = threadIdx.x & 63;
+        constexpr int per = kRow / 16;  // chunks per row
+        const int nblk = nrows * kRow / 1024;
+        for (int blk = wave; blk < nblk; blk += nwaves) {
+            const int u = blk * 64 + lane;
+            const int rr = u / per, ch = (u % per) ^ swz(rr);
+            const int row = min(max(r_begin + rr, 0), T - 1);
+            __builtin_amdgcn_global_load_lds(X + row * st + ch * (16 / (int)sizeof(S)),
+                                             (__attribute__((address_space(3))) void *)(buf + 1024 * blk), 16, 0, 0);
+        }
+    }
+
+    // ---- matrix products --------------------------------------------------------------
+    // <rows a, columns b> over the head dims, 16 x 16.
+    __device__ static __forceinline__ f32x4 scores(const Slice &a, const Slice &b) {
+        f32x4 r{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if constexpr (kF32) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    r = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.c[c][e]), __uint_as_float(b.c[c][e]), r,
+                                                             0, 0, 0);
+            } else {
+                r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.c[c]),
+                                                            __builtin_bit_cast(bf16x8, b.c[c]), r, 0, 0, 0);
+            }
+        }
+        return r;
+    }
+    // Weights of a 32-row chunk (two 16-row blocks of C-layout weights, p[4b + e] for row
+    // 16b + 4g + e and the lane's column), as matrix operands.
+    struct Weights {
+        u32x4 h, l;   // bfloat16: high and low parts
+        float f[8];   // float32
+    };
+    __device__ static __forceinline__ Weights weights(const float *p) {
+        Weights w;
+        if constexpr (kF32) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) w.f[e] = p[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                w.h[e] = pack_bf16(p[2 * e], p[2 * e + 1]);
+                w.l[e] = pack_bf16(p[2 * e] - bf16_lo(w.h[e]), p[2 * e + 1] - bf16_hi(w.h[e]));
+            }
+        }
+        return w;
+    }
+    // acc += rows^T . w over the staged rows [base, base + 32) (MFMA layout).
+    __device__ static __forceinline__ void accumulate(Acc &acc, const char *buf, int base, const Weights &w, int g) {
+        const int m = threadIdx.x & 15;
+        if constexpr (kF32) {
+            // A operand of step (block h, e): dim 16b + m of row base + 16h + 4g + e
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = base + 16 * h + 4 * g + e;
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        const float a = *reinterpret_cast<const float *>(chunk(buf, r, 4 * b + (m >> 2)) + 4 * (m & 3));
+                        acc.c[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w.f[4 * h + e], acc.c[b], 0, 0, 0);
+                    }
+                }
+        } else {
+            // A operand by LDS transpose reads (lane addressing as dma_operand_t)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                v4i16 t[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int r = base + 16 * h + 4 * g + (m >> 2);
+                    t[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                        (__attribute__((address_space(3))) v4i16 *)(chunk(buf, r, 4 * (b >> 1) + (m & 3)) + 8 * (b & 1)));
+                }
+                const bf16x8 A = __builtin_bit_cast(bf16x8, t);
+                acc.c[b] = mfma(A, __builtin_bit_cast(bf16x8, w.l), acc.c[b]);
+                acc.c[b] = mfma(A, __builtin_bit_cast(bf16x8, w.h), acc.c[b]);
+            }
+        }
+    }
+
+    // R^T (the inverse RoPE rotation) of the lane's slice at position t.  sf: revolutions
+    // per position of every frequency.  The partner of dim d < D/2 is d + D/2: D/8 slice
+    // positions on, except for bfloat16 rows of 32, whose partner lanes are g and g + 2.
+    __device__ static __forceinline__ void rope_t(Acc &a, int t, const double *sf, int g) {
+        if constexpr (!kF32 && D == 32) {
+            const bool hi = g & 2;  // this lane holds the second halves of its pairs
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                float c, s;
+                rope_cs_rev(t, sf[8 * (g & 1) + p], c, s);
+                const float x = a.c[p >> 2][p & 3];
+                const float o = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xF, 0xF, true));
+                a.c[p >> 2][p & 3] = hi ? x * c - o * s : x * c + o * s;
+            }
+        } else {
+            constexpr int HB = NB / 2;
+#pragma unroll
+            for (int b = 0; b < HB; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int p = 4 * b + e;
+                    const int dim = kF32 ? 16 * b + 4 * g + e : 32 * (p >> 3) + 8 * g + (p & 7);
+                    float c, s;
+                    if constexpr (kF32)
+                        rope_cs_f32(t, sf[dim], c, s);
+                    else
+                        rope_cs_rev(t, sf[dim], c, s);
+                    const float x = a.c[b][e], y = a.c[HB + b][e];
+                    a.c[b][e] = x * c + y * s;
+                    a.c[HB + b][e] = y * c - x * s;
+                }
+        }
+    }
+};
+
+// Weight and lane bookkeeping of a launch: `nw` waves per workgroup are `hs` query heads
+// of one group (all reading the same rows) times nw / hs runs of 16 rows.
+struct TileShape {
+    int tiles;  // workgroups along the sequence
+    int hs;     // query heads side by side
+    int nc;     // 32-row band chunks: they cover W + 16 rows
+    int cps;    // chunks staged at a time
+};
+
+inline int band_chunks(int W) { return (W + 16 + 31) / 32; }
+
+}  // namespace fibattn

@@ -1,0 +1,72 @@
+"""GPU parity of the tile kernels (every shape outside the bfloat16, d_head 64, W <= 16
+path) where they can go wrong: windows at the edges of the 32-row band chunks and of the
+chunks staged together, lengths around the 16- and 64-row tiles, each storage type and head
+size (the float32 d_head 128 launch has two waves per workgroup), one, two, three and four
+query heads side by side, more rungs than a wave has row groups, and strided placements."""
+import pytest
+import torch
+
+from paper_2606_28560_amd import fibattn as F
+from paper_2606_28560_amd import inputs, schedules
+from tests.parity import compare, gpu_run, oracle_run
+
+pytestmark = pytest.mark.gpu
+
+FIB, POW2 = schedules.FIB15, schedules.POW2_11
+MANY = list(range(3, 99, 3))  # K = 32
+
+CASES = [
+    # (B, H, H_kv, T, D, dtype, W, base, alpha)
+    (1, 2, 2, 200, 64, "bf16", 17, FIB, 1.1),     # first window past the 32-row chunk
+    (1, 2, 2, 200, 64, "bf16", 48, FIB, 1.0),     # two chunks exactly
+    (1, 2, 2, 333, 64, "bf16", 49, FIB, 1.3),     # three, and a ragged tail
+    (1, 8, 2, 333, 64, "bf16", 112, POW2, 0.9),   # four chunks, four heads side by side
+    (1, 2, 2, 333, 64, "bf16", 113, FIB, 1.0),    # five chunks, in two stages
+    (1, 2, 2, 100, 64, "bf16", 128, FIB, 1.0),    # a window longer than the sequence
+    (2, 4, 2, 129, 128, "bf16", 16, FIB, 0.85),   # two heads side by side
+    (1, 3, 1, 257, 128, "bf16", 33, FIB, 1.0),    # a group of three
+    (1, 2, 2, 65, 128, "bf16", 128, FIB, 0.7),
+    (2, 2, 2, 127, 32, "bf16", 16, POW2, 1.3),
+    (1, 4, 1, 200, 32, "bf16", 64, FIB, 1.0),
+    (1, 2, 2, 200, 32, "bf16", 0, MANY, 0.9),     # 32 rungs
+    (1, 2, 2, 200, 64, "fp32", 16, MANY, 1.0),
+    (1, 2, 1, 130, 32, "fp32", 17, FIB, 0.9),
+    (1, 4, 2, 97, 128, "fp32", 8, FIB, 1.2),      # two waves per workgroup
+    (1, 3, 3, 33, 128, "fp32", 128, FIB, 1.0),
+    (1, 1, 1, 1, 128, "fp32", 8, FIB, 1.0),
+    (1, 1, 1, 15, 128, "bf16", 0, FIB, 0.9),
+    (1, 2, 2, 2, 32, "fp32", 1, FIB, 0.5),        # rungs at d = 1.5 and beyond, T = 2
+    (3, 2, 2, 64, 32, "bf16", 12, [], 1.0),       # no rungs
+]
+
+
+@pytest.mark.parametrize("B,H,Hkv,T,D,dtype,W,base,alpha", CASES)
+def test_tile_parity(B, H, Hkv, T, D, dtype, W, base, alpha):
+    idx = CASES.index((B, H, Hkv, T, D, dtype, W, base, alpha))
+    print(f"tile case {idx}: B{B} H{H}/{Hkv} T{T} D{D} {dtype} W{W} K{len(base)} alpha={alpha}", flush=True)
+    x = inputs.attention_inputs(B, H, T, D, dtype, 800 + idx, 0, names=("q", "dO"))
+    x.update(inputs.attention_inputs(B, Hkv, T, D, dtype, 800 + idx, 0, names=("k", "v")))
+    got = gpu_run(x["q"], x["k"], x["v"], x["dO"], W, base, alpha)
+    ref = oracle_run(x["q"], x["k"], x["v"], x["dO"], W, base, alpha)
+    print(compare(got, ref, dtype, f"tile case {idx}"), flush=True)
+
+
+@pytest.mark.parametrize("D,dtype,W", [(64, "bf16", 40), (128, "bf16", 8), (32, "bf16", 12), (64, "fp32", 8)])
+def test_tile_strides(D, dtype, W):
+    # slices of one [B,T,3,H,D] buffer with poisoned gaps give the packed call's bits
+    B, H, T = 2, 3, 150
+    x = inputs.attention_inputs(B, H, T, D, dtype, 850, 0)
+    packed = {n: x[n].cuda() for n in ("q", "k", "v")}
+    dt = packed["q"].dtype
+    buf = torch.full((B, T, 3, H, D + 16), float("nan"), device="cuda", dtype=dt)
+    views = {}
+    for n, name in enumerate(("q", "k", "v")):
+        views[name] = buf[:, :, n, :, :D].transpose(1, 2)
+        views[name].copy_(packed[name])
+    want, want_lse = F.fibattn_forward(packed["q"], packed["k"], packed["v"], W, FIB, 0.9)
+    out = torch.full((B, T, H, D + 16), float("nan"), device="cuda", dtype=dt)
+    got, lse = F.fibattn_forward(views["q"], views["k"], views["v"], W, FIB, 0.9,
+                                 o=out[..., :D].transpose(1, 2))
+    torch.cuda.synchronize()
+    assert torch.equal(got.contiguous(), want) and torch.equal(lse, want_lse)
+    assert torch.isnan(out[..., D:]).all()
