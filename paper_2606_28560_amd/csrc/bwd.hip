@@ -25,112 +25,228 @@
 // The dk/dv kernel therefore owns one key row per lane group and gathers its
 // contributions, so every dk/dv row is written once, without atomics.
 #include "launch.h"
+#include "tile.h"
 
 namespace fibattn {
 
 // ---------------------------------------------------------------------------
 // dq, Delta and per-workgroup dalpha partials.
 // ---------------------------------------------------------------------------
+// A wave owns 16 consecutive queries (lane layouts in tile.h), as in the forward: the band
+// chunks' K and V rows are staged in LDS, S = K.Q^T and dP = V.dO^T taken on the matrix
+// cores, dq += K^T (tau dS) there; rungs are dot products of the rows r0 and r1 (r1 is
+// needed for dalpha even when w = 0) on the VALU, four lanes per row.  The dalpha parts are
+// float32 products added up in float64.
+//
+// What bounds it: as the forward, the latency of the rung gathers and their VALU work.
+// Against a kernel with one lane group per query, every row read from global memory by
+// every query (us a launch, interpolating): bf16 d 64 B4 H8 T2048 W64 135 -> 22.9; bf16
+// d 128 B2 H16 on 4 T2000 W8 82 -> 37; bf16 d 32 B8 H8 T1024 W10 23.6 -> 15.4; fp32 d 64 B4
+// H8 T1024 W12 37 -> 23.5 (the R^T of dq, then a launch of its own, included).
+template <typename S, int D>
+constexpr int dq_waves = Tile<S, D>::NC <= 2 ? 4 : Tile<S, D>::NC == 4 ? 3 : 2;
+
 // DEV: the rung table is the one at rtp, built on the device (rt_arg unused).
-template <typename S, int D, bool DEV>
-__global__ __launch_bounds__(256) void bwd_dq_kernel(
+template <typename S, int D, bool INTERP, bool DEV>
+__global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
     const S *__restrict__ q, const S *__restrict__ k, const S *__restrict__ v,
     const S *__restrict__ o, const float *__restrict__ lse, const S *__restrict__ dO,
     S *__restrict__ dq, float *__restrict__ delta_out, double *__restrict__ partials, int T,
-    int W, RungTable rt_arg, const RungTable *__restrict__ rtp, float tau, Heads hd, Layouts lay) {
+    int W, RungTable rt_arg, const RungTable *__restrict__ rtp, RopeFreq rf, float tau, float sl2, TileShape ts, Heads hd,
+    Layouts lay) {
+    using TL = Tile<S, D>;
+    using Slice = typename TL::Slice;
     const RungTable &rt = DEV ? *rtp : rt_arg;
     const bool bad = DEV && table_unusable(rt, W);  // bad device alpha, or another W
-    constexpr int VN = Vec<S>::N;
-    constexpr int LPQ = D / VN;
-    constexpr int QPB = 256 / LPQ;
-    __shared__ double red[256];
+    constexpr int NBUF = TL::NC <= 1 ? 2 : 1;       // rungs in flight
+    extern __shared__ __align__(16) char smem[];
+    __shared__ double sfreq[D / 2], red[4];
 
-    const int g = threadIdx.x / LPQ;
-    const int sub = threadIdx.x % LPQ;
-    const int i = blockIdx.x * QPB + g;
-    const int bk = hd.kv_of(blockIdx.y);
-    const S *Q = q + lay.q.head(blockIdx.y, hd.H);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nw = blockDim.x >> 6;
+    const int nm = lane & 15, gm = lane >> 4;  // MFMA layout
+    const int nq = lane >> 2, gq = lane & 3;   // quad layout
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int runs = nw / ts.hs, wv = wave / ts.hs;
+    const int bh = (blk / ts.tiles) * ts.hs + wave % ts.hs;  // this wave's query head
+    const int T0 = (blk % ts.tiles) * 16 * runs;
+    const int bk = hd.kv_of(bh);
     const S *K = k + lay.k.head(bk, hd.kv_heads());
     const S *V = v + lay.v.head(bk, hd.kv_heads());
-    const long long sq = lay.q.st, sk = lay.k.st, sv = lay.v.st;  // row strides
-    const int col = sub * VN;
-    const float sl2 = tau * kLog2e;
+    constexpr int es = (int)sizeof(S);
+    const uint32_t sk = (uint32_t)(lay.k.st * es), sv = (uint32_t)(lay.v.st * es);
 
-    double dal = 0.0;
-    if (i < T) {
-        float qv[VN], gv[VN], kv[VN], vv[VN], acc[VN];
-        Vec<S>::load(Q + i * sq + col, qv);
-        Vec<S>::load(dO + lay.g.head(blockIdx.y, hd.H) + i * lay.g.st + col, gv);
-        Vec<S>::load(o + lay.o.head(blockIdx.y, hd.H) + i * lay.o.st + col, kv);
-        const float delta = group_sum<LPQ>(dot<VN>(gv, kv));
-        if (sub == 0) delta_out[(size_t)blockIdx.y * T + i] = bad ? NAN : delta;
-        const float lse2 = lse[(size_t)blockIdx.y * T + i] * kLog2e;
-#pragma unroll
-        for (int c = 0; c < VN; ++c) acc[c] = 0.f;
+    const int t0 = T0 + 16 * wv;
+    const int im = t0 + nm;                     // MFMA layout query
+    const int i = t0 + nq, ic = min(i, T - 1);  // quad layout query
+    const S *Q = q + lay.q.head(bh, hd.H), *G = dO + lay.g.head(bh, hd.H);
+    Slice qq = TL::load(Q, ic, gq, (uint32_t)(lay.q.st * es));
+    Slice gg = TL::load(G, ic, gq, (uint32_t)(lay.g.st * es));
+    const float lse2 = lse[(size_t)bh * T + ic] * kLog2e;
+    float delta;
+    {
+        const Slice oo = TL::load(o + lay.o.head(bh, hd.H), ic, gq, (uint32_t)(lay.o.st * es));
+        delta = quad_sum(TL::dot(gg, oo));
+    }
+    if (rf.on && threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
 
-        double xa = 0.0, xb = 0.0, y = 0.0, dsum = 0.0;  // dalpha parts, Delta from the entries
-        const int wmax = min(W, i);
-        for (int d = 0; d <= wmax; ++d) {
-            Vec<S>::load(K + (i - d) * sk + col, kv);
-            Vec<S>::load(V + (i - d) * sv + col, vv);
-            const float s = group_sum<LPQ>(dot<VN>(qv, kv));
-            const float dP = group_sum<LPQ>(dot<VN>(gv, vv));
-            const float p = exp2f(s * sl2 - lse2);
-            const float c = tau * p * (dP - delta);
-            dsum += (double)p * (double)dP;
+    int nact = 0;  // rungs some query of this wave includes: a prefix of the table
 #pragma unroll
-            for (int x = 0; x < VN; ++x) acc[x] = fmaf(c, kv[x], acc[x]);
-        }
-        for (int r = 0; r < rt.n; ++r) {
-            const int d0 = rt.d0[r];
-            const float w = rt.w[r];
-            if (!(d0 < i || (d0 == i && w == 0.f))) break;
-            const int r0 = i - d0;
-            float k1[VN], v1[VN];
-            Vec<S>::load(K + r0 * sk + col, kv);
-            Vec<S>::load(V + r0 * sv + col, vv);
-            if (r0 >= 1) {
-                Vec<S>::load(K + (r0 - 1) * sk + col, k1);
-                Vec<S>::load(V + (r0 - 1) * sv + col, v1);
-            } else {
+    for (int r = 0; r < kMaxRungs; ++r) nact += ((r < rt.n) & (rt.d0[r] <= min(t0 + 15, T - 1))) ? 1 : 0;
+    nact = t0 < T ? __builtin_amdgcn_readfirstlane(nact) : 0;
+    // rows r0 and r1 of rung r
+    auto load_rung = [&](int r, const void *X, uint32_t st, Slice *x) {
+        const int d = rt.d0[r];
+        x[0] = TL::load(X, max(ic - d, 0), gq, st);
+        x[1] = TL::load(X, max(ic - d - 1, 0), gq, st);
+    };
+    Slice kx[NBUF][2], vx[NBUF][2];
+    // in flight during the band phase, as far as the registers go
+    if (TL::NC <= 2 && nact > 0) load_rung(0, V, sv, vx[0]);
+    if (TL::NC <= 1 && nact > 0) load_rung(0, K, sk, kx[0]);
+
+    // ---- window band (MFMA layout) ----
+    typename TL::Acc acc;
+    TL::zero(acc);
+    // the entries' sums of p dP and of p (this lane's parts).  The latter is 1 up to the
+    // rounding of lse and its conversion to base 2, which scales every p of a query alike:
+    // the results are divided by it.
+    double dsum = 0.0, psum = 0.0;
+    {
+        const Slice qm = TL::from_quad(qq, lane), gmm = TL::from_quad(gg, lane);
+        const float lse2_m = __shfl(lse2, 4 * nm, 64), delta_m = __shfl(delta, 4 * nm, 64);
+        const unsigned reach = (unsigned)min(W, im);  // 0 <= im - key <= W and key >= 0
+        for (int c0 = 0; c0 < ts.nc; c0 += ts.cps) {
+            // chunks as in the forward
+            const int n = min(ts.cps, ts.nc - c0);
+            const int rbeg = T0 + 16 - 32 * (c0 + n), rows = 16 * (runs - 1) + 32 * n;
+            char *kr = smem, *vr = smem + rows * TL::kRow;
+            if (c0 > 0) __syncthreads();  // every wave is done with the rows staged before
+            TL::stage(kr, K, rbeg, rows, T, lay.k.st, wave, nw);
+            TL::stage(vr, V, rbeg, rows, T, lay.v.st, wave, nw);
+            wait_vmem();
+            __syncthreads();
+            for (int c = 0; c < n; ++c) {
+                const int base = 16 * wv + 32 * (n - 1 - c);
+                float ds[8], pd = 0.f, ps = 0.f;
 #pragma unroll
-                for (int x = 0; x < VN; ++x) { k1[x] = 0.f; v1[x] = 0.f; }
+                for (int b = 0; b < 2; ++b) {
+                    const f32x4 s = TL::scores(TL::staged(kr, base + 16 * b + nm, gm), qm);
+                    const f32x4 dp = TL::scores(TL::staged(vr, base + 16 * b + nm, gm), gmm);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int key = rbeg + base + 16 * b + 4 * gm + e;
+                        const float p = (unsigned)(im - key) <= reach ? fast_exp2(fmaf(s[e], sl2, -lse2_m)) : 0.f;
+                        ds[4 * b + e] = tau * p * (dp[e] - delta_m);
+                        pd = fmaf(p, dp[e], pd);
+                        ps += p;
+                    }
+                }
+                dsum += (double)pd;
+                psum += (double)ps;
+                TL::accumulate(acc, kr, base, TL::weights(ds), gm);
             }
-            const float s0 = group_sum<LPQ>(dot<VN>(qv, kv));
-            const float s1 = group_sum<LPQ>(dot<VN>(qv, k1));
-            const float dP0 = group_sum<LPQ>(dot<VN>(gv, vv));
-            const float dP1 = group_sum<LPQ>(dot<VN>(gv, v1));
-            const float s = (1.f - w) * s0 + w * s1;
-            const float dP = (1.f - w) * dP0 + w * dP1;
-            const float p = exp2f(s * sl2 - lse2);
-            const float dS = p * (dP - delta);
-            const float c = tau * dS;
-            const float c0 = c * (1.f - w);
-            const float c1 = c * w;
-#pragma unroll
-            for (int x = 0; x < VN; ++x) acc[x] = fmaf(c0, kv[x], fmaf(c1, k1[x], acc[x]));
-            const double fp = (double)rt.f[r] * (double)p;
-            xa += fp * (double)dP * (double)(s1 - s0);
-            xb += fp * (double)(dP1 - dP0);
-            y += fp * (double)(s1 - s0);
-            dsum += (double)p * (double)dP;
         }
-        dal = (double)tau * (xa - dsum * y) + xb;
-        if (bad) {
-#pragma unroll
-            for (int x = 0; x < VN; ++x) acc[x] = NAN;
-            dal = NAN;
-        }
-        Vec<S>::store(dq + lay.dq.head(blockIdx.y, hd.H) + i * lay.dq.st + col, acc);
     }
-    red[threadIdx.x] = (sub == 0 && i < T) ? dal : 0.0;
+    if constexpr (TL::NC > 2) {
+        // wide rows: read again rather than held through the band phase (which would spill)
+        int row = ic;
+        asm volatile("" : "+v"(row));
+        qq = TL::load(Q, row, gq, (uint32_t)(lay.q.st * es));
+        gg = TL::load(G, row, gq, (uint32_t)(lay.g.st * es));
+    }
+    if (nact > 0) {
+        if (TL::NC > 2) load_rung(0, V, sv, vx[0]);
+        if (TL::NC > 1) load_rung(0, K, sk, kx[0]);
+    }
+    TL::to_quad_acc(acc, lane);
+    // the query's band sums, on each of its four quad lanes
+    auto band_sum = [&](double x) {
+        x += __shfl_xor(x, 16, 64);
+        x += __shfl_xor(x, 32, 64);
+        return __shfl(x, nq, 64);
+    };
+    dsum = band_sum(dsum);
+    psum = band_sum(psum);
+
+    // ---- rungs (quad layout); row r1 = -1 is the zero row ----
+    // xa, xb, y: this lane's parts of the sums over <q, k[r1]-k[r0]> and <dO, v[r1]-v[r0]>
+    double xa = 0.0, xb = 0.0, y = 0.0;
+    float dP = 0.f, dv = 0.f;
+    auto value_dots = [&](int r, const Slice *x) {
+        const bool has1 = i - rt.d0[r] - 1 >= 0;
+        const float w = rt.w[r];
+        const float a = TL::dot(gg, x[0]), t = TL::dot(gg, x[1]), b = has1 ? t : 0.f;
+        dv = b - a;
+        dP = quad_sum(INTERP ? (1.f - w) * a + w * b : a);
+    };
+    auto key_terms = [&](int r, const Slice *x) {
+        const int d0 = rt.d0[r];
+        const float w = rt.w[r];
+        const bool in = i < T && (INTERP ? d0 < i || (d0 == i && w == 0.f) : d0 <= i);
+        const float a = TL::dot(qq, x[0]), t = TL::dot(qq, x[1]), b = i - d0 - 1 >= 0 ? t : 0.f;
+        const float s = quad_sum(INTERP ? (1.f - w) * a + w * b : a);
+        const float p = in ? fast_exp2(fmaf(s, sl2, -lse2)) : 0.f;
+        const float c = tau * p * (dP - delta);
+        if constexpr (INTERP)
+            TL::axpy2(acc, c * (1.f - w), x[0], c * w, x[1]);
+        else
+            TL::axpy(acc, c, x[0]);
+        const float fp = (float)rt.f[r] * p;
+        const double ds = (double)(b - a);
+        xa = fma((double)(fp * dP), ds, xa);
+        xb = fma((double)fp, (double)dv, xb);
+        y = fma((double)fp, ds, y);
+        dsum += (double)(p * dP);
+        psum += (double)p;
+    };
+    if constexpr (NBUF == 2) {
+        for (int r = 0; r < nact; r += 2) {
+            if (r + 1 < nact) {
+                load_rung(r + 1, V, sv, vx[1]);
+                load_rung(r + 1, K, sk, kx[1]);
+            }
+            value_dots(r, vx[0]);
+            key_terms(r, kx[0]);
+            if (r + 1 < nact) {
+                if (r + 2 < nact) {
+                    load_rung(r + 2, V, sv, vx[0]);
+                    load_rung(r + 2, K, sk, kx[0]);
+                }
+                value_dots(r + 1, vx[1]);
+                key_terms(r + 1, kx[1]);
+            }
+        }
+    } else {
+        // one buffer each: the next rung's values load while this one's keys are used
+        for (int r = 0; r < nact; ++r) {
+            const int nx = min(r + 1, nact - 1);
+            value_dots(r, vx[0]);
+            load_rung(nx, V, sv, vx[0]);
+            key_terms(r, kx[0]);
+            load_rung(nx, K, sk, kx[0]);
+        }
+    }
+
+    const double inv = i < T ? 1.0 / psum : 0.0;
+    if (rf.on) TL::rope_t(acc, i, sfreq, gq);  // gradient w.r.t. the unrotated q
+    if (i < T) {
+        TL::store(dq + lay.dq.head(bh, hd.H) + i * lay.dq.st, gq, acc, bad ? NAN : (float)inv);
+        if (gq == 0) delta_out[(size_t)bh * T + i] = bad ? NAN : delta;
+    }
+    // this lane's part of the query's dalpha; wave sums, then the waves in order
+    double dal = inv * ((double)tau * (xa - inv * dsum * y) + xb);
+    if (bad) dal = NAN;
+#pragma unroll
+    for (int st = 32; st >= 1; st >>= 1) dal += __shfl_xor(dal, st, 64);
+    if (lane == 0) red[wave] = dal;
     __syncthreads();
-#pragma unroll
-    for (int st = 128; st >= 1; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = red[0];
+        for (int u = 1; u < nw; ++u) s += red[u];
+        partials[blockIdx.x] = s;
     }
-    if (threadIdx.x == 0) partials[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = red[0];
 }
 
 // ---------------------------------------------------------------------------
@@ -293,31 +409,45 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
                                const float *lse, const void *dO, void *dq, void *dk, void *dv,
                                float *dalpha, float *dtheta, float *delta_ws, double *partials, int BH,
                                const Heads &hd, int T, int W, const RungTable &rt,
-                               const RungTable *rtp, const Layouts &lay, hipStream_t s) {
+                               const RungTable *rtp, const RopeFreq &rf, const Layouts &lay, hipStream_t s) {
+    using TL = Tile<S, D>;
     constexpr int QPB = 256 / (D / Vec<S>::N);
+    constexpr int nw = TL::kRow == 512 ? 2 : 4;  // as the forward
     const float tau = 1.f / sqrtf((float)D);
-    dim3 grid((T + QPB - 1) / QPB, BH);
-    hipError_t e = launch(kBwdDq, rtp ? bwd_dq_kernel<S, D, true> : bwd_dq_kernel<S, D, false>, grid,
-                          dim3(256), 0, s, (const S *)q, (const S *)k, (const S *)v, (const S *)o,
-                          lse, (const S *)dO, (S *)dq, delta_ws, partials, T, W, rt, rtp, tau, hd, lay);
+    TileShape ts;
+    ts.hs = tile_heads(hd.G, nw);
+    const int runs = nw / ts.hs;
+    ts.tiles = (T + 16 * runs - 1) / (16 * runs);
+    ts.nc = band_chunks(W);
+    const size_t fixed = 2 * (size_t)16 * (runs - 1) * TL::kRow, per = 2 * (size_t)32 * TL::kRow;
+    ts.cps = tile_chunks(ts.nc, fixed, per, TL::NC);
+    const int nb = ts.tiles * (BH / ts.hs);  // dq workgroups = dalpha partials
+    bool interp = false;
+    for (int r = 0; r < rt.n && !interp; ++r) interp = rt.w[r] != 0.f;
+    auto dqk = rtp ? bwd_dq_tile_kernel<S, D, true, true>
+                   : interp ? bwd_dq_tile_kernel<S, D, true, false> : bwd_dq_tile_kernel<S, D, false, false>;
+    hipError_t e = launch(kBwdDq, dqk, dim3(nb), dim3(64 * nw), (unsigned)(fixed + per * ts.cps), s, (const S *)q,
+                          (const S *)k, (const S *)v, (const S *)o, lse, (const S *)dO, (S *)dq, delta_ws, partials,
+                          T, W, rt, rtp, rf, tau, kLog2e / sqrtf((float)D), ts, hd, lay);
     if (e != hipSuccess) return e;
+    dim3 grid((T + QPB - 1) / QPB, BH);
     e = launch(kBwdDkDv, rtp ? bwd_dkdv_kernel<S, D, true> : bwd_dkdv_kernel<S, D, false>,
                dim3(grid.x, BH / hd.G), dim3(256), 0, s, (const S *)q, (const S *)k, (const S *)v,
                lse, (const S *)dO, delta_ws, (S *)dk, (S *)dv, T, W, rt, rtp, tau, hd, lay);
     if (e != hipSuccess) return e;
     return launch(kDalphaReduce, dalpha_reduce_kernel, dim3(1), dim3(256), 0, s, partials,
-                  (size_t)grid.x * grid.y, dalpha, dtheta, rtp);
+                  (size_t)nb, dalpha, dtheta, rtp);
 }
 
 static hipError_t launch_backward_generic(int dtype, int D, const void *q, const void *k, const void *v,
                                           const void *o, const float *lse, const void *dO, void *dq,
                                           void *dk, void *dv, float *dalpha, float *dtheta, float *delta_ws,
                                           double *partials, int BH, const Heads &hd, int T, int W,
-                                          const RungTable &rt, const RungTable *rtp, const Layouts &lay,
-                                          hipStream_t s) {
+                                          const RungTable &rt, const RungTable *rtp, const RopeFreq &rf,
+                                          const Layouts &lay, hipStream_t s) {
 #define FIBATTN_BWD(S_, D_)                                                                  \
     return launch_bwd_t<S_, D_>(q, k, v, o, lse, dO, dq, dk, dv, dalpha, dtheta, delta_ws, partials, \
-                                BH, hd, T, W, rt, rtp, lay, s)
+                                BH, hd, T, W, rt, rtp, rf, lay, s)
     if (dtype == 0 && D == 32) FIBATTN_BWD(float, 32);
     if (dtype == 0 && D == 64) FIBATTN_BWD(float, 64);
     if (dtype == 1 && D == 32) FIBATTN_BWD(uint16_t, 32);
@@ -339,13 +469,12 @@ hipError_t launch_backward(int dtype, int D, const void *q, const void *k, const
         return launch_backward_mfma(q, k, v, o, lse, dO, dq, dk, dv, dalpha, dtheta, delta_ws, partials,
                                     terms, BH, hd, T, W, rt, rtp, rf, lay, s);
     hipError_t e = launch_backward_generic(dtype, D, q, k, v, o, lse, dO, dq, dk, dv, dalpha, dtheta, delta_ws,
-                                           partials, BH, hd, T, W, rt, rtp, lay, s);
-    // R^T on dq and dk in place: gradients w.r.t. the unrotated q, k (R^T is linear, so
-    // it also carries the group sum in dk)
-    if (e == hipSuccess && rf.on) {
-        e = launch_rope(dtype, D, dq, dq, lay.dq, lay.dq, dk, dk, lay.dk, lay.dk, BH, hd.H, T, rope_base, 1,
-                        s, BH / hd.G, hd.kv_heads());
-    }
+                                           partials, BH, hd, T, W, rt, rtp, rf, lay, s);
+    // R^T on dk in place: the gradient w.r.t. the unrotated k (R^T is linear, so it also
+    // carries the group sum)
+    if (e == hipSuccess && rf.on)
+        e = launch_rope(dtype, D, dk, dk, lay.dk, lay.dk, nullptr, nullptr, lay.dk, lay.dk, BH / hd.G, hd.kv_heads(),
+                        T, rope_base, 1, s);
     return e;
 }
 

@@ -112,15 +112,15 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
             float p[8], mx = -INFINITY;
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
-                const f32x4 s = TL::scores(TL::staged(kr, base + 16 * b + nm, gm), qm);
+                const f32x4 s = TL::template scores<TL::NC == 8 ? 8 : 4>(TL::staged(kr, base + 16 * b + nm, gm), qm);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int key = rbeg + base + 16 * b + 4 * gm + e;
-                    p[4 * b + e] = (unsigned)(im - key) <= reach ? s[e] * sl2 : -INFINITY;
+                    p[4 * b + e] = (unsigned)(im - key) <= reach ? s[e] : -INFINITY;
                     mx = fmaxf(mx, p[4 * b + e]);
                 }
             }
-            mx = max4(mx);
+            mx = max4(mx) * sl2;
             if (c0 + c == 0) {
                 m = mx;  // finite: the first chunk holds key im itself
             } else if (__builtin_amdgcn_ballot_w64(mx > m)) {
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                p[e] = fast_exp2(p[e] - m);
+                p[e] = fast_exp2(fmaf(p[e], sl2, -m));
                 l += p[e];
             }
             TL::accumulate(acc, vr, base, TL::weights(p), gm);
@@ -154,15 +154,15 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
             const float w = rt.w[rb];
             const bool in = d0 < i || (d0 == i && w == 0.f);
             const float part = quad_sum((1.f - w) * TL::dot(qq, x[0]) + w * TL::dot(qq, x[1]));
-            s[0] = in ? part * sl2 : -INFINITY;
-            mb = fmaxf(mb, s[0]);
+            s[0] = in ? part : -INFINITY;
+            mb = fmaxf(mb, s[0] * sl2);
         } else {
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
                 const float part = quad_sum(TL::dot(qq, x[y]));
                 const bool in = rb + y < nact && rt.d0[rb + y < nact ? rb + y : nact - 1] <= i;
-                s[y] = in ? part * sl2 : -INFINITY;
-                mb = fmaxf(mb, s[y]);
+                s[y] = in ? part : -INFINITY;
+                mb = fmaxf(mb, s[y] * sl2);
             }
         }
         // The running reference moves only when a logit exceeds it by more than kFwdSlack
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
         }
 #pragma unroll
         for (int y = 0; y < RB; ++y) {
-            p[y] = fast_exp2(s[y] - m);
+            p[y] = fast_exp2(fmaf(s[y], sl2, -m));
             l += p[y];
         }
     };

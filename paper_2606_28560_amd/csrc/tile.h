@@ -76,20 +76,20 @@ struct Tile {
         }
     }
 
-    // <x, y> over the slice, in two chains.
+    // <x, y> over the slice, in four chains.
     __device__ static __forceinline__ float dot(const Slice &x, const Slice &y) {
-        float s[2] = {0.f, 0.f};
+        float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float &t = s[e & 1];
+                float &t = s[e];
                 if constexpr (kF32)
                     t = fmaf(__uint_as_float(x.c[c][e]), __uint_as_float(y.c[c][e]), t);
                 else
                     t = __builtin_amdgcn_fdot2_f32_bf16(as_bf2(x.c[c][e]), as_bf2(y.c[c][e]), t, false);
             }
-        return s[0] + s[1];
+        return (s[0] + s[1]) + (s[2] + s[3]);
     }
 
     // acc += a x + b y with float32 weights.
@@ -186,22 +186,34 @@ struct Tile {
     }
 
     // ---- matrix products --------------------------------------------------------------
-    // <rows a, columns b> over the head dims, 16 x 16.
+    // <rows a, columns b> over the head dims, 16 x 16.  float32: CH chains, which the
+    // matrix pipeline overlaps and whose partial sums round less than one long chain.
+    template <int CH = 4>
     __device__ static __forceinline__ f32x4 scores(const Slice &a, const Slice &b) {
-        f32x4 r{0.f, 0.f, 0.f, 0.f};
+        const f32x4 z{0.f, 0.f, 0.f, 0.f};
+        if constexpr (kF32) {
+            f32x4 r[CH];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if constexpr (kF32) {
+            for (int x = 0; x < CH; ++x) r[x] = z;
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    r = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.c[c][e]), __uint_as_float(b.c[c][e]), r,
-                                                             0, 0, 0);
-            } else {
+                    r[(4 * c + e) % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        __uint_as_float(a.c[c][e]), __uint_as_float(b.c[c][e]), r[(4 * c + e) % CH], 0, 0, 0);
+#pragma unroll
+            for (int h = CH / 2; h >= 1; h >>= 1)
+#pragma unroll
+                for (int x = 0; x < h; ++x) r[x] += r[x + h];
+            return r[0];
+        } else {
+            f32x4 r = z;
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
                 r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.c[c]),
                                                             __builtin_bit_cast(bf16x8, b.c[c]), r, 0, 0, 0);
-            }
+            return r;
         }
-        return r;
     }
     // Weights of a 32-row chunk (two 16-row blocks of C-layout weights, p[4b + e] for row
     // 16b + 4g + e and the lane's column), as matrix operands.
@@ -291,6 +303,27 @@ struct Tile {
         }
     }
 };
+
+// Probabilities p = exp(tau s - lse) of the backward, as exp2(s sl2 - lse log2e) with the
+// forward's sl2 = fl(tau log2e) (whose rounding the saved lse shares).  float32 rows: what
+// the rounding of lse log2e loses, which would move every probability of a query alike, is
+// carried along (in natural units) and multiplied back in.
+struct Lse2 {
+    float v, low;
+};
+template <bool F32>
+__device__ __forceinline__ Lse2 lse_log2(float lse) {
+    Lse2 r;
+    r.v = lse * kLog2e;
+    // kLog2e + 1.925963e-8 = log2(e)
+    r.low = F32 ? fmaf(lse, 1.925963033500e-8f, fmaf(lse, kLog2e, -r.v)) * kLn2 : 0.f;
+    return r;
+}
+template <bool F32>
+__device__ __forceinline__ float prob(float sl2, float s, const Lse2 &l) {
+    const float p = fast_exp2(fmaf(s, sl2, -l.v));
+    return F32 ? fmaf(p, -l.low, p) : p;
+}
 
 // Weight and lane bookkeeping of a launch: `nw` waves per workgroup are `hs` query heads
 // of one group (all reading the same rows) times nw / hs runs of 16 rows.
