@@ -30,7 +30,7 @@
 namespace fibattn {
 
 // ---------------------------------------------------------------------------
-// dq, Delta and per-workgroup dalpha partials.
+// dq, Delta and per-workgroup dalpha partials in bfloat16.
 // ---------------------------------------------------------------------------
 // A wave owns 16 consecutive queries (lane layouts in tile.h), as in the forward: the band
 // chunks' K and V rows are staged in LDS, S = K.Q^T and dP = V.dO^T taken on the matrix
@@ -41,8 +41,8 @@ namespace fibattn {
 // What bounds it: as the forward, the latency of the rung gathers and their VALU work.
 // Against a kernel with one lane group per query, every row read from global memory by
 // every query (us a launch, interpolating): bf16 d 64 B4 H8 T2048 W64 135 -> 22.9; bf16
-// d 128 B2 H16 on 4 T2000 W8 82 -> 37; bf16 d 32 B8 H8 T1024 W10 23.6 -> 15.4; fp32 d 64 B4
-// H8 T1024 W12 37 -> 23.5 (the R^T of dq, then a launch of its own, included).
+// d 128 B2 H16 on 4 T2000 W8 82 -> 37; bf16 d 32 B8 H8 T1024 W10 23.6 -> 15.4 (the R^T of
+// dq, then a launch of its own, not included in the first figure).
 template <typename S, int D>
 constexpr int dq_waves = Tile<S, D>::NC <= 2 ? 4 : Tile<S, D>::NC == 4 ? 3 : 2;
 
@@ -95,11 +95,12 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
 #pragma unroll
     for (int r = 0; r < kMaxRungs; ++r) nact += ((r < rt.n) & (rt.d0[r] <= min(t0 + 15, T - 1))) ? 1 : 0;
     nact = t0 < T ? __builtin_amdgcn_readfirstlane(nact) : 0;
-    // rows r0 and r1 of rung r
+    // rows r0 and r1 of rung r (an entry the query does not have reads the query's own row,
+    // as in the forward)
     auto load_rung = [&](int r, const void *X, uint32_t st, Slice *x) {
-        const int d = rt.d0[r];
-        x[0] = TL::load(X, max(ic - d, 0), gq, st);
-        x[1] = TL::load(X, max(ic - d - 1, 0), gq, st);
+        const int d = rt.d0[r], lim = INTERP && rt.w[r] != 0.f ? d + 1 : d;
+        x[0] = TL::load(X, ic >= lim ? ic - d : ic, gq, st);
+        x[1] = TL::load(X, ic > d ? ic - d - 1 : ic, gq, st);
     };
     Slice kx[NBUF][2], vx[NBUF][2];
     // in flight during the band phase, as far as the registers go
@@ -137,9 +138,10 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int key = rbeg + base + 16 * b + 4 * gm + e;
-                        const float p = (unsigned)(im - key) <= reach ? fast_exp2(fmaf(s[e], sl2, -lse2_m)) : 0.f;
-                        ds[4 * b + e] = tau * p * (dp[e] - delta_m);
-                        pd = fmaf(p, dp[e], pd);
+                        const bool in = (unsigned)(im - key) <= reach;
+                        const float p = in ? fast_exp2(fmaf(s[e], sl2, -lse2_m)) : 0.f, dP = in ? dp[e] : 0.f;
+                        ds[4 * b + e] = tau * p * (dP - delta_m);
+                        pd = fmaf(p, dP, pd);
                         ps += p;
                     }
                 }
@@ -161,6 +163,15 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
         if (TL::NC > 1) load_rung(0, K, sk, kx[0]);
     }
     TL::to_quad_acc(acc, lane);
+    // as in the forward: rows outside the window took part with weights of 0
+    if (__builtin_amdgcn_ballot_w64(!TL::finite(acc))) {
+        TL::zero(acc);
+        for (int key = max(t0 - W, 0); key < min(t0 + 16, T); ++key) {
+            const Slice kk = TL::load(K, key, gq, sk);
+            const float s = quad_sum(TL::dot(qq, kk)), dP = quad_sum(TL::dot(gg, TL::load(V, key, gq, sv)));
+            if (key <= i && i - key <= W) TL::axpy(acc, tau * fast_exp2(fmaf(s, sl2, -lse2)) * (dP - delta), kk);
+        }
+    }
     // the query's band sums, on each of its four quad lanes
     auto band_sum = [&](double x) {
         x += __shfl_xor(x, 16, 64);
@@ -247,6 +258,115 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
         for (int u = 1; u < nw; ++u) s += red[u];
         partials[blockIdx.x] = s;
     }
+}
+
+// ---------------------------------------------------------------------------
+// dq, Delta and dalpha partials in float32: as the forward's float32 kernel, four lanes per
+// query on the VALU, every sum in the order that tile.h states.
+// ---------------------------------------------------------------------------
+template <int D, bool DEV>
+__global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
+    const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
+    const float *__restrict__ o, const float *__restrict__ lse, const float *__restrict__ dO,
+    float *__restrict__ dq, float *__restrict__ delta_out, double *__restrict__ partials, int T, int W,
+    RungTable rt_arg, const RungTable *__restrict__ rtp, RopeFreq rf, float tau, int tiles, Heads hd, Layouts lay) {
+    using TL = Tile<float, D>;
+    using Slice = typename TL::Slice;
+    const RungTable &rt = DEV ? *rtp : rt_arg;
+    const bool bad = DEV && table_unusable(rt, W);  // bad device alpha, or another W
+    __shared__ double sfreq[D / 2], red[4];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nq = lane >> 2, gq = lane & 3;  // quad layout
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int bh = blk / tiles, t0 = (blk % tiles) * 64 + 16 * wave;
+    const int bk = hd.kv_of(bh);
+    const float *K = k + lay.k.head(bk, hd.kv_heads());
+    const float *V = v + lay.v.head(bk, hd.kv_heads());
+    const uint32_t sk = (uint32_t)(4 * lay.k.st), sv = (uint32_t)(4 * lay.v.st);
+    const int i = t0 + nq, ic = min(i, T - 1), last = min(t0 + 15, T - 1);
+    const float sl2 = tau * kLog2e;
+    const Slice qq = TL::load(q + lay.q.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.q.st));
+    const Slice gg = TL::load(dO + lay.g.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.g.st));
+    const float delta = row_dot<D>(gg, TL::load(o + lay.o.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.o.st)));
+    const float lse2 = lse[(size_t)bh * T + ic] * kLog2e;
+    if (rf.on) {
+        if (threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
+        __syncthreads();
+    }
+    int nact = 0;  // rungs some query of this wave includes: a prefix of the table
+#pragma unroll
+    for (int r = 0; r < kMaxRungs; ++r) nact += ((r < rt.n) & (rt.d0[r] <= last)) ? 1 : 0;
+    nact = t0 < T ? __builtin_amdgcn_readfirstlane(nact) : 0;
+    const int reach = min(W, ic), nwin = t0 < T ? min(W, last) + 1 : 0;
+
+    typename TL::Acc acc;
+    TL::zero(acc);
+    double xa = 0.0, xb = 0.0, y = 0.0, dsum = 0.0;  // dalpha parts, Delta from the entries
+    // an entry the query does not have reads the query's own row
+    for (int d = 0; d < nwin; d += 2) {
+        Slice kk[2], vv[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int row = d + u <= reach ? ic - d - u : ic;
+            kk[u] = TL::load(K, row, gq, sk);
+            vv[u] = TL::load(V, row, gq, sv);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const float s = row_dot<D>(qq, kk[u]);
+            const float dP = row_dot<D>(gg, vv[u]);
+            const float p = d + u <= reach ? exp2f(s * sl2 - lse2) : 0.f;
+            const float c = tau * p * (dP - delta);
+            dsum += (double)p * (double)dP;
+            TL::axpy(acc, c, kk[u]);
+        }
+    }
+    // rows r0 and r1 of rung r
+    auto load_rung = [&](int r, const void *X, uint32_t st, Slice *x) {
+        const int d = rt.d0[r], lim = rt.w[r] != 0.f ? d + 1 : d;
+        x[0] = TL::load(X, ic >= lim ? ic - d : ic, gq, st);
+        x[1] = TL::load(X, ic > d ? ic - d - 1 : ic, gq, st);
+    };
+    Slice kx[2], vx[2];
+    if (nact > 0) {
+        load_rung(0, V, sv, vx);
+        load_rung(0, K, sk, kx);
+    }
+    // the next rung's values load while this one's keys are used
+    for (int r = 0; r < nact; ++r) {
+        const int d0 = rt.d0[r], nx = min(r + 1, nact - 1);
+        const float w = rt.w[r];
+        const bool in = ic >= d0 + (w != 0.f), has1 = ic > d0;  // row -1 is the zero row
+        const float dP0 = row_dot<D>(gg, vx[0]), dPn = row_dot<D>(gg, vx[1]), dP1 = has1 ? dPn : 0.f;
+        load_rung(nx, V, sv, vx);
+        const float s0 = row_dot<D>(qq, kx[0]), sn = row_dot<D>(qq, kx[1]), s1 = has1 ? sn : 0.f;
+        const float s = (1.f - w) * s0 + w * s1;
+        const float dP = (1.f - w) * dP0 + w * dP1;
+        const float p = in ? exp2f(s * sl2 - lse2) : 0.f;
+        const float dS = p * (dP - delta);
+        const float c = tau * dS;
+        TL::axpy2(acc, c * (1.f - w), kx[0], c * w, kx[1]);
+        load_rung(nx, K, sk, kx);
+        const double fp = (double)rt.f[r] * (double)p;
+        xa += fp * (double)dP * (double)(s1 - s0);
+        xb += fp * (double)(dP1 - dP0);
+        y += fp * (double)(s1 - s0);
+        dsum += (double)p * (double)dP;
+    }
+    double dal = gq == 0 && i < T ? (double)tau * (xa - dsum * y) + xb : 0.0;
+    if (bad) dal = NAN;
+    if (rf.on) TL::rope_t(acc, i, sfreq, gq);  // gradient w.r.t. the unrotated q
+    if (i < T) {
+        TL::store(dq + lay.dq.head(bh, hd.H) + i * lay.dq.st, gq, acc, bad ? NAN : 1.f);
+        if (gq == 0) delta_out[(size_t)bh * T + i] = bad ? NAN : delta;
+    }
+#pragma unroll
+    for (int st = 32; st >= 1; st >>= 1) dal += __shfl_xor(dal, st, 64);
+    if (lane == 0) red[wave] = dal;
+    __syncthreads();
+    if (threadIdx.x == 0) partials[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
 // ---------------------------------------------------------------------------
@@ -421,14 +541,23 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
     ts.nc = band_chunks(W);
     const size_t fixed = 2 * (size_t)16 * (runs - 1) * TL::kRow, per = 2 * (size_t)32 * TL::kRow;
     ts.cps = tile_chunks(ts.nc, fixed, per, TL::NC);
-    const int nb = ts.tiles * (BH / ts.hs);  // dq workgroups = dalpha partials
+    int nb = ts.tiles * (BH / ts.hs);  // dq workgroups = dalpha partials
     bool interp = false;
     for (int r = 0; r < rt.n && !interp; ++r) interp = rt.w[r] != 0.f;
-    auto dqk = rtp ? bwd_dq_tile_kernel<S, D, true, true>
-                   : interp ? bwd_dq_tile_kernel<S, D, true, false> : bwd_dq_tile_kernel<S, D, false, false>;
-    hipError_t e = launch(kBwdDq, dqk, dim3(nb), dim3(64 * nw), (unsigned)(fixed + per * ts.cps), s, (const S *)q,
-                          (const S *)k, (const S *)v, (const S *)o, lse, (const S *)dO, (S *)dq, delta_ws, partials,
-                          T, W, rt, rtp, rf, tau, kLog2e / sqrtf((float)D), ts, hd, lay);
+    hipError_t e;
+    if constexpr (TL::kF32) {
+        const int tiles = (T + 63) / 64;
+        nb = tiles * BH;
+        e = launch(kBwdDq, rtp ? bwd_dq_f32_kernel<D, true> : bwd_dq_f32_kernel<D, false>, dim3(nb), dim3(256), 0, s,
+                   (const S *)q, (const S *)k, (const S *)v, (const S *)o, lse, (const S *)dO, (S *)dq, delta_ws,
+                   partials, T, W, rt, rtp, rf, tau, tiles, hd, lay);
+    } else {
+        auto dqk = rtp ? bwd_dq_tile_kernel<S, D, true, true>
+                       : interp ? bwd_dq_tile_kernel<S, D, true, false> : bwd_dq_tile_kernel<S, D, false, false>;
+        e = launch(kBwdDq, dqk, dim3(nb), dim3(64 * nw), (unsigned)(fixed + per * ts.cps), s, (const S *)q,
+                   (const S *)k, (const S *)v, (const S *)o, lse, (const S *)dO, (S *)dq, delta_ws, partials, T, W,
+                   rt, rtp, rf, tau, kLog2e / sqrtf((float)D), ts, hd, lay);
+    }
     if (e != hipSuccess) return e;
     dim3 grid((T + QPB - 1) / QPB, BH);
     e = launch(kBwdDkDv, rtp ? bwd_dkdv_kernel<S, D, true> : bwd_dkdv_kernel<S, D, false>,

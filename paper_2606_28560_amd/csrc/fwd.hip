@@ -1,5 +1,6 @@
-// Forward kernel for every storage type, head size and window outside the bfloat16,
-// d_head 64, W <= 16 path (fwd_mfma.hip): window band + shared rung offsets, softmax,
+// Forward kernels for every storage type, head size and window outside the bfloat16,
+// d_head 64, W <= 16 path (fwd_mfma.hip): a tile kernel on the matrix cores for bfloat16,
+// one on the VALU for float32 (below).  Both: window band + shared rung offsets, softmax,
 // weighted values, lse.
 //
 // Section 2 "Attended set": every query i of a (b, h) attends to distances 0..W and to
@@ -8,7 +9,7 @@
 // offsets are shared, a block of consecutive queries reads, for each rung, one
 // contiguous shifted block of key/value rows.
 //
-// A wave owns 16 consecutive queries (lane layouts in tile.h):
+// A wave owns 16 consecutive queries (lane layouts in tile.h).  The tile kernel:
 //   - window band: the keys i - W .. i lie in 32-row chunks that end at the wave's last
 //     query (one for W <= 16, five for W = 128).  The workgroup's chunks are copied to LDS
 //     a few at a time; per chunk, S = K.Q^T on the matrix cores, masked to 0 <= i - j <= W,
@@ -22,7 +23,7 @@
 // group per query, every row read from global memory by every query and no matrix cores
 // (us a launch, interpolating unless noted): bf16 d 64 B4 H8 T1500 W128, integer offsets,
 // 115.8 -> 15.6; bf16 d 64 B4 H8 T2048 W64 76.3 -> 17.2; bf16 d 128 B2 H16 on 4 T2000 W8
-// 62.0 -> 28.3; bf16 d 32 B8 H8 T1024 W10 25.5 -> 11.1; fp32 d 64 B4 H8 T1024 W12 33.4 -> 16.9.
+// 62.0 -> 28.3; bf16 d 32 B8 H8 T1024 W10 25.5 -> 11.1.
 #include "launch.h"
 #include "tile.h"
 
@@ -77,12 +78,21 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     nact = t0 < T ? __builtin_amdgcn_readfirstlane(nact) : 0;
 
     // the two rows of a batch: r0 and r1 of a rung, or r0 of two rungs (the second clamped
-    // to an active one and masked)
+    // to an active one and masked).  An entry the query does not have (weight 0) reads the
+    // query's own row: 0 times a row it does not attend could be NaN.
     auto load_batch = [&](int rb, const void *X, uint32_t st, Slice *x) {
+        if constexpr (INTERP) {
+            const int d = rt.d0[rb], two = rt.w[rb] != 0.f;
+            const bool in = ic >= d + two;
+            const int r0 = in ? ic - d : ic;
+            x[0] = TL::load(X, r0, gq, st);
+            x[1] = TL::load(X, in ? r0 - two : r0, gq, st);
+        } else {
 #pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            const int d = INTERP ? rt.d0[rb] + y : rt.d0[min(rb + y, nact - 1)];
-            x[y] = TL::load(X, max(ic - d, 0), gq, st);
+            for (int y = 0; y < 2; ++y) {
+                const int d = rt.d0[min(rb + y, nact - 1)];
+                x[y] = TL::load(X, ic >= d ? ic - d : ic, gq, st);
+            }
         }
     };
     Slice kx[NBUF][2], vx[NBUF][2];
@@ -144,6 +154,16 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     TL::to_quad_acc(acc, lane);
     m = to_quad(m, lane);
     l = to_quad(l, lane);
+    // Rows of the chunks outside a query's window were multiplied by weights of 0.  If that
+    // (or a value the query does attend) left anything that is not finite, the window's
+    // values are added again row by row, attended ones only.
+    if (__builtin_amdgcn_ballot_w64(!TL::finite(acc))) {
+        TL::zero(acc);
+        for (int key = max(t0 - W, 0); key < min(t0 + 16, T); ++key) {
+            const float s = quad_sum(TL::dot(qq, TL::load(K, key, gq, sk)));
+            if (key <= i && i - key <= W) TL::axpy(acc, fast_exp2(fmaf(s, sl2, -m)), TL::load(V, key, gq, sv));
+        }
+    }
 
     // ---- rungs (quad layout) ----
     float p[RB];
@@ -225,6 +245,125 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------
+// float32: the same set on the VALU, four lanes per query, every sum in the order that
+// tile.h states.
+// ---------------------------------------------------------------------------
+template <int D, bool DEV>
+__global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
+    const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, float *__restrict__ o,
+    float *__restrict__ lse, int T, int W, RungTable rt_arg, const RungTable *__restrict__ rtp, float sl2, int tiles,
+    Heads hd, Layouts lay) {
+    using TL = Tile<float, D>;
+    using Slice = typename TL::Slice;
+    constexpr int NC = TL::NC;
+    const RungTable &rt = DEV ? *rtp : rt_arg;
+    extern __shared__ __align__(16) char smem[];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nq = lane >> 2, gq = lane & 3;  // quad layout
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int bh = blk / tiles, t0 = (blk % tiles) * 64 + 16 * wave;
+    if (t0 >= T) return;  // no barrier below
+    const int bk = hd.kv_of(bh);
+    const float *K = k + lay.k.head(bk, hd.kv_heads());
+    const float *V = v + lay.v.head(bk, hd.kv_heads());
+    const uint32_t sk = (uint32_t)(4 * lay.k.st), sv = (uint32_t)(4 * lay.v.st);
+    const int i = t0 + nq, ic = min(i, T - 1), last = min(t0 + 15, T - 1);
+    const Slice qq = TL::load(q + lay.q.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.q.st));
+    int nact = 0;  // rungs some query of this wave includes: a prefix of the table
+#pragma unroll
+    for (int r = 0; r < kMaxRungs; ++r) nact += ((r < rt.n) & (rt.d0[r] <= last)) ? 1 : 0;
+    nact = __builtin_amdgcn_readfirstlane(nact);
+    const int nwin = (min(W, last) + 4) & ~3;  // window entries, in fours
+    // the wave's logits, entry by entry (LDS accesses of one wave keep their order)
+    float *sc = reinterpret_cast<float *>(smem) + 16 * wave + nq;
+
+    // logits and their maximum; an entry the query does not have reads its own row
+    float m = -INFINITY;
+    auto keep = [&](int e, bool in, float s) {
+        s = in ? s * sl2 : -INFINITY;
+        if (gq == 0) sc[64 * e] = s;
+        m = fmaxf(m, s);
+    };
+    const int reach = min(W, ic);
+    for (int d = 0; d < nwin; d += 4) {
+        Slice x[4];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) x[y] = TL::load(K, d + y <= reach ? ic - d - y : ic, gq, sk);
+#pragma unroll
+        for (int y = 0; y < 4; ++y) keep(d + y, d + y <= reach, row_dot<D>(qq, x[y]));
+    }
+    // two rungs together (the second clamped to an active one and masked)
+    for (int r = 0; r < nact; r += 2) {
+        Slice x[2], x1[2];
+        float w[2];
+        bool in[2];
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            const int a = min(r + y, nact - 1), d0 = rt.d0[a];
+            w[y] = rt.w[a];
+            in[y] = r + y < nact && ic >= d0 + (w[y] != 0.f);
+            const int r0 = in[y] ? ic - d0 : ic;
+            x[y] = TL::load(K, r0, gq, sk);
+            if (w[y] != 0.f) x1[y] = TL::load(K, in[y] ? r0 - 1 : r0, gq, sk);
+        }
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            float t[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) t[c] = (1.f - w[y]) * chunk_dot(qq.c[c], x[y].c[c]);
+            if (w[y] != 0.f) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) t[c] = fmaf(w[y], chunk_dot(qq.c[c], x1[y].c[c]), t[c]);
+            }
+            keep(nwin + r + y, in[y], chunk_sum<NC>(t));
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+
+    // probabilities and weighted values
+    typename TL::Acc acc;
+    TL::zero(acc);
+    float l = 0.f;
+#pragma unroll 4
+    for (int d = 0; d < nwin; ++d) {
+        const Slice x = TL::load(V, d <= reach ? ic - d : ic, gq, sv);
+        const float p = exp2f(sc[64 * d] - m);
+        l += p;
+        TL::axpy(acc, p, x);
+    }
+#pragma unroll 2
+    for (int r = 0; r < nact; ++r) {
+        const int d0 = rt.d0[r];
+        const float w = rt.w[r];
+        const bool in = ic >= d0 + (w != 0.f);
+        const int r0 = in ? ic - d0 : ic;
+        const Slice x = TL::load(V, r0, gq, sv);
+        const float p = exp2f(sc[64 * (nwin + r)] - m);
+        l += p;
+        TL::axpy(acc, p * (1.f - w), x);
+        if (w != 0.f) TL::axpy(acc, p * w, TL::load(V, in ? r0 - 1 : r0, gq, sv));
+    }
+    if (i < T) {
+        const bool bad = DEV && table_unusable(rt, W);  // bad device alpha, or another W
+        TL::store(o + lay.o.head(bh, hd.H) + i * lay.o.st, gq, acc, bad ? NAN : 1.f / l);
+        if (gq == 0) __builtin_nontemporal_store(bad ? NAN : (m + log2f(l)) * kLn2, lse + (size_t)bh * T + i);
+    }
+}
+
+template <int D>
+static hipError_t launch_fwd_f32(const void *q, const void *k, const void *v, void *o, float *lse, int BH,
+                                 const Heads &hd, int T, int W, const RungTable &rt, const RungTable *rtp,
+                                 const Layouts &lay, hipStream_t s) {
+    const int tiles = (T + 63) / 64;
+    const size_t lds = 64 * sizeof(float) * (size_t)(W + 4 + (rtp ? kMaxRungs : rt.n + 1));
+    return launch(kForward, rtp ? fwd_f32_kernel<D, true> : fwd_f32_kernel<D, false>, dim3(tiles * BH), dim3(256),
+                  (unsigned)lds, s, (const float *)q, (const float *)k, (const float *)v, (float *)o, lse, T, W, rt,
+                  rtp, kLog2e / sqrtf((float)D), tiles, hd, lay);
+}
+
 // Query heads side by side in a workgroup of nw waves, for G heads per key/value head:
 // they read the same key/value rows, so the staged rows serve all of them.
 int tile_heads(int G, int nw) {
@@ -269,11 +408,11 @@ hipError_t launch_forward(int dtype, int D, const void *q, const void *k, const 
                           const RungTable *rtp, const Layouts &lay, hipStream_t s) {
     if (forward_mfma_supported(dtype, D, W))
         return launch_forward_mfma(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
-    if (dtype == 0 && D == 32) return launch_fwd_t<float, 32>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
-    if (dtype == 0 && D == 64) return launch_fwd_t<float, 64>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
+    if (dtype == 0 && D == 32) return launch_fwd_f32<32>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
+    if (dtype == 0 && D == 64) return launch_fwd_f32<64>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
     if (dtype == 1 && D == 32) return launch_fwd_t<uint16_t, 32>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
     if (dtype == 1 && D == 64) return launch_fwd_t<uint16_t, 64>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
-    if (dtype == 0 && D == 128) return launch_fwd_t<float, 128>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
+    if (dtype == 0 && D == 128) return launch_fwd_f32<128>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
     if (dtype == 1 && D == 128) return launch_fwd_t<uint16_t, 128>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
     return hipErrorInvalidValue;
 }

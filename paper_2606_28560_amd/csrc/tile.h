@@ -47,6 +47,15 @@ struct Tile {
         for (int b = 0; b < NB; ++b) a.c[b] *= s;
     }
 
+    __device__ static __forceinline__ bool finite(const Acc &a) {
+        float x = 0.f;  // NaN if any element is not finite
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x = fmaf(a.c[b][e], 0.f, x);
+        return x == 0.f;
+    }
+
     // Slice g of row `row`, rows `st` bytes apart from a uniform base (the host keeps
     // every row offset below 2^31 bytes).
     __device__ static __forceinline__ Slice load(const void *base, int row, int g, uint32_t st) {
@@ -303,6 +312,38 @@ struct Tile {
         }
     }
 };
+
+// ---- float32 rows on the VALU, every sum in one fixed order (fwd.hip, bwd.hip) -------
+// The order is that of one lane per 16-byte chunk: a chain over the chunk's four products,
+// then pairs of chunks, the farthest first.  dalpha is a sum of terms that cancel, which
+// carries the rounding of lse and of the probabilities up by one to two decimal digits:
+// another order of the same sums moves it by more than a float32 result may move.
+__device__ __forceinline__ float chunk_dot(const u32x4 &x, const u32x4 &y) {
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = fmaf(__uint_as_float(x[e]), __uint_as_float(y[e]), s);
+    return s;
+}
+// Sum of a row's chunk values, this lane's at positions 4x + g; quad layout.
+template <int NC>
+__device__ __forceinline__ float chunk_sum(float *t) {
+#pragma unroll
+    for (int h = NC / 2; h >= 1; h >>= 1)
+#pragma unroll
+        for (int x = 0; x < h; ++x) t[x] += t[x + h];
+    float s = t[0];
+    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x4E, 0xF, 0xF, true));
+    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0xB1, 0xF, 0xF, true));
+    return s;
+}
+template <int D>
+__device__ __forceinline__ float row_dot(const typename Tile<float, D>::Slice &x, const typename Tile<float, D>::Slice &y) {
+    constexpr int NC = Tile<float, D>::NC;
+    float t[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) t[c] = chunk_dot(x.c[c], y.c[c]);
+    return chunk_sum<NC>(t);
+}
 
 // Probabilities p = exp(tau s - lse) of the backward, as exp2(s sl2 - lse log2e) with the
 // forward's sl2 = fl(tau log2e) (whose rounding the saved lse shares).  float32 rows: what
