@@ -318,8 +318,7 @@ static fibattn_status_t backward_impl(const void *q, const void *k, const void *
     const RopeFreq rf = make_rope_freq((double)rope_base, d_head);
     const Heads hd{H, H / H_kv};
     hipError_t e = launch_backward((int)dtype, d_head, q, k, v, o, lse, dO, dq, dk, dv, dalpha, nullptr,
-                                   delta_ws, partials, terms, B * H, hd, T, W, rt, nullptr, rf,
-                                   rope_base, lay, stream);
+                                   delta_ws, partials, terms, B * H, hd, T, W, rt, nullptr, rf, lay, stream);
     return e == hipSuccess ? FIBATTN_OK : FIBATTN_ERR_HIP;
 }
 
@@ -470,8 +469,7 @@ fibattn_status_t fibattn_backward_dt(const void *q, const void *k, const void *v
     const Heads hd{H, H / H_kv};
     hipError_t e = launch_backward((int)dtype, d_head, q, k, v, o, lse, dO, dq, dk, dv, dalpha, dtheta,
                                    delta_ws, partials, terms, B * H, hd, T, W, unused,
-                                   (const RungTable *)table, rf, rope_base,
-                                   packed_layouts(H, H_kv, T, d_head), stream);
+                                   (const RungTable *)table, rf, packed_layouts(H, H_kv, T, d_head), stream);
     return e == hipSuccess ? FIBATTN_OK : FIBATTN_ERR_HIP;
 }
 

@@ -24,6 +24,8 @@
 // (as the row r0, weight 1-w) and j + floor(d_k) + 1 (as r1, weight w) through rung k.
 // The dk/dv kernel therefore owns one key row per lane group and gathers its
 // contributions, so every dk/dv row is written once, without atomics.
+#include <algorithm>
+
 #include "launch.h"
 #include "tile.h"
 
@@ -370,141 +372,306 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// dk, dv: one key row per lane group.
+// dk, dv: key-stationary, no atomics.
 // ---------------------------------------------------------------------------
-template <typename S, int D, bool DEV>
-__global__ __launch_bounds__(256) void bwd_dkdv_kernel(
+// A wave owns 16 consecutive keys of one key/value head and the terms of one query head at
+// a time; the waves of a workgroup are ts.hs query heads of the group side by side times
+// runs of 16 keys, a group of G heads takes G / hs passes, and the heads' sums meet in LDS
+// at the end.
+//   - window band: the queries j .. j + W lie in 32-row chunks from the wave's first key on.
+//     Their q and dO rows are staged in LDS; S = Q.K^T and dP = dO.V^T on the matrix cores,
+//     dk += Q^T (tau dS) and dv += dO^T P there (weights as in tile.h);
+//   - rungs, four lanes per key: query i0 = j + floor(d) reads key j as r0 (weight 1 - w)
+//     and j - 1 as r1, query i0 + 1 reads j + 1 as r0 and j as r1 (weight w).  A key takes
+//     the products of its own row with both queries; the two with its neighbours' rows
+//     are those of the keys four lanes before and on.  For the wave's first and last key
+//     (the edges) they are taken before the loop, 16 rungs at a time.
+//
+// What bounds it: as dq, the latency of the rung gathers and their VALU work; two (NC 4) or
+// four (NC 2) waves per SIMD, as the registers of two query and two dO rows in flight allow.
+// Us a launch: bf16 d 64 B4 H8 T2048 W64 26.3; bf16 d 128 B2 H16 on 4 T2000 W8 51.7; bf16
+// d 32 B8 H8 T1024 W10 17.8; fp32 d 64 B4 H8 T1024 W12 23.4.  With one lane group per key,
+// every query row read from global memory by every key it attends, and the R^T of dk and
+// the dalpha sum as launches of their own, the training step of each took 82, 66, 15 and
+// 38 us more.
+template <typename S, int D>
+constexpr int dkdv_waves = Tile<S, D>::NC <= 2 ? 4 : Tile<S, D>::NC == 4 ? 2 : 1;
+
+template <typename S, int D, bool INTERP, bool DEV>
+__global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
     const S *__restrict__ q, const S *__restrict__ k, const S *__restrict__ v,
     const float *__restrict__ lse, const S *__restrict__ dO, const float *__restrict__ delta_in,
-    S *__restrict__ dk, S *__restrict__ dv, int T, int W, RungTable rt_arg,
-    const RungTable *__restrict__ rtp, float tau, Heads hd, Layouts lay) {
+    S *__restrict__ dk, S *__restrict__ dv, const double *__restrict__ partials, int n_partials,
+    float *__restrict__ dalpha, float *__restrict__ dtheta, int T, int W, RungTable rt_arg,
+    const RungTable *__restrict__ rtp, RopeFreq rf, float tau, float sl2, TileShape ts, Heads hd, Layouts lay) {
+    using TL = Tile<S, D>;
+    using Slice = typename TL::Slice;
     const RungTable &rt = DEV ? *rtp : rt_arg;
-    constexpr int VN = Vec<S>::N;
-    constexpr int LPQ = D / VN;
-    constexpr int QPB = 256 / LPQ;
+    extern __shared__ __align__(16) char smem[];
+    __shared__ double sfreq[D / 2];
 
-    const int g = threadIdx.x / LPQ;
-    const int sub = threadIdx.x % LPQ;
-    const int j = blockIdx.x * QPB + g;
-    if (j >= T) return;  // whole lane groups leave together; no block barrier below
-    const int bk = blockIdx.y;  // batch * key/value heads + key/value head
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nw = blockDim.x >> 6;
+    const int nm = lane & 15, gm = lane >> 4;  // MFMA layout
+    const int nq = lane >> 2, gq = lane & 3;   // quad layout
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int runs = nw / ts.hs, wv = wave / ts.hs, hs = wave % ts.hs;  // run of keys, head slot
+    const int bk = blk / ts.tiles;  // batch * key/value heads + key/value head
+    const int T0 = (blk % ts.tiles) * 16 * runs;
     const S *K = k + lay.k.head(bk, hd.kv_heads());
     const S *V = v + lay.v.head(bk, hd.kv_heads());
-    const long long sq = lay.q.st, sk = lay.k.st, sv = lay.v.st, sg = lay.g.st;  // row strides
-    const int col = sub * VN;
-    const float sl2 = tau * kLog2e;
+    constexpr int es = (int)sizeof(S);
+    const uint32_t sq = (uint32_t)(lay.q.st * es), sg = (uint32_t)(lay.g.st * es);
+    const uint32_t sk = (uint32_t)(lay.k.st * es), sv = (uint32_t)(lay.v.st * es);
+    if (rf.on && threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
 
-    float kj[VN], vj[VN], adk[VN], adv[VN], qv[VN], gv[VN];
-    Vec<S>::load(K + j * sk + col, kj);
-    Vec<S>::load(V + j * sv + col, vj);
-#pragma unroll
-    for (int c = 0; c < VN; ++c) { adk[c] = 0.f; adv[c] = 0.f; }
-
-    // every query head of the group reads this key row; their terms add up
-    for (int hg = 0; hg < hd.G; ++hg) {
-        const int bh = hd.q_of(blockIdx.y, hg);
-        const S *Q = q + lay.q.head(bh, hd.H);
-        const S *G = dO + lay.g.head(bh, hd.H);
-        const float *L = lse + (size_t)bh * T;
-        const float *Dl = delta_in + (size_t)bh * T;
-
-        // window: queries i = j .. j+W read row j with weight 1
-        const int imax = min(T - 1, j + W);
-        for (int i = j; i <= imax; ++i) {
-            Vec<S>::load(Q + i * sq + col, qv);
-            Vec<S>::load(G + i * sg + col, gv);
-            const float s = group_sum<LPQ>(dot<VN>(qv, kj));
-            const float dP = group_sum<LPQ>(dot<VN>(gv, vj));
-            const float p = exp2f(s * sl2 - L[i] * kLog2e);
-            const float c = tau * p * (dP - Dl[i]);
-#pragma unroll
-            for (int x = 0; x < VN; ++x) {
-                adk[x] = fmaf(c, qv[x], adk[x]);
-                adv[x] = fmaf(p, gv[x], adv[x]);
-            }
+    // dalpha: the partials of the dq kernel, which has completed, in a fixed order
+    if (blockIdx.x == 0) {
+        double *red = reinterpret_cast<double *>(smem);
+        double s = 0.0;
+        for (int t = threadIdx.x; t < n_partials; t += blockDim.x) s += partials[t];
+        red[threadIdx.x] = s;
+        __syncthreads();
+        for (int st = blockDim.x >> 1; st >= 1; st >>= 1) {
+            if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+            __syncthreads();
         }
-        // rungs
-        for (int r = 0; r < rt.n; ++r) {
-            const int d0 = rt.d0[r];
-            const float w = rt.w[r];
-            const int i0 = j + d0;
-            if (i0 >= T) break;  // d0 increases with r
-            float kn[VN], vn[VN];
-            // query i0 reads row j as r0 (weight 1-w) and row j-1 as r1; included iff w <= j
-            if (w == 0.f || j >= 1) {
-                Vec<S>::load(Q + i0 * sq + col, qv);
-                Vec<S>::load(G + i0 * sg + col, gv);
-                float s = (1.f - w) * dot<VN>(qv, kj);
-                float dP = (1.f - w) * dot<VN>(gv, vj);
-                if (w != 0.f) {
-                    Vec<S>::load(K + (j - 1) * sk + col, kn);
-                    Vec<S>::load(V + (j - 1) * sv + col, vn);
-                    s = fmaf(w, dot<VN>(qv, kn), s);
-                    dP = fmaf(w, dot<VN>(gv, vn), dP);
-                }
-                s = group_sum<LPQ>(s);
-                dP = group_sum<LPQ>(dP);
-                const float p = exp2f(s * sl2 - L[i0] * kLog2e);
-                const float c = tau * p * (dP - Dl[i0]) * (1.f - w);
-                const float pw = p * (1.f - w);
-#pragma unroll
-                for (int x = 0; x < VN; ++x) {
-                    adk[x] = fmaf(c, qv[x], adk[x]);
-                    adv[x] = fmaf(pw, gv[x], adv[x]);
-                }
-            }
-            // query i0+1 reads row j+1 as r0 and row j as r1 (weight w); always included
-            const int i1 = i0 + 1;
-            if (w != 0.f && i1 < T) {
-                Vec<S>::load(Q + i1 * sq + col, qv);
-                Vec<S>::load(G + i1 * sg + col, gv);
-                Vec<S>::load(K + (j + 1) * sk + col, kn);
-                Vec<S>::load(V + (j + 1) * sv + col, vn);
-                float s = fmaf(1.f - w, dot<VN>(qv, kn), w * dot<VN>(qv, kj));
-                float dP = fmaf(1.f - w, dot<VN>(gv, vn), w * dot<VN>(gv, vj));
-                s = group_sum<LPQ>(s);
-                dP = group_sum<LPQ>(dP);
-                const float p = exp2f(s * sl2 - L[i1] * kLog2e);
-                const float c = tau * p * (dP - Dl[i1]) * w;
-                const float pw = p * w;
-#pragma unroll
-                for (int x = 0; x < VN; ++x) {
-                    adk[x] = fmaf(c, qv[x], adk[x]);
-                    adv[x] = fmaf(pw, gv[x], adv[x]);
-                }
-            }
+        if (threadIdx.x == 0) {
+            const float da = (float)red[0];
+            *dalpha = da;
+            // a table built from theta: d L / d theta = dalpha * d alpha / d theta
+            if (DEV && dtheta) *dtheta = (float)((double)da * rt.dadtheta);
         }
-    }
-    if (DEV && table_unusable(rt, W)) {  // bad device alpha, or another W
-#pragma unroll
-        for (int x = 0; x < VN; ++x) { adk[x] = NAN; adv[x] = NAN; }
-    }
-    Vec<S>::store(dk + lay.dk.head(bk, hd.kv_heads()) + j * lay.dk.st + col, adk);
-    Vec<S>::store(dv + lay.dv.head(bk, hd.kv_heads()) + j * lay.dv.st + col, adv);
-}
-
-// ---------------------------------------------------------------------------
-// dalpha: one workgroup sums the partials in a fixed order, in float64.
-// ---------------------------------------------------------------------------
-// dtheta (device tables built from theta): dalpha (as stored) times d alpha / d theta.
-__global__ __launch_bounds__(256) void dalpha_reduce_kernel(const double *__restrict__ partials,
-                                                            size_t n, float *__restrict__ dalpha,
-                                                            float *__restrict__ dtheta,
-                                                            const RungTable *__restrict__ rtp) {
-    __shared__ double red[256];
-    double s = 0.0;
-    for (size_t t = threadIdx.x; t < n; t += 256) s += partials[t];
-    red[threadIdx.x] = s;
-    __syncthreads();
-#pragma unroll
-    for (int st = 128; st >= 1; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        const float da = (float)red[0];
-        *dalpha = da;
-        if (dtheta) *dtheta = (float)((double)da * rtp->dadtheta);
+
+    const int t0 = T0 + 16 * wv;
+    const int jm = t0 + nm;                     // MFMA layout key
+    const int j = t0 + nq, jc = min(j, T - 1);  // quad layout key
+    Slice kj = TL::load(K, jc, gq, sk), vj = TL::load(V, jc, gq, sv);
+    int nact = 0;  // rungs through which a query reads some key of this wave: a prefix
+#pragma unroll
+    for (int r = 0; r < kMaxRungs; ++r) nact += ((r < rt.n) & (rt.d0[r] < T - t0)) ? 1 : 0;
+    nact = __builtin_amdgcn_readfirstlane(nact);
+    const int passes = hd.G / ts.hs;
+
+    // ---- window band (MFMA layout) ----
+    typename TL::Acc adk, adv;
+    TL::zero(adk);
+    TL::zero(adv);
+    {
+        const Slice km = TL::from_quad(kj, lane), vm = TL::from_quad(vj, lane);
+        const unsigned reach = (unsigned)min(W, T - 1 - jm);  // 0 <= query - jm <= W and query < T
+        bool first = true;
+        for (int pass = 0; pass < passes; ++pass)
+            for (int c0 = 0; c0 < ts.nc; c0 += ts.cps) {
+                // chunks c0 .. c0 + n - 1 of every run: chunk c of run wv is the queries
+                // [T0 + 16 wv + 32 c, T0 + 16 wv + 32 (c + 1))
+                const int n = min(ts.cps, ts.nc - c0);
+                const int rbeg = T0 + 32 * c0, rows = 16 * (runs - 1) + 32 * n;
+                char *qr = smem, *gr = smem + ts.hs * rows * TL::kRow;
+                float *sl = reinterpret_cast<float *>(gr + ts.hs * rows * TL::kRow), *sd = sl + ts.hs * rows;
+                if (!first) __syncthreads();  // every wave is done with the rows staged before
+                first = false;
+                for (int u = 0; u < ts.hs; ++u) {
+                    const int bh = hd.q_of(bk, pass * ts.hs + u);
+                    TL::stage(qr + u * rows * TL::kRow, q + lay.q.head(bh, hd.H), rbeg, rows, T, lay.q.st, wave, nw);
+                    TL::stage(gr + u * rows * TL::kRow, dO + lay.g.head(bh, hd.H), rbeg, rows, T, lay.g.st, wave, nw);
+                }
+                for (int x = threadIdx.x; x < ts.hs * rows; x += blockDim.x) {
+                    const size_t at = (size_t)hd.q_of(bk, pass * ts.hs + x / rows) * T + min(rbeg + x % rows, T - 1);
+                    sl[x] = lse[at] * kLog2e;
+                    sd[x] = delta_in[at];
+                }
+                wait_vmem();
+                __syncthreads();
+                const char *qb = qr + hs * rows * TL::kRow, *gb = gr + hs * rows * TL::kRow;
+                for (int c = 0; c < n; ++c) {
+                    const int base = 16 * wv + 32 * c;  // the chunk's first staged row
+                    float ds[8], p[8];
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        const f32x4 s = TL::scores(TL::staged(qb, base + 16 * b + nm, gm), km);
+                        const f32x4 dp = TL::scores(TL::staged(gb, base + 16 * b + nm, gm), vm);
+                        const int si = base + 16 * b + 4 * gm;
+                        const f32x4 l2 = *reinterpret_cast<const f32x4 *>(sl + hs * rows + si);
+                        const f32x4 de = *reinterpret_cast<const f32x4 *>(sd + hs * rows + si);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const bool in = jm < T && (unsigned)(rbeg + si + e - jm) <= reach;
+                            const float x = fast_exp2(fmaf(s[e], sl2, -l2[e]));
+                            p[4 * b + e] = in ? x : 0.f;
+                            ds[4 * b + e] = in ? tau * x * (dp[e] - de[e]) : 0.f;
+                        }
+                    }
+                    TL::accumulate(adk, qb, base, TL::weights(ds), gm);
+                    TL::accumulate(adv, gb, base, TL::weights(p), gm);
+                }
+            }
+    }
+    TL::to_quad_acc(adk, lane);
+    TL::to_quad_acc(adv, lane);
+    if constexpr (TL::NC > 1) {
+        // read again rather than held through the band phase
+        int row = jc;
+        asm volatile("" : "+v"(row));
+        kj = TL::load(K, row, gq, sk);
+        vj = TL::load(V, row, gq, sv);
+    }
+    // as in the forward: rows outside the window took part with weights of 0
+    if (__builtin_amdgcn_ballot_w64(!(TL::finite(adk) && TL::finite(adv)))) {
+        TL::zero(adk);
+        TL::zero(adv);
+        for (int pass = 0; pass < passes; ++pass) {
+            const int bh = hd.q_of(bk, pass * ts.hs + hs);
+            const S *Q = q + lay.q.head(bh, hd.H), *G = dO + lay.g.head(bh, hd.H);
+            for (int i = t0; i < min(t0 + 16 + W, T); ++i) {
+                const Slice x = TL::load(Q, i, gq, sq), y = TL::load(G, i, gq, sg);
+                const float s = quad_sum(TL::dot(x, kj)), dP = quad_sum(TL::dot(y, vj));
+                const float p = fast_exp2(fmaf(s, sl2, -lse[(size_t)bh * T + i] * kLog2e));
+                if (i >= j && i - j <= W) {
+                    TL::axpy(adk, tau * p * (dP - delta_in[(size_t)bh * T + i]), x);
+                    TL::axpy(adv, p, y);
+                }
+            }
+        }
+    }
+
+    // ---- rungs (quad layout) ----
+    for (int pass = 0; pass < (nact > 0 ? passes : 0); ++pass) {
+        // opaque copies keep the index arithmetic inside the pass loop (hoisted for all
+        // rungs at once it would not fit the registers)
+        int jp = j, tp = t0;
+        asm volatile("" : "+v"(jp), "+s"(tp));
+        const int bh = hd.q_of(bk, pass * ts.hs + hs);
+        const S *Q = q + lay.q.head(bh, hd.H), *G = dO + lay.g.head(bh, hd.H);
+        const float *L = lse + (size_t)bh * T, *Dl = delta_in + (size_t)bh * T;
+        // Query rows of a rung: those of i0 and i0 + 1, or those of two rungs.  A query that
+        // does not read the key is replaced by the one at the key's own position, which does.
+        Slice xq[2], xg[2];
+        float xl[2], xd[2];
+        auto has = [&](int r, int y) {
+            if constexpr (INTERP) {
+                const bool two = rt.w[r] != 0.f;  // row r1 exists
+                return jp + rt.d0[r] + y < T && (y ? two : !two || jp >= 1);
+            } else {
+                return r + y < nact && jp + rt.d0[min(r + y, nact - 1)] < T;
+            }
+        };
+        auto row_of = [&](int r, int y) {
+            return has(r, y) ? jp + (INTERP ? rt.d0[r] + y : rt.d0[min(r + y, nact - 1)]) : min(jp, T - 1);
+        };
+        auto load_q = [&](int r) {
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                const int row = row_of(r, y);
+                xq[y] = TL::load(Q, row, gq, sq);
+                xl[y] = L[row];
+                xd[y] = Dl[row];
+            }
+        };
+        auto load_g = [&](int r) {
+#pragma unroll
+            for (int y = 0; y < 2; ++y) xg[y] = TL::load(G, row_of(r, y), gq, sg);
+        };
+
+        // <q, k> and <dO, v> of the wave's edges, rung nq (and nq + 16) on this quad: query
+        // t0 + d with key t0 - 1, query t0 + 16 + d with key t0 + 16
+        float es_[2][2], ep_[2][2];
+        if constexpr (INTERP) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    es_[h][u] = ep_[h][u] = 0.f;
+                    if (16 * h < nact) {
+                        const int i = tp + 16 * u + rt.d0[min(nq + 16 * h, nact - 1)];
+                        const int key = u ? min(tp + 16, T - 1) : max(tp - 1, 0), row = i < T ? i : key;
+                        es_[h][u] = quad_sum(TL::dot(TL::load(Q, row, gq, sq), TL::load(K, key, gq, sk)));
+                        ep_[h][u] = quad_sum(TL::dot(TL::load(G, row, gq, sg), TL::load(V, key, gq, sv)));
+                    }
+                }
+        }
+        load_q(0);
+        load_g(0);
+        constexpr int RB = INTERP ? 1 : 2;
+        for (int r = 0; r < nact; r += RB) {
+            const int nx = min(r + RB, nact - 1);
+            // logits and dP of the two entries
+            float s[2], dP[2], c[2], p[2];
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                s[y] = quad_sum(TL::dot(xq[y], kj));
+                dP[y] = quad_sum(TL::dot(xg[y], vj));
+            }
+            if constexpr (INTERP) {
+                // query i0 with key j - 1 is query i0 + 1 of the key four lanes before,
+                // query i0 + 1 with key j + 1 is query i0 of the key four lanes on
+                const float w = rt.w[r];
+                auto shift = [&](float x, int by, bool edge, const float *e0, const float *e1, int u) {
+                    const float y = __shfl(x, lane + by, 64);
+                    const float e = r < 16 ? e0[u] : e1[u];
+                    const float z = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e), 4 * (r & 15)));
+                    return edge ? z : y;
+                };
+                const float sb = shift(s[1], -4, lane < 4, es_[0], es_[1], 0);
+                const float pb = shift(dP[1], -4, lane < 4, ep_[0], ep_[1], 0);
+                const float sn = shift(s[0], 4, lane >= 60, es_[0], es_[1], 1);
+                const float pn = shift(dP[0], 4, lane >= 60, ep_[0], ep_[1], 1);
+                if (w != 0.f) {
+                    s[0] = fmaf(w, sb, (1.f - w) * s[0]);
+                    dP[0] = fmaf(w, pb, (1.f - w) * dP[0]);
+                    s[1] = fmaf(w, s[1], (1.f - w) * sn);
+                    dP[1] = fmaf(w, dP[1], (1.f - w) * pn);
+                }
+            }
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                const bool in = has(r, y);
+                const float x = fast_exp2(fmaf(s[y], sl2, -xl[y] * kLog2e));
+                const float wt = INTERP ? (y ? rt.w[r] : 1.f - rt.w[r]) : 1.f;
+                p[y] = in ? x * wt : 0.f;
+                c[y] = in ? tau * x * (dP[y] - xd[y]) * wt : 0.f;
+            }
+            // the next rung's rows load as soon as this one's are used
+            TL::axpy2(adk, c[0], xq[0], c[1], xq[1]);
+            load_q(nx);
+            __builtin_amdgcn_sched_barrier(0);
+            TL::axpy2(adv, p[0], xg[0], p[1], xg[1]);
+            load_g(nx);
+        }
+    }
+
+    if (ts.hs > 1) {
+        // head slots 1 .. hand their sums to slot 0 of the same keys, vector by vector,
+        // lane-minor (a wave's accesses cover consecutive banks)
+        f32x4 *xfer = reinterpret_cast<f32x4 *>(smem);
+        __syncthreads();  // every wave is done with the staged rows
+        if (hs > 0) {
+            f32x4 *dst = xfer + (size_t)(wv * (ts.hs - 1) + hs - 1) * 2 * TL::NB * 64 + lane;
+#pragma unroll
+            for (int b = 0; b < TL::NB; ++b) {
+                dst[b * 64] = adk.c[b];
+                dst[(TL::NB + b) * 64] = adv.c[b];
+            }
+        }
+        __syncthreads();
+        if (hs > 0) return;  // no barrier below
+        for (int u = 1; u < ts.hs; ++u) {
+            const f32x4 *src = xfer + (size_t)(wv * (ts.hs - 1) + u - 1) * 2 * TL::NB * 64 + lane;
+#pragma unroll
+            for (int b = 0; b < TL::NB; ++b) {
+                adk.c[b] += src[b * 64];
+                adv.c[b] += src[(TL::NB + b) * 64];
+            }
+        }
+    }
+    if (rf.on) TL::rope_t(adk, j, sfreq, gq);  // gradient w.r.t. the unrotated k
+    if (j < T) {
+        const float sc = DEV && table_unusable(rt, W) ? NAN : 1.f;  // bad device alpha, or another W
+        TL::store(dk + lay.dk.head(bk, hd.kv_heads()) + j * lay.dk.st, gq, adk, sc);
+        TL::store(dv + lay.dv.head(bk, hd.kv_heads()) + j * lay.dv.st, gq, adv, sc);
     }
 }
 
@@ -531,7 +698,6 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
                                const Heads &hd, int T, int W, const RungTable &rt,
                                const RungTable *rtp, const RopeFreq &rf, const Layouts &lay, hipStream_t s) {
     using TL = Tile<S, D>;
-    constexpr int QPB = 256 / (D / Vec<S>::N);
     constexpr int nw = TL::kRow == 512 ? 2 : 4;  // as the forward
     const float tau = 1.f / sqrtf((float)D);
     TileShape ts;
@@ -559,13 +725,19 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
                    rt, rtp, rf, tau, kLog2e / sqrtf((float)D), ts, hd, lay);
     }
     if (e != hipSuccess) return e;
-    dim3 grid((T + QPB - 1) / QPB, BH);
-    e = launch(kBwdDkDv, rtp ? bwd_dkdv_kernel<S, D, true> : bwd_dkdv_kernel<S, D, false>,
-               dim3(grid.x, BH / hd.G), dim3(256), 0, s, (const S *)q, (const S *)k, (const S *)v,
-               lse, (const S *)dO, delta_ws, (S *)dk, (S *)dv, T, W, rt, rtp, tau, hd, lay);
-    if (e != hipSuccess) return e;
-    return launch(kDalphaReduce, dalpha_reduce_kernel, dim3(1), dim3(256), 0, s, partials,
-                  (size_t)nb, dalpha, dtheta, rtp);
+    // dk, dv: a head slot's q and dO rows of the staged chunks, their lse and Delta; the
+    // sums of the slots past the first take their place at the end
+    TileShape tk = ts;
+    const size_t row = 2 * TL::kRow + 2 * sizeof(float);
+    const size_t kfixed = row * ts.hs * 16 * (runs - 1), kper = row * ts.hs * 32;
+    tk.cps = tile_chunks(ts.nc, kfixed, kper, TL::NC);
+    const size_t sums = (size_t)(nw - runs) * 64 * 2 * sizeof(typename TL::Acc);
+    const size_t lds = std::max({kfixed + kper * tk.cps, sums, 64 * nw * sizeof(double)});
+    auto dkk = rtp ? bwd_dkdv_tile_kernel<S, D, true, true>
+                   : interp ? bwd_dkdv_tile_kernel<S, D, true, false> : bwd_dkdv_tile_kernel<S, D, false, false>;
+    return launch(kBwdDkDv, dkk, dim3(ts.tiles * (BH / hd.G)), dim3(64 * nw), (unsigned)lds, s, (const S *)q,
+                  (const S *)k, (const S *)v, lse, (const S *)dO, delta_ws, (S *)dk, (S *)dv, partials, nb, dalpha,
+                  dtheta, T, W, rt, rtp, rf, tau, kLog2e / sqrtf((float)D), tk, hd, lay);
 }
 
 static hipError_t launch_backward_generic(int dtype, int D, const void *q, const void *k, const void *v,
@@ -587,24 +759,17 @@ static hipError_t launch_backward_generic(int dtype, int D, const void *q, const
     return hipErrorInvalidValue;
 }
 
-
 hipError_t launch_backward(int dtype, int D, const void *q, const void *k, const void *v,
                            const void *o, const float *lse, const void *dO, void *dq, void *dk,
                            void *dv, float *dalpha, float *dtheta, float *delta_ws, double *partials,
                            const RungTerms &terms, int BH, const Heads &hd, int T, int W,
                            const RungTable &rt, const RungTable *rtp, const RopeFreq &rf,
-                           float rope_base, const Layouts &lay, hipStream_t s) {
+                           const Layouts &lay, hipStream_t s) {
     if (backward_mfma_supported(dtype, D, W))
         return launch_backward_mfma(q, k, v, o, lse, dO, dq, dk, dv, dalpha, dtheta, delta_ws, partials,
                                     terms, BH, hd, T, W, rt, rtp, rf, lay, s);
-    hipError_t e = launch_backward_generic(dtype, D, q, k, v, o, lse, dO, dq, dk, dv, dalpha, dtheta, delta_ws,
-                                           partials, BH, hd, T, W, rt, rtp, rf, lay, s);
-    // R^T on dk in place: the gradient w.r.t. the unrotated k (R^T is linear, so it also
-    // carries the group sum)
-    if (e == hipSuccess && rf.on)
-        e = launch_rope(dtype, D, dk, dk, lay.dk, lay.dk, nullptr, nullptr, lay.dk, lay.dk, BH / hd.G, hd.kv_heads(),
-                        T, rope_base, 1, s);
-    return e;
+    return launch_backward_generic(dtype, D, q, k, v, o, lse, dO, dq, dk, dv, dalpha, dtheta, delta_ws,
+                                   partials, BH, hd, T, W, rt, rtp, rf, lay, s);
 }
 
 }  // namespace fibattn

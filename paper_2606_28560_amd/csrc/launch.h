@@ -51,7 +51,7 @@ hipError_t launch_backward(int dtype, int D, const void *q, const void *k, const
                            void *dv, float *dalpha, float *dtheta, float *delta_ws, double *partials,
                            const RungTerms &terms, int BH, const Heads &hd, int T, int W,
                            const RungTable &rt, const RungTable *rtp, const RopeFreq &rf,
-                           float rope_base, const Layouts &lay, hipStream_t s);
+                           const Layouts &lay, hipStream_t s);
 
 // bfloat16, d_head = 64, W <= 16: matrix-core band + VALU rungs (fwd_mfma.hip, bwd_mfma.hip).
 bool forward_mfma_supported(int dtype, int D, int W);

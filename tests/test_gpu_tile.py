@@ -6,6 +6,7 @@ query heads side by side, more rungs than a wave has row groups, and strided pla
 import pytest
 import torch
 
+import oracle
 from paper_2606_28560_amd import fibattn as F
 from paper_2606_28560_amd import inputs, schedules
 from tests.parity import compare, gpu_run, oracle_run
@@ -70,3 +71,50 @@ def test_tile_strides(D, dtype, W):
     torch.cuda.synchronize()
     assert torch.equal(got.contiguous(), want) and torch.equal(lse, want_lse)
     assert torch.isnan(out[..., D:]).all()
+
+
+@pytest.mark.parametrize("B,H,Hkv,T,D,dtype,W,base,alpha", [
+    (1, 2, 1, 150, 64, "bf16", 40, FIB, 0.9),
+    (1, 2, 2, 150, 64, "bf16", 20, FIB, 1.0),
+    (1, 2, 2, 90, 128, "bf16", 8, FIB, 1.0),
+    (1, 2, 2, 90, 32, "bf16", 12, POW2, 0.8),
+    (1, 2, 1, 90, 64, "fp32", 9, FIB, 0.9),
+    (1, 1, 1, 90, 128, "fp32", 40, FIB, 1.0),
+])
+def test_tile_unattended_rows_that_are_not_finite(B, H, Hkv, T, D, dtype, W, base, alpha):
+    # key j is NaN in K and inf in V: queries that do not attend it keep the results they
+    # have with finite rows there, and those that do are not finite
+    x = inputs.attention_inputs(B, H, T, D, dtype, 870, 0, names=("q", "dO"))
+    x.update(inputs.attention_inputs(B, Hkv, T, D, dtype, 870, 0, names=("k", "v")))
+    j = T // 2 + 3
+    seen = torch.zeros(T, dtype=torch.bool)
+    seen[j : j + W + 1] = True
+    for d0, w, _, _ in oracle.rungs(alpha, base, W):
+        seen[j + d0 : j + d0 + 1] = True
+        # row r1: attended when w != 0, and read for dalpha (with weight w = 0 times it) else
+        seen[j + d0 + 1 : j + d0 + 2] = True
+    want = gpu_run(x["q"], x["k"], x["v"], x["dO"], W, base, alpha)
+    x["k"][:, :, j], x["v"][:, :, j] = float("nan"), float("inf")
+    got = gpu_run(x["q"], x["k"], x["v"], x["dO"], W, base, alpha)
+    for n in ("o", "lse", "dq"):
+        a, b = torch.from_numpy(got[n])[:, :, ~seen], torch.from_numpy(want[n])[:, :, ~seen]
+        # the rows added again row by row: another order of the same sums
+        scale = b.abs().max()
+        assert torch.isfinite(a).all(), n
+        assert (a - b).abs().max() <= (1e-5 if dtype == "fp32" else 1e-2) * scale, n
+    assert not torch.isfinite(torch.from_numpy(got["o"])[:, :, j : j + W + 1]).all(-1).any()
+    # query j is NaN in q and dO: keys it does not attend keep their gradients
+    x["k"][:, :, j], x["v"][:, :, j] = 0.5, 0.5
+    want = gpu_run(x["q"], x["k"], x["v"], x["dO"], W, base, alpha)
+    x["q"][:, :, j], x["dO"][:, :, j] = float("nan"), float("nan")
+    got = gpu_run(x["q"], x["k"], x["v"], x["dO"], W, base, alpha)
+    seen = torch.zeros(T, dtype=torch.bool)
+    seen[max(j - W, 0) : j + 1] = True
+    for d0, w, _, _ in oracle.rungs(alpha, base, W):
+        if j - d0 >= 0:
+            seen[max(j - d0 - (w != 0), 0) : j - d0 + 1] = True
+    for n in ("dk", "dv"):
+        a, b = torch.from_numpy(got[n])[:, :, ~seen], torch.from_numpy(want[n])[:, :, ~seen]
+        assert torch.isfinite(a).all(), n
+        assert (a - b).abs().max() <= (1e-5 if dtype == "fp32" else 1e-2) * b.abs().max(), n
+        assert not torch.isfinite(torch.from_numpy(got[n])[:, :, j - W : j + 1]).all(-1).any(), n
