@@ -188,6 +188,36 @@ __device__ __forceinline__ void rope_cs_f32(int t, double fr, float &c, float &s
     c = (quad == 1 || quad == 2) ? -w : w;
 }
 
+// The same angle with its Taylor series in float64 (first dropped terms below 2e-16 at
+// pi / 4), so cos and sin are the exact values rounded to float32 once.
+__device__ __forceinline__ void rope_cs_f64(int t, double fr, float &c, float &s) {
+    const double a = (double)t * fr;
+    const double n = rint(4.0 * a);  // quarter turns
+    const double x = (a - 0.25 * n) * 6.283185307179586476925286766559;
+    const double x2 = x * x;
+    double sx = -1.0 / 1307674368000.0, cx = 1.0 / 20922789888000.0;  // 1/15!, 1/16!
+    sx = fma(sx, x2, 1.0 / 6227020800.0);
+    sx = fma(sx, x2, -1.0 / 39916800.0);
+    sx = fma(sx, x2, 1.0 / 362880.0);
+    sx = fma(sx, x2, -1.0 / 5040.0);
+    sx = fma(sx, x2, 1.0 / 120.0);
+    sx = fma(sx, x2, -1.0 / 6.0);
+    sx = fma(sx * x2, x, x);
+    cx = fma(cx, x2, -1.0 / 87178291200.0);
+    cx = fma(cx, x2, 1.0 / 479001600.0);
+    cx = fma(cx, x2, -1.0 / 3628800.0);
+    cx = fma(cx, x2, 1.0 / 40320.0);
+    cx = fma(cx, x2, -1.0 / 720.0);
+    cx = fma(cx, x2, 1.0 / 24.0);
+    cx = fma(cx, x2, -0.5);
+    cx = fma(cx, x2, 1.0);
+    const int quad = (int)(long long)n & 3;
+    const float fs = (float)sx, fc = (float)cx;
+    const float u = quad & 1 ? fc : fs, w = quad & 1 ? fs : fc;
+    s = quad & 2 ? -u : u;
+    c = (quad == 1 || quad == 2) ? -w : w;
+}
+
 // RoPE rotation of the rotate-half pair (u, v) = (x_j, x_{j + D/2}) by the angle with
 // cosine c and sine s, with explicit fused multiply-adds.
 __device__ __forceinline__ void rope_rotate(float u, float v, float c, float s, float &x, float &y) {

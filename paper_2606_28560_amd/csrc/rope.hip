@@ -4,63 +4,78 @@
 // Rotate-half pairing: for j < D/2 the pair (x_j, x_{j+D/2}) of the row at position t
 // rotates by theta = t * base^(-2j/D).  A workgroup owns a few consecutive positions
 // and a group of (b, h) rows at those positions; it evaluates cos/sin of its angles
-// once, in float64, rounds them to float32 in LDS, and rotates every row with them.
+// once, rounds them to float32 in LDS, and rotates every row with them.
+#include <algorithm>
+
 #include "launch.h"
 
 namespace fibattn {
 
-constexpr int kRopeTP = 8;   // positions per workgroup (generic kernel)
-constexpr int kRopeRB = 16;  // (b, h) rows per workgroup (generic kernel)
+// blockIdx.z selects the tensor: (x0 -> y0) or (x1 -> y1), each with its own row count
+// (batch * heads) and head count (k may have fewer heads than q) and placed by its io.
+struct RopeIO {
+    Layout x, y;
+    int BH, heads;
+};
 
-template <typename S> __device__ __forceinline__ float ld1(const S *p);
-template <> __device__ __forceinline__ float ld1<float>(const float *p) { return *p; }
-template <> __device__ __forceinline__ float ld1<uint16_t>(const uint16_t *p) {
-    return __uint_as_float((uint32_t)(*p) << 16);
-}
-template <typename S> __device__ __forceinline__ void st1(S *p, float x);
-template <> __device__ __forceinline__ void st1<float>(float *p, float x) { *p = x; }
-template <> __device__ __forceinline__ void st1<uint16_t>(uint16_t *p, float x) {
-    *p = (uint16_t)f32_to_bf16(x);
-}
-
-// Generic kernel (any storage type and head size): one element pair per thread.
-// BH = batch * heads rows of positions [0, T); x and y placed by lx and ly.
-template <typename S, int D>
-__global__ __launch_bounds__(256) void rope_kernel(const S *x, S *y, int BH, int T, double rope_base,
-                                                   int transpose, int heads, Layout lx, Layout ly,
-                                                   TableJob job) {
-    constexpr int HALF = D / 2;
-    __shared__ float cs[kRopeTP * HALF], sn[kRopeTP * HALF];
-    if (job.out && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+// Any storage type and head size (bfloat16 with d_head 64 has the kernel below): a lane
+// rotates the pairs of a 16-byte piece of the row's first half and the matching piece of
+// its second half, NP heads apart by blockDim / lanes; a workgroup owns 512 / D positions,
+// one angle per thread.  The loads are issued before the angles are evaluated.
+// What bounds it: the latency of one load, one angle and one store per workgroup, and memory
+// for large tensors.  NP = 2 from 1024 workgroups on (four a CU), where fewer angles per row
+// pay; NP = 1 below, where workgroups are short.
+// Us a launch, against one element pair per thread with float64 pow and sincos: bf16 d 128
+// B2 H16 T2000 20.2 -> 5.0; bf16 d 32 B8 H8 T1024 8.0 -> 4.9; fp32 d 64 B4 H8 T1024 11.4 -> 5.8.
+template <typename S, int D, int NP>
+__global__ __launch_bounds__(256) void rope_kernel(const S *x0, S *y0, const S *x1, S *y1, int T, RopeFreq rf,
+                                                   int transpose, RopeIO io0, RopeIO io1, TableJob job) {
+    constexpr int HALF = D / 2, TP = 256 / HALF, VN = Vec<S>::N;
+    constexpr int LPR = HALF / VN;              // lanes per row
+    constexpr int HR = 256 / (LPR * TP);        // heads per pass
+    __shared__ float cs[256], sn[256];
+    if (job.out && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0)
         table_from_theta(job.theta, job.alpha, job.b, job.W, job.out);
-    const int t0 = blockIdx.x * kRopeTP;
-    for (int a = threadIdx.x; a < kRopeTP * HALF; a += 256) {
-        const int t = t0 + a / HALF;
-        const int jj = a % HALF;
-        const double inv_freq = pow(rope_base, -2.0 * (double)jj / (double)D);
-        const double ang = (double)t * inv_freq;
-        double sv, cv;
-        sincos(ang, &sv, &cv);
-        cs[a] = (float)cv;
-        sn[a] = transpose ? -(float)sv : (float)sv;
-    }
-    __syncthreads();
-    const int bh0 = blockIdx.y * kRopeRB;
-    for (int a = threadIdx.x; a < kRopeRB * kRopeTP * HALF; a += 256) {
-        const int jj = a % HALF;
-        const int tt = (a / HALF) % kRopeTP;
-        const int rr = a / (HALF * kRopeTP);
-        const int t = t0 + tt;
-        const int bh = bh0 + rr;
-        if (t >= T || bh >= BH) continue;
-        const S *xr = x + lx.head(bh, heads) + (long long)t * lx.st;
-        S *yr = y + ly.head(bh, heads) + (long long)t * ly.st;
-        const float c = cs[tt * HALF + jj], s = sn[tt * HALF + jj];
-        const float u = ld1<S>(xr + jj);
-        const float w = ld1<S>(xr + jj + HALF);
-        st1<S>(yr + jj, u * c - w * s);
-        st1<S>(yr + jj + HALF, w * c + u * s);
-    }
+    const S *x = blockIdx.z ? x1 : x0;
+    S *y = blockIdx.z ? y1 : y0;
+    const RopeIO &io = blockIdx.z ? io1 : io0;
+    const int col = VN * (threadIdx.x % LPR), tt = threadIdx.x / LPR % TP, hh = threadIdx.x / (LPR * TP);
+    // one pass each unless the grid had to be cut to its limits
+    for (long long t0 = (long long)blockIdx.x * TP; t0 < T; t0 += (long long)gridDim.x * TP)
+        for (int b = blockIdx.y; b * HR * NP < io.BH; b += gridDim.y) {
+            const int t = (int)min(t0 + tt, (long long)T - 1), bh0 = b * HR * NP + hh;
+            float u[NP][VN], w[NP][VN];
+#pragma unroll
+            for (int n = 0; n < NP; ++n) {
+                const S *p = x + io.x.head(min(bh0 + n * HR, io.BH - 1), io.heads) + t * io.x.st + col;
+                Vec<S>::load(p, u[n]);
+                Vec<S>::load(p + HALF, w[n]);
+            }
+            if (b == (int)blockIdx.y) {
+                float c, s;
+                rope_cs_f64((int)t0 + (int)threadIdx.x / HALF,
+                            rf.inv[threadIdx.x % HALF] * 0.15915494309189533576888376337251, c, s);
+                __syncthreads();  // the angles of the positions before are done with
+                cs[threadIdx.x] = c;
+                sn[threadIdx.x] = transpose ? -s : s;
+                __syncthreads();
+            }
+            if (t0 + tt >= T) continue;
+#pragma unroll
+            for (int n = 0; n < NP; ++n) {
+                if (bh0 + n * HR >= io.BH) continue;
+                float ox[VN], oy[VN];
+#pragma unroll
+                for (int e = 0; e < VN; ++e) {
+                    const float c = cs[tt * HALF + col + e], s = sn[tt * HALF + col + e];
+                    ox[e] = u[n][e] * c - w[n][e] * s;
+                    oy[e] = w[n][e] * c + u[n][e] * s;
+                }
+                S *p = y + io.y.head(bh0 + n * HR, io.heads) + t * io.y.st + col;
+                Vec<S>::store(p, ox);
+                Vec<S>::store(p + HALF, oy);
+            }
+        }
 }
 
 // bfloat16, d_head 64: a workgroup owns 4 NP positions of 16 (b, h) rows; each lane group
@@ -82,13 +97,7 @@ __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((rope_f32x2){lo, hi}, rope_bf16x2));
 }
 
-// blockIdx.z selects the tensor: (x0 -> y0) or (x1 -> y1), each with its own row count
-// (batch * heads) and head count (k may have fewer heads than q) and placed by its io
-// (STRIDED; else every tensor is packed [BH, T, 64]).
-struct RopeIO {
-    Layout x, y;
-    int BH, heads;
-};
+// STRIDED: rows placed by the io's layouts (else every tensor is packed [BH, T, 64]).
 template <bool STRIDED, int NP>
 __global__ __launch_bounds__(256) void rope_bf16_d64_kernel(const uint16_t *x0, uint16_t *y0,
                                                             const uint16_t *x1, uint16_t *y1,
@@ -156,22 +165,16 @@ RopeFreq make_rope_freq(double rope_base, int D) {
     return rf;
 }
 
-static hipError_t launch_rope_generic(int dtype, int D, const void *x, void *y, int BH, int T,
-                                      double lb, int transpose, int heads, const Layout &lx,
-                                      const Layout &ly, const TableJob &job, hipStream_t s) {
-    dim3 grid((T + kRopeTP - 1) / kRopeTP, (BH + kRopeRB - 1) / kRopeRB);
-#define FIBATTN_ROPE(S, DD)                                                                          \
-    if ((dtype == 0) == (sizeof(S) == 4) && D == DD)                                                  \
-        return launch(kRope, rope_kernel<S, DD>, grid, dim3(256), 0, s, x, y, BH, T, lb, transpose, \
-                      heads, lx, ly, job);
-    FIBATTN_ROPE(float, 32)
-    FIBATTN_ROPE(float, 64)
-    FIBATTN_ROPE(float, 128)
-    FIBATTN_ROPE(uint16_t, 32)
-    FIBATTN_ROPE(uint16_t, 64)
-    FIBATTN_ROPE(uint16_t, 128)
-#undef FIBATTN_ROPE
-    return hipErrorInvalidValue;
+template <typename S, int D>
+static hipError_t launch_rope_t(const void *x0, void *y0, const void *x1, void *y1, int T, const RopeFreq &rf,
+                                int transpose, const RopeIO &io0, const RopeIO &io1, const TableJob &job,
+                                hipStream_t s) {
+    constexpr int TP = 512 / D, HR = 256 * Vec<S>::N / (D / 2 * TP);
+    const int rows = x1 ? std::max(io0.BH, io1.BH) : io0.BH, nt = T / TP + (T % TP != 0), z = x1 ? 2 : 1;
+    const int np = (long long)nt * ((rows + 2 * HR - 1) / (2 * HR)) * z >= 1024 ? 2 : 1;
+    return launch(kRope, np == 2 ? rope_kernel<S, D, 2> : rope_kernel<S, D, 1>,
+                  dim3(std::min(nt, 1 << 22), std::min((rows + np * HR - 1) / (np * HR), 65535), z), dim3(256), 0, s, (const S *)x0, (S *)y0,
+                  (const S *)x1, (S *)y1, T, rf, transpose, io0, io1, job);
 }
 
 // One launch for one tensor (x1 == nullptr) or two tensors (BH1 rows of heads1 heads for
@@ -203,10 +206,18 @@ hipError_t launch_rope(int dtype, int D, const void *x0, void *y0, const Layout 
                       dim3(256), 0, s, x0, y0, x1, y1, T, rf, transpose, RopeIO{lx0, ly0, BH, heads},
                       RopeIO{lx1, ly1, BH1, heads1}, tj);
     }
-    hipError_t e = launch_rope_generic(dtype, D, x0, y0, BH, T, lb, transpose, heads, lx0, ly0, tj, s);
-    if (e == hipSuccess && x1)
-        e = launch_rope_generic(dtype, D, x1, y1, BH1, T, lb, transpose, heads1, lx1, ly1, nojob, s);
-    return e;
+    const RopeFreq rf = make_rope_freq(lb, D);
+    const RopeIO io0{lx0, ly0, BH, heads}, io1{lx1, ly1, BH1, heads1};
+#define FIBATTN_ROPE(S, DD)                                                    \
+    if ((dtype == 0) == (sizeof(S) == 4) && D == DD)                           \
+        return launch_rope_t<S, DD>(x0, y0, x1, y1, T, rf, transpose, io0, io1, tj, s);
+    FIBATTN_ROPE(float, 32)
+    FIBATTN_ROPE(float, 64)
+    FIBATTN_ROPE(float, 128)
+    FIBATTN_ROPE(uint16_t, 32)
+    FIBATTN_ROPE(uint16_t, 128)
+#undef FIBATTN_ROPE
+    return hipErrorInvalidValue;
 }
 
 }  // namespace fibattn
