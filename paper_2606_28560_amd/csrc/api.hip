@@ -203,24 +203,13 @@ static fibattn_status_t forward_rope_q_impl(const void *q, const void *k, const 
         !aligned16(q_out) || !aligned16(rtp))
         return FIBATTN_ERR_INVALID_ARG;
     if (!(rope_base > 1.f) || !isfinite(rope_base)) return FIBATTN_ERR_INVALID_ARG;
-    const bool on_load = forward_mfma_supported((int)dtype, d_head, W);
-    if (!on_load && !q_out) return FIBATTN_ERR_UNSUPPORTED;  // the rotated rows need a home
-    const Heads hd{H, H / H_kv};
-    hipError_t e;
-    if (on_load) {
-        // one launch: each query row is rotated where the forward loads it
-        const RopeFreq rf = make_rope_freq((double)rope_base, d_head);
-        e = launch_forward_mfma(q, k, v, o, lse, B * H, hd, T, W, rt, rtp, lay, stream, &rf, q_out);
-    } else {
-        // the RoPE launch on q into q_out, then the forward on it
-        if ((long long)B * H > 65535ll * 16) return FIBATTN_ERR_UNSUPPORTED;
-        e = launch_rope((int)dtype, d_head, q, q_out, lay.q, lay.dq, nullptr, nullptr, lay.q, lay.dq, B * H, H,
-                        T, rope_base, 0, stream);
-        Layouts lr = lay;
-        lr.q = lay.dq;
-        if (e == hipSuccess)
-            e = launch_forward((int)dtype, d_head, q_out, k, v, o, lse, B * H, hd, T, W, rt, rtp, lr, stream);
-    }
+    // the rotated rows need a home, except on the path that keeps none for the backward
+    const bool no_copy = forward_mfma_supported((int)dtype, d_head, W);
+    if (!no_copy && (!q_out || (long long)B * H > 65535ll * 16)) return FIBATTN_ERR_UNSUPPORTED;
+    // one launch: each query row is rotated where the forward loads it
+    const RopeFreq rf = make_rope_freq((double)rope_base, d_head);
+    const hipError_t e = launch_forward((int)dtype, d_head, q, k, v, o, lse, B * H, Heads{H, H / H_kv}, T, W, rt, rtp,
+                                        lay, stream, &rf, q_out);
     return e == hipSuccess ? FIBATTN_OK : FIBATTN_ERR_HIP;
 }
 

@@ -38,15 +38,18 @@ constexpr int fwd_waves = Tile<S, D>::NC <= 2 ? 4 : Tile<S, D>::NC == 4 ? 3 : 2;
 
 // INTERP: some rung has w != 0, so the second row r1 is read; otherwise two rungs are
 // taken together.  DEV: the rung table is the one at rtp, built on the device (rt_arg
-// unused).
+// unused).  rf.on: q holds unrotated rows; each is rotated where it is loaded (a query row
+// is used by one query only) and written to qrot, placed by lay.dq, for the backward: 2 to 4
+// us more here against 5 to 7 us for a launch of its own.
 template <typename S, int D, bool INTERP, bool DEV>
 __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     const S *__restrict__ q, const S *__restrict__ k, const S *__restrict__ v, S *__restrict__ o,
     float *__restrict__ lse, int T, int W, RungTable rt_arg, const RungTable *__restrict__ rtp, float sl2,
-    TileShape ts, Heads hd, Layouts lay) {
+    TileShape ts, Heads hd, Layouts lay, S *qrot, RopeFreq rf) {
     using TL = Tile<S, D>;
     using Slice = typename TL::Slice;
     const RungTable &rt = DEV ? *rtp : rt_arg;
+    __shared__ double sfreq[D / 2];
     constexpr int RB = INTERP ? 1 : 2;          // rungs per batch: two rows of K and of V
     constexpr int NBUF = TL::NC <= 2 ? 2 : 1;   // batches in flight
     extern __shared__ __align__(16) char smem[];
@@ -69,7 +72,11 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     const int t0 = T0 + 16 * wv;
     const int im = t0 + nm;                        // MFMA layout query
     const int i = t0 + nq, ic = min(i, T - 1);     // quad layout query
-    const Slice qq = TL::load(Q, ic, gq, (uint32_t)(lay.q.st * (int)sizeof(S)));
+    Slice qq = TL::load(Q, ic, gq, (uint32_t)(lay.q.st * (int)sizeof(S)));
+    if (rf.on) {
+        if (threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
+        __syncthreads();
+    }
 
     // rungs some query of this wave includes: a prefix of the table (sorted by d)
     int nact = 0;
@@ -101,7 +108,7 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     if (TL::NC <= 2 && nact > 0) load_batch(0, V, sv, vx[0]);
 
     // ---- window band (MFMA layout) ----
-    const Slice qm = TL::from_quad(qq, lane);
+    Slice qm;
     float m = 0.f, l = 0.f;
     typename TL::Acc acc;
     TL::zero(acc);
@@ -115,6 +122,13 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
         if (c0 > 0) __syncthreads();  // every wave is done with the rows staged before
         TL::stage(kr, K, rbeg, rows, T, lay.k.st, wave, nw);
         TL::stage(vr, V, rbeg, rows, T, lay.v.st, wave, nw);
+        if (c0 == 0) {
+            if (rf.on) {  // rotated while the copies are in flight
+                TL::rope(qq, i, sfreq, gq);
+                if (i < T) TL::put(qrot + lay.dq.head(bh, hd.H) + i * lay.dq.st, gq, qq);
+            }
+            qm = TL::from_quad(qq, lane);
+        }
         wait_vmem();
         __syncthreads();
         for (int c = 0; c < n; ++c) {
@@ -253,25 +267,34 @@ template <int D, bool DEV>
 __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
     const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, float *__restrict__ o,
     float *__restrict__ lse, int T, int W, RungTable rt_arg, const RungTable *__restrict__ rtp, float sl2, int tiles,
-    Heads hd, Layouts lay) {
+    Heads hd, Layouts lay, float *qrot, RopeFreq rf) {
     using TL = Tile<float, D>;
     using Slice = typename TL::Slice;
     constexpr int NC = TL::NC;
     const RungTable &rt = DEV ? *rtp : rt_arg;
     extern __shared__ __align__(16) char smem[];
+    __shared__ double sfreq[D / 2];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nq = lane >> 2, gq = lane & 3;  // quad layout
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     const int bh = blk / tiles, t0 = (blk % tiles) * 64 + 16 * wave;
+    if (rf.on) {
+        if (threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
+        __syncthreads();
+    }
     if (t0 >= T) return;  // no barrier below
     const int bk = hd.kv_of(bh);
     const float *K = k + lay.k.head(bk, hd.kv_heads());
     const float *V = v + lay.v.head(bk, hd.kv_heads());
     const uint32_t sk = (uint32_t)(4 * lay.k.st), sv = (uint32_t)(4 * lay.v.st);
     const int i = t0 + nq, ic = min(i, T - 1), last = min(t0 + 15, T - 1);
-    const Slice qq = TL::load(q + lay.q.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.q.st));
+    Slice qq = TL::load(q + lay.q.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.q.st));
+    if (rf.on) {  // as in the tile kernel
+        TL::rope(qq, i, sfreq, gq);
+        if (i < T) TL::put(qrot + lay.dq.head(bh, hd.H) + i * lay.dq.st, gq, qq);
+    }
     int nact = 0;  // rungs some query of this wave includes: a prefix of the table
 #pragma unroll
     for (int r = 0; r < kMaxRungs; ++r) nact += ((r < rt.n) & (rt.d0[r] <= last)) ? 1 : 0;
@@ -356,12 +379,12 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
 template <int D>
 static hipError_t launch_fwd_f32(const void *q, const void *k, const void *v, void *o, float *lse, int BH,
                                  const Heads &hd, int T, int W, const RungTable &rt, const RungTable *rtp,
-                                 const Layouts &lay, hipStream_t s) {
+                                 const Layouts &lay, hipStream_t s, const RopeFreq &rf, void *q_rot) {
     const int tiles = (T + 63) / 64;
     const size_t lds = 64 * sizeof(float) * (size_t)(W + 4 + (rtp ? kMaxRungs : rt.n + 1));
     return launch(kForward, rtp ? fwd_f32_kernel<D, true> : fwd_f32_kernel<D, false>, dim3(tiles * BH), dim3(256),
                   (unsigned)lds, s, (const float *)q, (const float *)k, (const float *)v, (float *)o, lse, T, W, rt,
-                  rtp, kLog2e / sqrtf((float)D), tiles, hd, lay);
+                  rtp, kLog2e / sqrtf((float)D), tiles, hd, lay, (float *)q_rot, rf);
 }
 
 // Query heads side by side in a workgroup of nw waves, for G heads per key/value head:
@@ -384,7 +407,8 @@ int tile_chunks(int nc, size_t fixed, size_t per, int slice_pieces) {
 template <typename S, int D>
 static hipError_t launch_fwd_t(const void *q, const void *k, const void *v, void *o, float *lse,
                                int BH, const Heads &hd, int T, int W, const RungTable &rt,
-                               const RungTable *rtp, const Layouts &lay, hipStream_t s) {
+                               const RungTable *rtp, const Layouts &lay, hipStream_t s, const RopeFreq &rf,
+                               void *q_rot) {
     using TL = Tile<S, D>;
     constexpr int nw = TL::kRow == 512 ? 2 : 4;  // rows of 512 bytes: 32 queries' band in 48 KB
     TileShape ts;
@@ -400,20 +424,23 @@ static hipError_t launch_fwd_t(const void *q, const void *k, const void *v, void
     auto kern = rtp ? fwd_tile_kernel<S, D, true, true>
                     : interp ? fwd_tile_kernel<S, D, true, false> : fwd_tile_kernel<S, D, false, false>;
     return launch(kForward, kern, dim3(ts.tiles * (BH / ts.hs)), dim3(64 * nw), (unsigned)(fixed + per * ts.cps), s,
-                  (const S *)q, (const S *)k, (const S *)v, (S *)o, lse, T, W, rt, rtp, sl2, ts, hd, lay);
+                  (const S *)q, (const S *)k, (const S *)v, (S *)o, lse, T, W, rt, rtp, sl2, ts, hd, lay,
+                  (S *)q_rot, rf);
 }
 
 hipError_t launch_forward(int dtype, int D, const void *q, const void *k, const void *v, void *o,
                           float *lse, int BH, const Heads &hd, int T, int W, const RungTable &rt,
-                          const RungTable *rtp, const Layouts &lay, hipStream_t s) {
+                          const RungTable *rtp, const Layouts &lay, hipStream_t s,
+                          const RopeFreq *rq, void *q_rot) {
     if (forward_mfma_supported(dtype, D, W))
-        return launch_forward_mfma(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
-    if (dtype == 0 && D == 32) return launch_fwd_f32<32>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
-    if (dtype == 0 && D == 64) return launch_fwd_f32<64>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
-    if (dtype == 1 && D == 32) return launch_fwd_t<uint16_t, 32>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
-    if (dtype == 1 && D == 64) return launch_fwd_t<uint16_t, 64>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
-    if (dtype == 0 && D == 128) return launch_fwd_f32<128>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
-    if (dtype == 1 && D == 128) return launch_fwd_t<uint16_t, 128>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s);
+        return launch_forward_mfma(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rq, q_rot);
+    const RopeFreq rf = rq ? *rq : RopeFreq{};
+    if (dtype == 0 && D == 32) return launch_fwd_f32<32>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
+    if (dtype == 0 && D == 64) return launch_fwd_f32<64>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
+    if (dtype == 1 && D == 32) return launch_fwd_t<uint16_t, 32>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
+    if (dtype == 1 && D == 64) return launch_fwd_t<uint16_t, 64>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
+    if (dtype == 0 && D == 128) return launch_fwd_f32<128>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
+    if (dtype == 1 && D == 128) return launch_fwd_t<uint16_t, 128>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
     return hipErrorInvalidValue;
 }
 

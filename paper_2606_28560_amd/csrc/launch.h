@@ -32,10 +32,13 @@ hipError_t launch(int id, void (*kernel)(P...), dim3 grid, dim3 block, unsigned 
 
 // dtype: 0 float32, 1 bfloat16.  All launchers return hipGetLastError() of their launches.
 // BH = batch * query heads; k, v (and dk, dv) hold BH / hd.G heads.  rtp != nullptr:
-// the rung table is the device-resident one at rtp (rt unused).
+// the rung table is the device-resident one at rtp (rt unused).  rq: q is unrotated and
+// each query row is rotated with these frequencies where the forward loads it; the rotated
+// rows go to q_rot, placed by lay.dq (null: only where forward_mfma_supported).
 hipError_t launch_forward(int dtype, int D, const void *q, const void *k, const void *v, void *o,
                           float *lse, int BH, const Heads &hd, int T, int W, const RungTable &rt,
-                          const RungTable *rtp, const Layouts &lay, hipStream_t s);
+                          const RungTable *rtp, const Layouts &lay, hipStream_t s,
+                          const RopeFreq *rq = nullptr, void *q_rot = nullptr);
 
 // Tile kernels (fwd.hip, bwd.hip): query heads side by side in a workgroup of nw waves, and
 // band chunks staged at a time (tile.h).
@@ -55,8 +58,7 @@ hipError_t launch_backward(int dtype, int D, const void *q, const void *k, const
 
 // bfloat16, d_head = 64, W <= 16: matrix-core band + VALU rungs (fwd_mfma.hip, bwd_mfma.hip).
 bool forward_mfma_supported(int dtype, int D, int W);
-// rq: q is unrotated and each query row is rotated with these frequencies where the
-// forward loads it; the rotated rows go to q_rot, placed by lay.dq, unless it is null.
+// rq, q_rot: as launch_forward.
 hipError_t launch_forward_mfma(const void *q, const void *k, const void *v, void *o, float *lse,
                                int BH, const Heads &hd, int T, int W, const RungTable &rt,
                                const RungTable *rtp, const Layouts &lay, hipStream_t s,

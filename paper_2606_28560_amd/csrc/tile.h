@@ -278,6 +278,61 @@ struct Tile {
         }
     }
 
+    // RoPE of the lane's slice of a row at position t, rounded to S (as the RoPE launch
+    // rounds it); partners as in rope_t.  float32: exact cos and sin, rounded once.
+    __device__ static __forceinline__ void rope(Slice &x, int t, const double *sf, int g) {
+        if constexpr (kF32) {
+#pragma unroll
+            for (int a = 0; a < NC / 2; ++a)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float c, s, u, w;
+                    rope_cs_f64(t, sf[16 * a + 4 * g + e], c, s);
+                    rope_rotate(__uint_as_float(x.c[a][e]), __uint_as_float(x.c[a + NC / 2][e]), c, s, u, w);
+                    x.c[a][e] = __float_as_uint(u);
+                    x.c[a + NC / 2][e] = __float_as_uint(w);
+                }
+        } else if constexpr (D == 32) {
+            const bool hi = g & 2;  // this lane holds the second halves of its pairs
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t own = x.c[0][e];
+                const uint32_t oth = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0x4E, 0xF, 0xF, true);
+                float r[2];
+#pragma unroll
+                for (int z = 0; z < 2; ++z) {
+                    float c, s, u, w;
+                    rope_cs_rev(t, sf[8 * (g & 1) + 2 * e + z], c, s);
+                    const float a = z ? bf16_hi(own) : bf16_lo(own), b = z ? bf16_hi(oth) : bf16_lo(oth);
+                    rope_rotate(hi ? b : a, hi ? a : b, c, s, u, w);
+                    r[z] = hi ? w : u;
+                }
+                x.c[0][e] = pack_bf16(r[0], r[1]);
+            }
+        } else {
+#pragma unroll
+            for (int a = 0; a < NC / 2; ++a)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t uw = x.c[a][e], vw = x.c[a + NC / 2][e];
+                    float u[2], w[2];
+#pragma unroll
+                    for (int z = 0; z < 2; ++z) {
+                        float c, s;
+                        rope_cs_rev(t, sf[32 * a + 8 * g + 2 * e + z], c, s);
+                        rope_rotate(z ? bf16_hi(uw) : bf16_lo(uw), z ? bf16_hi(vw) : bf16_lo(vw), c, s, u[z], w[z]);
+                    }
+                    x.c[a][e] = pack_bf16(u[0], u[1]);
+                    x.c[a + NC / 2][e] = pack_bf16(w[0], w[1]);
+                }
+        }
+    }
+    // The lane's slice written to a row (read again by the backward: ordinary stores).
+    __device__ static __forceinline__ void put(void *row, int g, const Slice &x) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(row) + 16 * g + 64 * c) = x.c[c];
+    }
+
     // R^T (the inverse RoPE rotation) of the lane's slice at position t.  sf: revolutions
     // per position of every frequency.  The partner of dim d < D/2 is d + D/2: D/8 slice
     // positions on, except for bfloat16 rows of 32, whose partner lanes are g and g + 2.
