@@ -68,8 +68,8 @@ __global__ __launch_bounds__(256) void rope_kernel(const S *x0, S *y0, const S *
 #pragma unroll
                 for (int e = 0; e < VN; ++e) {
                     const float c = cs[tt * HALF + col + e], s = sn[tt * HALF + col + e];
-                    ox[e] = u[n][e] * c - w[n][e] * s;
-                    oy[e] = w[n][e] * c + u[n][e] * s;
+                    ox[e] = fmaf(c, u[n][e], -(s * w[n][e]));
+                    oy[e] = fmaf(s, u[n][e], c * w[n][e]);
                 }
                 S *p = y + io.y.head(bh0 + n * HR, io.heads) + t * io.y.st + col;
                 Vec<S>::store(p, ox);

@@ -288,9 +288,11 @@ struct Tile {
                 for (int e = 0; e < 4; ++e) {
                     float c, s, u, w;
                     rope_cs_f64(t, sf[16 * a + 4 * g + e], c, s);
-                    rope_rotate(__uint_as_float(x.c[a][e]), __uint_as_float(x.c[a + NC / 2][e]), c, s, u, w);
-                    x.c[a][e] = __float_as_uint(u);
-                    x.c[a + NC / 2][e] = __float_as_uint(w);
+                    // in the order of the RoPE launch: the same bits
+                    u = __uint_as_float(x.c[a][e]);
+                    w = __uint_as_float(x.c[a + NC / 2][e]);
+                    x.c[a][e] = __float_as_uint(fmaf(c, u, -(s * w)));
+                    x.c[a + NC / 2][e] = __float_as_uint(fmaf(s, u, c * w));
                 }
         } else if constexpr (D == 32) {
             const bool hi = g & 2;  // this lane holds the second halves of its pairs

@@ -118,3 +118,16 @@ def test_tile_unattended_rows_that_are_not_finite(B, H, Hkv, T, D, dtype, W, bas
         assert torch.isfinite(a).all(), n
         assert (a - b).abs().max() <= (1e-5 if dtype == "fp32" else 1e-2) * b.abs().max(), n
         assert not torch.isfinite(torch.from_numpy(got[n])[:, :, j - W : j + 1]).all(-1).any(), n
+
+
+@pytest.mark.parametrize("B,H,T,D", [(1, 2, 129, 32), (2, 3, 65, 64), (1, 1, 17, 128), (8, 16, 700, 64)])
+def test_float32_rotated_q_has_the_bits_of_the_rope_launch(B, H, T, D):
+    # float32 rows rotated where the forward loads them: the launch's angles and order (the
+    # last size takes the launch's two heads a lane), and the results of rotating before
+    x = inputs.attention_inputs(B, H, T, D, "fp32", 880, 0)
+    q, k, v = (x[n].cuda() for n in ("q", "k", "v"))
+    K, Q = F.fibattn_rope(k), F.fibattn_rope(q)
+    o, lse, got = F.fibattn_forward_rope_q(q, K, v, 12, FIB, 0.9)
+    want_o, want_lse = F.fibattn_forward(Q, K, v, 12, FIB, 0.9)
+    torch.cuda.synchronize()
+    assert torch.equal(got, Q) and torch.equal(o, want_o) and torch.equal(lse, want_lse)
