@@ -277,20 +277,4 @@ template <> struct Vec<uint16_t> {
     }
 };
 
-// Sum over the G lanes of an aligned lane group (G a power of two, G <= 64).
-template <int G>
-__device__ __forceinline__ float group_sum(float x) {
-#pragma unroll
-    for (int m = G / 2; m >= 1; m >>= 1) x += __shfl_xor(x, m, 64);
-    return x;
-}
-
-template <int N>
-__device__ __forceinline__ float dot(const float *a, const float *b) {
-    float s = 0.f;
-#pragma unroll
-    for (int c = 0; c < N; ++c) s = fmaf(a[c], b[c], s);
-    return s;
-}
-
 }  // namespace fibattn

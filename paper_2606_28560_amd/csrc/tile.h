@@ -177,17 +177,26 @@ struct Tile {
         for (int x = 0; x < NC; ++x) s.c[x] = *reinterpret_cast<const u32x4 *>(chunk(buf, r, 4 * x + g));
         return s;
     }
+    // A buffer laid out for the quad layout (stage with quad), whose eight neighbouring lanes
+    // read four chunks each of two consecutive rows: slot c ^ 4 (r & 1).
+    __device__ static __forceinline__ Slice staged_quad(const char *buf, int r, int g) {
+        Slice s;
+#pragma unroll
+        for (int x = 0; x < NC; ++x)
+            s.c[x] = *reinterpret_cast<const u32x4 *>(buf + r * kRow + 16 * ((4 * x + g) ^ (4 * (r & 1))));
+        return s;
+    }
     // Rows [r_begin, r_begin + nrows) of rows `st` elements apart, copied by direct-to-LDS
     // loads (1 KB per wave and instruction; nrows is a multiple of 16).  Rows outside [0, T)
     // are clamped copies of real rows: callers mask them.
     __device__ static __forceinline__ void stage(char *buf, const S *X, int r_begin, int nrows, int T, long long st,
-                                                 int wave, int nwaves) {
+                                                 int wave, int nwaves, bool quad = false) {
         const int lane = threadIdx.x & 63;
         constexpr int per = kRow / 16;  // chunks per row
         const int nblk = nrows * kRow / 1024;
         for (int blk = wave; blk < nblk; blk += nwaves) {
             const int u = blk * 64 + lane;
-            const int rr = u / per, ch = (u % per) ^ swz(rr);
+            const int rr = u / per, ch = (u % per) ^ (quad ? 4 * (rr & 1) : swz(rr));
             const int row = min(max(r_begin + rr, 0), T - 1);
             __builtin_amdgcn_global_load_lds(X + row * st + ch * (16 / (int)sizeof(S)),
                                              (__attribute__((address_space(3))) void *)(buf + 1024 * blk), 16, 0, 0);
@@ -400,27 +409,6 @@ __device__ __forceinline__ float row_dot(const typename Tile<float, D>::Slice &x
 #pragma unroll
     for (int c = 0; c < NC; ++c) t[c] = chunk_dot(x.c[c], y.c[c]);
     return chunk_sum<NC>(t);
-}
-
-// Probabilities p = exp(tau s - lse) of the backward, as exp2(s sl2 - lse log2e) with the
-// forward's sl2 = fl(tau log2e) (whose rounding the saved lse shares).  float32 rows: what
-// the rounding of lse log2e loses, which would move every probability of a query alike, is
-// carried along (in natural units) and multiplied back in.
-struct Lse2 {
-    float v, low;
-};
-template <bool F32>
-__device__ __forceinline__ Lse2 lse_log2(float lse) {
-    Lse2 r;
-    r.v = lse * kLog2e;
-    // kLog2e + 1.925963e-8 = log2(e)
-    r.low = F32 ? fmaf(lse, 1.925963033500e-8f, fmaf(lse, kLog2e, -r.v)) * kLn2 : 0.f;
-    return r;
-}
-template <bool F32>
-__device__ __forceinline__ float prob(float sl2, float s, const Lse2 &l) {
-    const float p = fast_exp2(fmaf(s, sl2, -l.v));
-    return F32 ? fmaf(p, -l.low, p) : p;
 }
 
 // Weight and lane bookkeeping of a launch: `nw` waves per workgroup are `hs` query heads
