@@ -69,7 +69,8 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
     const int nw = blockDim.x >> 6;
     const int nm = lane & 15, gm = lane >> 4;  // MFMA layout
     const int nq = lane >> 2, gq = lane & 3;   // quad layout
-    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    if (block_number() >= ts.blocks) return;
+    const int blk = xcd_remap(block_number(), ts.blocks);
     const int runs = nw / ts.hs, wv = wave / ts.hs;
     const int bh = (blk / ts.tiles) * ts.hs + wave % ts.hs;  // this wave's query head
     const int T0 = (blk % ts.tiles) * 16 * runs;
@@ -258,7 +259,7 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
     if (threadIdx.x == 0) {
         double s = red[0];
         for (int u = 1; u < nw; ++u) s += red[u];
-        partials[blockIdx.x] = s;
+        partials[block_number()] = s;
     }
 }
 
@@ -274,8 +275,8 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
     const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
     const float *__restrict__ o, const float *__restrict__ lse, const float *__restrict__ dO,
     float *__restrict__ dq, float *__restrict__ delta_out, double *__restrict__ partials, int T, int W,
-    RungTable rt_arg, const RungTable *__restrict__ rtp, RopeFreq rf, float tau, int tiles, int rows, Heads hd,
-    Layouts lay) {
+    RungTable rt_arg, const RungTable *__restrict__ rtp, RopeFreq rf, float tau, int tiles, int blocks, int rows,
+    Heads hd, Layouts lay) {
     using TL = Tile<float, D>;
     using Slice = typename TL::Slice;
     const RungTable &rt = DEV ? *rtp : rt_arg;
@@ -286,7 +287,8 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nq = lane >> 2, gq = lane & 3;  // quad layout
-    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    if (block_number() >= blocks) return;
+    const int blk = xcd_remap(block_number(), blocks);
     const int bh = blk / tiles, T0 = (blk % tiles) * 64, t0 = T0 + 16 * wave;
     const int bk = hd.kv_of(bh);
     const float *K = k + lay.k.head(bk, hd.kv_heads());
@@ -379,7 +381,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
     for (int st = 32; st >= 1; st >>= 1) dal += __shfl_xor(dal, st, 64);
     if (lane == 0) red[wave] = dal;
     __syncthreads();
-    if (threadIdx.x == 0) partials[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+    if (threadIdx.x == 0) partials[block_number()] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
 // ---------------------------------------------------------------------------
@@ -426,7 +428,8 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
     const int nw = blockDim.x >> 6;
     const int nm = lane & 15, gm = lane >> 4;  // MFMA layout
     const int nq = lane >> 2, gq = lane & 3;   // quad layout
-    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    if (block_number() >= ts.blocks) return;
+    const int blk = xcd_remap(block_number(), ts.blocks);
     const int runs = nw / ts.hs, wv = wave / ts.hs, hs = wave % ts.hs;  // run of keys, head slot
     const int bk = blk / ts.tiles;  // batch * key/value heads + key/value head
     const int T0 = (blk % ts.tiles) * 16 * runs;
@@ -438,7 +441,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
     if (rf.on && threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
 
     // dalpha: the partials of the dq kernel, which has completed, in a fixed order
-    if (blockIdx.x == 0) {
+    if (block_number() == 0) {
         double *red = reinterpret_cast<double *>(smem);
         double s = 0.0;
         for (int t = threadIdx.x; t < n_partials; t += blockDim.x) s += partials[t];
@@ -715,10 +718,11 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
     ts.hs = tile_heads(hd.G, nw);
     const int runs = nw / ts.hs;
     ts.tiles = (T + 16 * runs - 1) / (16 * runs);
+    ts.blocks = ts.tiles * (BH / ts.hs);
     ts.nc = band_chunks(W);
     const size_t fixed = 2 * (size_t)16 * (runs - 1) * TL::kRow, per = 2 * (size_t)32 * TL::kRow;
     ts.cps = tile_chunks(ts.nc, fixed, per, TL::NC);
-    int nb = ts.tiles * (BH / ts.hs);  // dq workgroups = dalpha partials
+    int nb = ts.blocks;  // dq workgroups = dalpha partials
     bool interp = false;
     for (int r = 0; r < rt.n && !interp; ++r) interp = rt.w[r] != 0.f;
     hipError_t e;
@@ -728,13 +732,13 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
         int rows = 64 + ((W + 15) & ~15);
         if (2 * (size_t)rows * TL::kRow > 78 * 1024) rows = 0;
         nb = tiles * BH;
-        e = launch(kBwdDq, rtp ? bwd_dq_f32_kernel<D, true> : bwd_dq_f32_kernel<D, false>, dim3(nb), dim3(256),
+        e = launch(kBwdDq, rtp ? bwd_dq_f32_kernel<D, true> : bwd_dq_f32_kernel<D, false>, grid_of(nb), dim3(256),
                    (unsigned)(2 * rows * TL::kRow), s, (const S *)q, (const S *)k, (const S *)v, (const S *)o, lse,
-                   (const S *)dO, (S *)dq, delta_ws, partials, T, W, rt, rtp, rf, tau, tiles, rows, hd, lay);
+                   (const S *)dO, (S *)dq, delta_ws, partials, T, W, rt, rtp, rf, tau, tiles, nb, rows, hd, lay);
     } else {
         auto dqk = rtp ? bwd_dq_tile_kernel<S, D, true, true>
                        : interp ? bwd_dq_tile_kernel<S, D, true, false> : bwd_dq_tile_kernel<S, D, false, false>;
-        e = launch(kBwdDq, dqk, dim3(nb), dim3(64 * nw), (unsigned)(fixed + per * ts.cps), s, (const S *)q,
+        e = launch(kBwdDq, dqk, grid_of(nb), dim3(64 * nw), (unsigned)(fixed + per * ts.cps), s, (const S *)q,
                    (const S *)k, (const S *)v, (const S *)o, lse, (const S *)dO, (S *)dq, delta_ws, partials, T, W,
                    rt, rtp, rf, tau, kLog2e / sqrtf((float)D), ts, hd, lay);
     }
@@ -744,12 +748,13 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
     TileShape tk = ts;
     const size_t row = 2 * TL::kRow + 2 * sizeof(float);
     const size_t kfixed = row * ts.hs * 16 * (runs - 1), kper = row * ts.hs * 32;
+    tk.blocks = ts.tiles * (BH / hd.G);
     tk.cps = tile_chunks(ts.nc, kfixed, kper, TL::NC);
     const size_t sums = (size_t)(nw - runs) * 64 * 2 * sizeof(typename TL::Acc);
     const size_t lds = std::max({kfixed + kper * tk.cps, sums, 64 * nw * sizeof(double)});
     auto dkk = rtp ? bwd_dkdv_tile_kernel<S, D, true, true>
                    : interp ? bwd_dkdv_tile_kernel<S, D, true, false> : bwd_dkdv_tile_kernel<S, D, false, false>;
-    return launch(kBwdDkDv, dkk, dim3(ts.tiles * (BH / hd.G)), dim3(64 * nw), (unsigned)lds, s, (const S *)q,
+    return launch(kBwdDkDv, dkk, grid_of(tk.blocks), dim3(64 * nw), (unsigned)lds, s, (const S *)q,
                   (const S *)k, (const S *)v, lse, (const S *)dO, delta_ws, (S *)dk, (S *)dv, partials, nb, dalpha,
                   dtheta, T, W, rt, rtp, rf, tau, kLog2e / sqrtf((float)D), tk, hd, lay);
 }

@@ -59,7 +59,8 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     const int nw = blockDim.x >> 6;
     const int nm = lane & 15, gm = lane >> 4;  // MFMA layout
     const int nq = lane >> 2, gq = lane & 3;   // quad layout
-    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    if (block_number() >= ts.blocks) return;
+    const int blk = xcd_remap(block_number(), ts.blocks);
     const int runs = nw / ts.hs, wv = wave / ts.hs;
     const int bh = (blk / ts.tiles) * ts.hs + wave % ts.hs;  // this wave's query head
     const int T0 = (blk % ts.tiles) * 16 * runs;
@@ -267,7 +268,7 @@ template <int D, bool DEV>
 __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
     const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, float *__restrict__ o,
     float *__restrict__ lse, int T, int W, RungTable rt_arg, const RungTable *__restrict__ rtp, float sl2, int tiles,
-    Heads hd, Layouts lay, float *qrot, RopeFreq rf) {
+    int blocks, Heads hd, Layouts lay, float *qrot, RopeFreq rf) {
     using TL = Tile<float, D>;
     using Slice = typename TL::Slice;
     constexpr int NC = TL::NC;
@@ -278,7 +279,8 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nq = lane >> 2, gq = lane & 3;  // quad layout
-    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    if (block_number() >= blocks) return;
+    const int blk = xcd_remap(block_number(), blocks);
     const int bh = blk / tiles, t0 = (blk % tiles) * 64 + 16 * wave;
     if (rf.on) {
         if (threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
@@ -382,9 +384,9 @@ static hipError_t launch_fwd_f32(const void *q, const void *k, const void *v, vo
                                  const Layouts &lay, hipStream_t s, const RopeFreq &rf, void *q_rot) {
     const int tiles = (T + 63) / 64;
     const size_t lds = 64 * sizeof(float) * (size_t)(W + 4 + (rtp ? kMaxRungs : rt.n + 1));
-    return launch(kForward, rtp ? fwd_f32_kernel<D, true> : fwd_f32_kernel<D, false>, dim3(tiles * BH), dim3(256),
+    return launch(kForward, rtp ? fwd_f32_kernel<D, true> : fwd_f32_kernel<D, false>, grid_of((long long)tiles * BH), dim3(256),
                   (unsigned)lds, s, (const float *)q, (const float *)k, (const float *)v, (float *)o, lse, T, W, rt,
-                  rtp, kLog2e / sqrtf((float)D), tiles, hd, lay, (float *)q_rot, rf);
+                  rtp, kLog2e / sqrtf((float)D), tiles, tiles * BH, hd, lay, (float *)q_rot, rf);
 }
 
 // Query heads side by side in a workgroup of nw waves, for G heads per key/value head:
@@ -415,6 +417,7 @@ static hipError_t launch_fwd_t(const void *q, const void *k, const void *v, void
     ts.hs = tile_heads(hd.G, nw);
     const int runs = nw / ts.hs;
     ts.tiles = (T + 16 * runs - 1) / (16 * runs);
+    ts.blocks = ts.tiles * (BH / ts.hs);
     ts.nc = band_chunks(W);
     const size_t fixed = 2 * (size_t)16 * (runs - 1) * TL::kRow, per = 2 * (size_t)32 * TL::kRow;
     ts.cps = tile_chunks(ts.nc, fixed, per, TL::NC);
@@ -423,7 +426,7 @@ static hipError_t launch_fwd_t(const void *q, const void *k, const void *v, void
     const float sl2 = kLog2e / sqrtf((float)D);
     auto kern = rtp ? fwd_tile_kernel<S, D, true, true>
                     : interp ? fwd_tile_kernel<S, D, true, false> : fwd_tile_kernel<S, D, false, false>;
-    return launch(kForward, kern, dim3(ts.tiles * (BH / ts.hs)), dim3(64 * nw), (unsigned)(fixed + per * ts.cps), s,
+    return launch(kForward, kern, grid_of(ts.blocks), dim3(64 * nw), (unsigned)(fixed + per * ts.cps), s,
                   (const S *)q, (const S *)k, (const S *)v, (S *)o, lse, T, W, rt, rtp, sl2, ts, hd, lay,
                   (S *)q_rot, rf);
 }

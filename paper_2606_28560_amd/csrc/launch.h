@@ -30,6 +30,13 @@ hipError_t launch(int id, void (*kernel)(P...), dim3 grid, dim3 block, unsigned 
     return hipGetLastError();
 }
 
+// Grid of `blocks` workgroups of up to 256 threads: one row, or rows of 2^23 (a dimension
+// times the workgroup's threads stays below 2^32); kernels drop the last row's excess.
+inline dim3 grid_of(long long blocks) {
+    const long long x = blocks < (1ll << 23) ? blocks : 1ll << 23;
+    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+}
+
 // dtype: 0 float32, 1 bfloat16.  All launchers return hipGetLastError() of their launches.
 // BH = batch * query heads; k, v (and dk, dv) hold BH / hd.G heads.  rtp != nullptr:
 // the rung table is the device-resident one at rtp (rt unused).  rq: q is unrotated and

@@ -414,11 +414,15 @@ __device__ __forceinline__ float row_dot(const typename Tile<float, D>::Slice &x
 // Weight and lane bookkeeping of a launch: `nw` waves per workgroup are `hs` query heads
 // of one group (all reading the same rows) times nw / hs runs of 16 rows.
 struct TileShape {
+    int blocks; // workgroups
     int tiles;  // workgroups along the sequence
     int hs;     // query heads side by side
     int nc;     // 32-row band chunks: they cover W + 16 rows
     int cps;    // chunks staged at a time
 };
+
+// This workgroup's number in a grid_of grid (>= the workgroup count: nothing to do).
+__device__ __forceinline__ int block_number() { return (int)(blockIdx.y * gridDim.x + blockIdx.x); }
 
 inline int band_chunks(int W) { return (W + 16 + 31) / 32; }
 
