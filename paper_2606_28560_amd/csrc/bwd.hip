@@ -22,8 +22,8 @@
 // Because every rung offset is shared, the queries that read key row j are again a
 // fixed set of shifted positions: j .. j+W through the window, and j + floor(d_k)
 // (as the row r0, weight 1-w) and j + floor(d_k) + 1 (as r1, weight w) through rung k.
-// The dk/dv kernel therefore owns one key row per lane group and gathers its
-// contributions, so every dk/dv row is written once, without atomics.
+// The dk/dv kernel therefore keeps its key rows and gathers their contributions, so
+// every dk/dv row is written once, without atomics.
 #include <algorithm>
 
 #include "launch.h"
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
     const float sl2 = tau * kLog2e;
     const Slice qq = TL::load(q + lay.q.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.q.st));
     const Slice gg = TL::load(dO + lay.g.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.g.st));
-    const float delta = row_dot<D>(gg, TL::load(o + lay.o.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.o.st)));
+    const float delta = TL::quad_dot(gg, TL::load(o + lay.o.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.o.st)));
     const float lse2 = lse[(size_t)bh * T + ic] * kLog2e;
     // the window's rows of the workgroup, [T0 + 64 - rows, T0 + 64), where they are staged
     const int rbeg = T0 + 64 - rows;
@@ -330,8 +330,8 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const float s = row_dot<D>(qq, kk[u]);
-            const float dP = row_dot<D>(gg, vv[u]);
+            const float s = TL::quad_dot(qq, kk[u]);
+            const float dP = TL::quad_dot(gg, vv[u]);
             const float p = d + u <= reach ? exp2f(s * sl2 - lse2) : 0.f;
             const float c = tau * p * (dP - delta);
             dsum += (double)p * (double)dP;
@@ -354,9 +354,9 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
         const int d0 = rt.d0[r], nx = min(r + 1, nact - 1);
         const float w = rt.w[r];
         const bool in = ic >= d0 + (w != 0.f), has1 = ic > d0;  // row -1 is the zero row
-        const float dP0 = row_dot<D>(gg, vx[0]), dPn = row_dot<D>(gg, vx[1]), dP1 = has1 ? dPn : 0.f;
+        const float dP0 = TL::quad_dot(gg, vx[0]), dPn = TL::quad_dot(gg, vx[1]), dP1 = has1 ? dPn : 0.f;
         load_rung(nx, V, sv, vx);
-        const float s0 = row_dot<D>(qq, kx[0]), sn = row_dot<D>(qq, kx[1]), s1 = has1 ? sn : 0.f;
+        const float s0 = TL::quad_dot(qq, kx[0]), sn = TL::quad_dot(qq, kx[1]), s1 = has1 ? sn : 0.f;
         const float s = (1.f - w) * s0 + w * s1;
         const float dP = (1.f - w) * dP0 + w * dP1;
         const float p = in ? exp2f(s * sl2 - lse2) : 0.f;
@@ -403,12 +403,12 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
 // What bounds it: as dq, the latency of the rung gathers and their VALU work; two (NC 4) or
 // four (NC 2) waves per SIMD, as the registers of two query and two dO rows in flight allow.
 // Us a launch: bf16 d 64 B4 H8 T2048 W64 26.3; bf16 d 128 B2 H16 on 4 T2000 W8 51.7; bf16
-// d 32 B8 H8 T1024 W10 17.8; fp32 d 64 B4 H8 T1024 W12 23.4.  With one lane group per key,
+// d 32 B8 H8 T1024 W10 17.8; fp32 d 64 B4 H8 T1024 W12 25.6.  With one lane group per key,
 // every query row read from global memory by every key it attends, and the R^T of dk and
 // the dalpha sum as launches of their own, the training step of each took 82, 66, 15 and
 // 38 us more.
 template <typename S, int D>
-constexpr int dkdv_waves = Tile<S, D>::NC <= 2 ? 4 : Tile<S, D>::NC == 4 ? 2 : 1;
+constexpr int dkdv_waves = Tile<S, D>::kF32 ? (D == 32 ? 3 : D == 64 ? 2 : 1) : Tile<S, D>::NC <= 2 ? 4 : 2;
 
 template <typename S, int D, bool INTERP, bool DEV>
 __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
@@ -436,6 +436,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
     const S *K = k + lay.k.head(bk, hd.kv_heads());
     const S *V = v + lay.v.head(bk, hd.kv_heads());
     constexpr int es = (int)sizeof(S);
+    constexpr float kLse = TL::kF32 ? 1.f : kLog2e;  // lse as prob takes it
     const uint32_t sq = (uint32_t)(lay.q.st * es), sg = (uint32_t)(lay.g.st * es);
     const uint32_t sk = (uint32_t)(lay.k.st * es), sv = (uint32_t)(lay.v.st * es);
     if (rf.on && threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
@@ -471,6 +472,12 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
     const int passes = hd.G / ts.hs;
 
     // ---- window band (MFMA layout) ----
+    // float32 with a window of one chunk: on the VALU, every product in the forward's order.
+    // The rounding of a logit is then the one that lse holds too, and cancels in the
+    // probability; logits from the matrix cores have errors of their own (dk, dv 5 to 25 %
+    // further from 64 bits than the VALU's at W <= 16, nearer at W >= 79; B4 H8 T1024 d 64
+    // W 12: 25.1 us with them, 25.6 here).
+    const bool valu = TL::kF32 && W <= 16;
     typename TL::Acc adk, adv;
     TL::zero(adk);
     TL::zero(adv);
@@ -495,26 +502,50 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                 }
                 for (int x = threadIdx.x; x < ts.hs * rows; x += blockDim.x) {
                     const size_t at = (size_t)hd.q_of(bk, pass * ts.hs + x / rows) * T + min(rbeg + x % rows, T - 1);
-                    sl[x] = lse[at] * kLog2e;
+                    sl[x] = lse[at] * kLse;
                     sd[x] = delta_in[at];
                 }
                 wait_vmem();
                 __syncthreads();
                 const char *qb = qr + hs * rows * TL::kRow, *gb = gr + hs * rows * TL::kRow;
+                if (valu) {  // one chunk: query j + d in staged row 16 wv + nq + d
+                    int row = jc;
+                    asm volatile("" : "+v"(row));  // read here, not held beside the other path's
+                    const Slice ka = TL::load(K, row, gq, sk), va = TL::load(V, row, gq, sv);
+                    for (int d = 0; d <= W; ++d) {
+                        const int r = 16 * wv + nq + d;
+                        const bool in = j + d < T;
+                        Slice x = TL::staged(qb, r, gq), y = TL::staged(gb, r, gq);
+                        const float s = TL::quad_dot(x, ka), dP = TL::quad_dot(y, va);
+                        const float pr = prob<TL::kF32>(s, sl2, sl[hs * rows + r]);
+                        const float c = in ? tau * pr * (dP - sd[hs * rows + r]) : 0.f;
+                        if (__builtin_amdgcn_ballot_w64(!in)) {  // clamped rows: 0 times them must be 0
+#pragma unroll
+                            for (int e = 0; e < TL::NC; ++e) {
+                                x.c[e] = in ? x.c[e] : u32x4{0u, 0u, 0u, 0u};
+                                y.c[e] = in ? y.c[e] : u32x4{0u, 0u, 0u, 0u};
+                            }
+                        }
+                        TL::axpy(adk, c, x);
+                        TL::axpy(adv, in ? pr : 0.f, y);
+                    }
+                    continue;
+                }
                 for (int c = 0; c < n; ++c) {
                     const int base = 16 * wv + 32 * c;  // the chunk's first staged row
                     float ds[8], p[8];
 #pragma unroll
                     for (int b = 0; b < 2; ++b) {
-                        const f32x4 s = TL::scores(TL::staged(qb, base + 16 * b + nm, gm), km);
-                        const f32x4 dp = TL::scores(TL::staged(gb, base + 16 * b + nm, gm), vm);
+                        constexpr int CH = TL::NC == 2 ? 4 : 8;
+                        const f32x4 s = TL::template scores<CH>(TL::staged(qb, base + 16 * b + nm, gm), km);
+                        const f32x4 dp = TL::template scores<CH>(TL::staged(gb, base + 16 * b + nm, gm), vm);
                         const int si = base + 16 * b + 4 * gm;
                         const f32x4 l2 = *reinterpret_cast<const f32x4 *>(sl + hs * rows + si);
                         const f32x4 de = *reinterpret_cast<const f32x4 *>(sd + hs * rows + si);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const bool in = jm < T && (unsigned)(rbeg + si + e - jm) <= reach;
-                            const float x = fast_exp2(fmaf(s[e], sl2, -l2[e]));
+                            const float x = prob<TL::kF32>(s[e], sl2, l2[e]);
                             p[4 * b + e] = in ? x : 0.f;
                             ds[4 * b + e] = in ? tau * x * (dp[e] - de[e]) : 0.f;
                         }
@@ -524,8 +555,10 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                 }
             }
     }
-    TL::to_quad_acc(adk, lane);
-    TL::to_quad_acc(adv, lane);
+    if (!valu) {
+        TL::to_quad_acc(adk, lane);
+        TL::to_quad_acc(adv, lane);
+    }
     if constexpr (TL::NC > 1) {
         // read again rather than held through the band phase
         int row = jc;
@@ -534,7 +567,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
         vj = TL::load(V, row, gq, sv);
     }
     // as in the forward: rows outside the window took part with weights of 0
-    if (__builtin_amdgcn_ballot_w64(!(TL::finite(adk) && TL::finite(adv)))) {
+    if (!valu && __builtin_amdgcn_ballot_w64(!(TL::finite(adk) && TL::finite(adv)))) {
         TL::zero(adk);
         TL::zero(adv);
         for (int pass = 0; pass < passes; ++pass) {
@@ -542,8 +575,8 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
             const S *Q = q + lay.q.head(bh, hd.H), *G = dO + lay.g.head(bh, hd.H);
             for (int i = t0; i < min(t0 + 16 + W, T); ++i) {
                 const Slice x = TL::load(Q, i, gq, sq), y = TL::load(G, i, gq, sg);
-                const float s = quad_sum(TL::dot(x, kj)), dP = quad_sum(TL::dot(y, vj));
-                const float p = fast_exp2(fmaf(s, sl2, -lse[(size_t)bh * T + i] * kLog2e));
+                const float s = TL::quad_dot(x, kj), dP = TL::quad_dot(y, vj);
+                const float p = prob<TL::kF32>(s, sl2, lse[(size_t)bh * T + i] * kLse);
                 if (i >= j && i - j <= W) {
                     TL::axpy(adk, tau * p * (dP - delta_in[(size_t)bh * T + i]), x);
                     TL::axpy(adv, p, y);
@@ -602,8 +635,8 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                     if (16 * h < nact) {
                         const int i = tp + 16 * u + rt.d0[min(nq + 16 * h, nact - 1)];
                         const int key = u ? min(tp + 16, T - 1) : max(tp - 1, 0), row = i < T ? i : key;
-                        es_[h][u] = quad_sum(TL::dot(TL::load(Q, row, gq, sq), TL::load(K, key, gq, sk)));
-                        ep_[h][u] = quad_sum(TL::dot(TL::load(G, row, gq, sg), TL::load(V, key, gq, sv)));
+                        es_[h][u] = TL::quad_dot(TL::load(Q, row, gq, sq), TL::load(K, key, gq, sk));
+                        ep_[h][u] = TL::quad_dot(TL::load(G, row, gq, sg), TL::load(V, key, gq, sv));
                     }
                 }
         }
@@ -616,8 +649,8 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
             float s[2], dP[2], c[2], p[2];
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
-                s[y] = quad_sum(TL::dot(xq[y], kj));
-                dP[y] = quad_sum(TL::dot(xg[y], vj));
+                s[y] = TL::quad_dot(xq[y], kj);
+                dP[y] = TL::quad_dot(xg[y], vj);
             }
             if constexpr (INTERP) {
                 // query i0 with key j - 1 is query i0 + 1 of the key four lanes before,
@@ -643,7 +676,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
                 const bool in = has(r, y);
-                const float x = fast_exp2(fmaf(s[y], sl2, -xl[y] * kLog2e));
+                const float x = prob<TL::kF32>(s[y], sl2, xl[y] * kLse);
                 const float wt = INTERP ? (y ? rt.w[r] : 1.f - rt.w[r]) : 1.f;
                 p[y] = in ? x * wt : 0.f;
                 c[y] = in ? tau * x * (dP[y] - xd[y]) * wt : 0.f;
@@ -759,7 +792,7 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
                   dtheta, T, W, rt, rtp, rf, tau, kLog2e / sqrtf((float)D), tk, hd, lay);
 }
 
-static hipError_t launch_backward_generic(int dtype, int D, const void *q, const void *k, const void *v,
+static hipError_t launch_backward_rows(int dtype, int D, const void *q, const void *k, const void *v,
                                           const void *o, const float *lse, const void *dO, void *dq,
                                           void *dk, void *dv, float *dalpha, float *dtheta, float *delta_ws,
                                           double *partials, int BH, const Heads &hd, int T, int W,
@@ -787,7 +820,7 @@ hipError_t launch_backward(int dtype, int D, const void *q, const void *k, const
     if (backward_mfma_supported(dtype, D, W))
         return launch_backward_mfma(q, k, v, o, lse, dO, dq, dk, dv, dalpha, dtheta, delta_ws, partials,
                                     terms, BH, hd, T, W, rt, rtp, rf, lay, s);
-    return launch_backward_generic(dtype, D, q, k, v, o, lse, dO, dq, dk, dv, dalpha, dtheta, delta_ws,
+    return launch_backward_rows(dtype, D, q, k, v, o, lse, dO, dq, dk, dv, dalpha, dtheta, delta_ws,
                                    partials, BH, hd, T, W, rt, rtp, rf, lay, s);
 }
 

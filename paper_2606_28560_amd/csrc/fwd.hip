@@ -318,7 +318,7 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
 #pragma unroll
         for (int y = 0; y < 4; ++y) x[y] = TL::load(K, d + y <= reach ? ic - d - y : ic, gq, sk);
 #pragma unroll
-        for (int y = 0; y < 4; ++y) keep(d + y, d + y <= reach, row_dot<D>(qq, x[y]));
+        for (int y = 0; y < 4; ++y) keep(d + y, d + y <= reach, TL::quad_dot(qq, x[y]));
     }
     // two rungs together (the second clamped to an active one and masked)
     for (int r = 0; r < nact; r += 2) {

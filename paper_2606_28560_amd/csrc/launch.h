@@ -52,7 +52,7 @@ hipError_t launch_forward(int dtype, int D, const void *q, const void *k, const 
 int tile_heads(int G, int nw);
 int tile_chunks(int nc, size_t fixed, size_t per, int slice_pieces);
 
-// Number of dalpha partials the dq kernel writes (one per workgroup).
+// dalpha partials the workspace holds: at least one per workgroup of the dq kernel.
 size_t bwd_num_partials(int dtype, int D, int BH, int T);
 
 // dtheta (nullable, device tables only): also writes dalpha * rtp->dadtheta there.

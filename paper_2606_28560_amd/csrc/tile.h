@@ -24,6 +24,29 @@
 
 namespace fibattn {
 
+// ---- float32 rows on the VALU, every sum in one fixed order (fwd.hip, bwd.hip) -------
+// The order is that of one lane per 16-byte chunk: a chain over the chunk's four products,
+// then pairs of chunks, the farthest first.  dalpha is a sum of terms that cancel, which
+// carries the rounding of lse and of the probabilities up by one to two decimal digits:
+// another order of the same sums moves it by more than a float32 result may move.
+__device__ __forceinline__ float chunk_dot(const u32x4 &x, const u32x4 &y) {
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = fmaf(__uint_as_float(x[e]), __uint_as_float(y[e]), s);
+    return s;
+}
+// Sum of a row's chunk values, this lane's at positions 4x + g; quad layout.
+template <int NC>
+__device__ __forceinline__ float chunk_sum(float *t) {
+#pragma unroll
+    for (int h = NC / 2; h >= 1; h >>= 1)
+#pragma unroll
+        for (int x = 0; x < h; ++x) t[x] += t[x + h];
+    float s = t[0];
+    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x4E, 0xF, 0xF, true));
+    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0xB1, 0xF, 0xF, true));
+    return s;
+}
 template <typename S, int D>
 struct Tile {
     static constexpr int kRow = D * (int)sizeof(S);  // bytes of a row
@@ -99,6 +122,18 @@ struct Tile {
                     t = __builtin_amdgcn_fdot2_f32_bf16(as_bf2(x.c[c][e]), as_bf2(y.c[c][e]), t, false);
             }
         return (s[0] + s[1]) + (s[2] + s[3]);
+    }
+
+    // The same over the four lanes of a quad; float32 rows in the fixed order above.
+    __device__ static __forceinline__ float quad_dot(const Slice &x, const Slice &y) {
+        if constexpr (kF32) {
+            float t[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) t[c] = chunk_dot(x.c[c], y.c[c]);
+            return chunk_sum<NC>(t);
+        } else {
+            return quad_sum(dot(x, y));
+        }
     }
 
     // acc += a x + b y with float32 weights.
@@ -379,36 +414,18 @@ struct Tile {
     }
 };
 
-// ---- float32 rows on the VALU, every sum in one fixed order (fwd.hip, bwd.hip) -------
-// The order is that of one lane per 16-byte chunk: a chain over the chunk's four products,
-// then pairs of chunks, the farthest first.  dalpha is a sum of terms that cancel, which
-// carries the rounding of lse and of the probabilities up by one to two decimal digits:
-// another order of the same sums moves it by more than a float32 result may move.
-__device__ __forceinline__ float chunk_dot(const u32x4 &x, const u32x4 &y) {
-    float s = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) s = fmaf(__uint_as_float(x[e]), __uint_as_float(y[e]), s);
-    return s;
-}
-// Sum of a row's chunk values, this lane's at positions 4x + g; quad layout.
-template <int NC>
-__device__ __forceinline__ float chunk_sum(float *t) {
-#pragma unroll
-    for (int h = NC / 2; h >= 1; h >>= 1)
-#pragma unroll
-        for (int x = 0; x < h; ++x) t[x] += t[x + h];
-    float s = t[0];
-    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x4E, 0xF, 0xF, true));
-    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0xB1, 0xF, 0xF, true));
-    return s;
-}
-template <int D>
-__device__ __forceinline__ float row_dot(const typename Tile<float, D>::Slice &x, const typename Tile<float, D>::Slice &y) {
-    constexpr int NC = Tile<float, D>::NC;
-    float t[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) t[c] = chunk_dot(x.c[c], y.c[c]);
-    return chunk_sum<NC>(t);
+// Probability exp(tau s - lse) of a backward entry as exp2(s sl2 - lse log2e), with the
+// forward's sl2 = fl(tau log2e), whose rounding the saved lse shares.  l: lse for float32
+// rows, lse log2e for bfloat16.  float32: what the rounding of lse log2e loses (up to 1.7e-7
+// of every probability of a query alike, at lse = 4) is multiplied back in.
+template <bool F32>
+__device__ __forceinline__ float prob(float s, float sl2, float l) {
+    if constexpr (!F32) return fast_exp2(fmaf(s, sl2, -l));
+    const float v = l * kLog2e;
+    // kLog2e + 1.925963e-8 = log2(e)
+    const float low = fmaf(l, 1.925963033500e-8f, fmaf(l, kLog2e, -v)) * kLn2;
+    const float p = fast_exp2(fmaf(s, sl2, -v));
+    return fmaf(p, -low, p);
 }
 
 // Weight and lane bookkeeping of a launch: `nw` waves per workgroup are `hs` query heads
