@@ -113,10 +113,7 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
     // ---- window band (MFMA layout) ----
     typename TL::Acc acc;
     TL::zero(acc);
-    // the entries' sums of p dP and of p (this lane's parts).  The latter is 1 up to the
-    // rounding of lse and its conversion to base 2, which scales every p of a query alike:
-    // the results are divided by it.
-    double dsum = 0.0, psum = 0.0;
+    double dsum = 0.0;  // the entries' sum of p dP (this lane's part)
     {
         const Slice qm = TL::from_quad(qq, lane), gmm = TL::from_quad(gg, lane);
         const float lse2_m = __shfl(lse2, 4 * nm, 64), delta_m = __shfl(delta, 4 * nm, 64);
@@ -133,7 +130,7 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
             __syncthreads();
             for (int c = 0; c < n; ++c) {
                 const int base = 16 * wv + 32 * (n - 1 - c);
-                float ds[8], pd = 0.f, ps = 0.f;
+                float ds[8], pd = 0.f;
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
                     const f32x4 s = TL::scores(TL::staged(kr, base + 16 * b + nm, gm), qm);
@@ -145,11 +142,9 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
                         const float p = in ? fast_exp2(fmaf(s[e], sl2, -lse2_m)) : 0.f, dP = in ? dp[e] : 0.f;
                         ds[4 * b + e] = tau * p * (dP - delta_m);
                         pd = fmaf(p, dP, pd);
-                        ps += p;
                     }
                 }
                 dsum += (double)pd;
-                psum += (double)ps;
                 TL::accumulate(acc, kr, base, TL::weights(ds), gm);
             }
         }
@@ -175,14 +170,10 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
             if (key <= i && i - key <= W) TL::axpy(acc, tau * fast_exp2(fmaf(s, sl2, -lse2)) * (dP - delta), kk);
         }
     }
-    // the query's band sums, on each of its four quad lanes
-    auto band_sum = [&](double x) {
-        x += __shfl_xor(x, 16, 64);
-        x += __shfl_xor(x, 32, 64);
-        return __shfl(x, nq, 64);
-    };
-    dsum = band_sum(dsum);
-    psum = band_sum(psum);
+    // the query's band sum, on each of its four quad lanes
+    dsum += __shfl_xor(dsum, 16, 64);
+    dsum += __shfl_xor(dsum, 32, 64);
+    dsum = __shfl(dsum, nq, 64);
 
     // ---- rungs (quad layout); row r1 = -1 is the zero row ----
     // xa, xb, y: this lane's parts of the sums over <q, k[r1]-k[r0]> and <dO, v[r1]-v[r0]>
@@ -213,7 +204,6 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
         xb = fma((double)fp, (double)dv, xb);
         y = fma((double)fp, ds, y);
         dsum += (double)(p * dP);
-        psum += (double)p;
     };
     if constexpr (NBUF == 2) {
         for (int r = 0; r < nact; r += 2) {
@@ -243,14 +233,13 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
         }
     }
 
-    const double inv = i < T ? 1.0 / psum : 0.0;
     if (rf.on) TL::rope_t(acc, i, sfreq, gq);  // gradient w.r.t. the unrotated q
     if (i < T) {
-        TL::store(dq + lay.dq.head(bh, hd.H) + i * lay.dq.st, gq, acc, bad ? NAN : (float)inv);
+        TL::store(dq + lay.dq.head(bh, hd.H) + i * lay.dq.st, gq, acc, bad ? NAN : 1.f);
         if (gq == 0) delta_out[(size_t)bh * T + i] = bad ? NAN : delta;
     }
     // this lane's part of the query's dalpha; wave sums, then the waves in order
-    double dal = inv * ((double)tau * (xa - inv * dsum * y) + xb);
+    double dal = i < T ? (double)tau * (xa - dsum * y) + xb : 0.0;
     if (bad) dal = NAN;
 #pragma unroll
     for (int st = 32; st >= 1; st >>= 1) dal += __shfl_xor(dal, st, 64);

@@ -417,13 +417,15 @@ struct Tile {
 // Probability exp(tau s - lse) of a backward entry as exp2(s sl2 - lse log2e), with the
 // forward's sl2 = fl(tau log2e), whose rounding the saved lse shares.  l: lse for float32
 // rows, lse log2e for bfloat16.  float32: what the rounding of lse log2e loses (up to 1.7e-7
-// of every probability of a query alike, at lse = 4) is multiplied back in.
+// of every probability of a query alike, at lse = 4) is multiplied back in; an infinite
+// lse (a query dropped by its caller) loses nothing.
 template <bool F32>
 __device__ __forceinline__ float prob(float s, float sl2, float l) {
     if constexpr (!F32) return fast_exp2(fmaf(s, sl2, -l));
     const float v = l * kLog2e;
     // kLog2e + 1.925963e-8 = log2(e)
-    const float low = fmaf(l, 1.925963033500e-8f, fmaf(l, kLog2e, -v)) * kLn2;
+    float low = fmaf(l, 1.925963033500e-8f, fmaf(l, kLog2e, -v)) * kLn2;
+    low = __builtin_isfinite(v) ? low : 0.f;
     const float p = fast_exp2(fmaf(s, sl2, -v));
     return fmaf(p, -low, p);
 }

@@ -1,0 +1,167 @@
+"""The kernels outside the bfloat16, d_head 64, W <= 16 path at the edges of what their
+arguments may hold: an lse that is not the forward's own, infinities, probabilities below the
+normal range, sums that cancel, angles near a half turn.  The reference (rows below) takes the
+entries of every query one by one in float64; an entry that a query does not have is not read."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_28560_amd import fibattn as F
+from paper_2606_28560_amd import inputs, schedules
+
+pytestmark = pytest.mark.gpu
+
+FIB, POW2 = schedules.FIB15, schedules.POW2_11
+DT = {"bf16": torch.bfloat16, "fp32": torch.float32}
+INF = float("inf")
+
+
+def make(B, H, Hkv, T, D, dtype, seed):
+    x = inputs.attention_inputs(B, H, T, D, dtype, seed, 0, names=("q", "dO"))
+    x.update(inputs.attention_inputs(B, Hkv, T, D, dtype, seed, 0, names=("k", "v")))
+    return x
+
+
+def entries(W, base, alpha, T):
+    """(distance of row r0, weight of row r1, base value; 0 in the window), as the table has them."""
+    return [(d, 0.0, 0) for d in range(min(W, T - 1) + 1)] + [
+        (d, float(w), f) for d, w, f in F.fibattn_rung_table(alpha, base, W) if d < T]
+
+
+def rows(x, W, base, alpha, o=None, lse=None):
+    """Forward and (with x["dO"]) backward in float64, on the given o and lse where passed."""
+    q, k, v = (x[n].double() for n in ("q", "k", "v"))
+    B, H, T, D = q.shape
+    G, tau = H // k.shape[1], 1.0 / math.sqrt(D)
+    k, v = k.repeat_interleave(G, 1), v.repeat_interleave(G, 1)
+    pos = torch.arange(T)
+    ent = entries(W, base, alpha, T)
+
+    def shifted(t, d):  # row i of the result is row i - d; zero rows before the start
+        return torch.cat([torch.zeros_like(t[:, :, :min(d, T)]), t[:, :, :T - min(d, T)]], 2)
+
+    def blend(t, d, w):
+        return shifted(t, d) if w == 0 else (1 - w) * shifted(t, d) + w * shifted(t, d + 1)
+
+    s = torch.full((len(ent), B, H, T), -INF, dtype=torch.float64)
+    for n, (d, w, _) in enumerate(ent):
+        dot = (q * shifted(k, d)).sum(-1)
+        if w:
+            dot = (1 - w) * dot + w * (q * shifted(k, d + 1)).sum(-1)
+        s[n] = torch.where(pos >= d + (w > 0), dot * tau, s[n])
+    has = [(pos >= d + (w > 0)) for d, w, _ in ent]
+    m = torch.where(s.isnan(), -INF, s).max(0).values
+    e = torch.exp(s - m)
+    e = torch.stack([torch.where(h, a, 0.0) for h, a in zip(has, e)])
+    l = e.sum(0)
+    out = {"lse": m + torch.log(l)}
+    acc = torch.zeros_like(q)
+    for n, (d, w, _) in enumerate(ent):
+        t = e[n][..., None] * blend(v, d, w)
+        acc = acc + torch.where(has[n][:, None], t, 0.0)
+    out["o"] = acc / l[..., None]
+    if "dO" not in x:
+        return out
+    dO = x["dO"].double()
+    o, lse = (out["o"] if o is None else o.double()), (out["lse"] if lse is None else lse.double())
+    delta = (dO * o).sum(-1)
+    dq, dk, dv = torch.zeros_like(q), torch.zeros_like(q), torch.zeros_like(q)
+    xa, xb, y, dsum = (torch.zeros_like(lse) for _ in range(4))
+    l1 = torch.zeros_like(lse)
+
+    def back(t, d, keep):  # row i goes to row i - d
+        t = torch.where(keep[:, None], t, 0.0)
+        return torch.cat([t[:, :, d:], torch.zeros_like(t[:, :, :min(d, T)])], 2)
+
+    for n, (d, w, f) in enumerate(ent):
+        h = has[n]
+        p = torch.exp(s[n] - lse)
+        dP = (dO * shifted(v, d)).sum(-1)
+        if w:
+            dP = (1 - w) * dP + w * (dO * shifted(v, d + 1)).sum(-1)
+        c = tau * p * (dP - delta)
+        dq = dq + torch.where(h[:, None], c[..., None] * blend(k, d, w), 0.0)
+        dsum = dsum + torch.where(h, p * dP, 0.0)
+        gk, gv = c[..., None] * q, p[..., None] * dO
+        dk, dv = dk + back((1 - w) * gk if w else gk, d, h), dv + back((1 - w) * gv if w else gv, d, h)
+        if w:
+            dk, dv = dk + back(w * gk, d + 1, h), dv + back(w * gv, d + 1, h)
+        if f:
+            ds = (q * (shifted(k, d + 1) - shifted(k, d))).sum(-1)
+            db = (dO * (shifted(v, d + 1) - shifted(v, d))).sum(-1)
+            xa, xb = xa + torch.where(h, f * p * dP * ds, 0.0), xb + torch.where(h, f * p * db, 0.0)
+            y = y + torch.where(h, f * p * ds, 0.0)
+            l1 = l1 + torch.where(h, (f * (c * ds + p * db)).abs(), 0.0)
+    out["dalpha"] = float((tau * (xa - dsum * y) + xb).sum().detach())
+    out["l1"] = float(l1.sum().detach())
+    out["dq"] = dq
+    out["dk"], out["dv"] = (t.view(B, H // G, G, T, D).sum(2) for t in (dk, dv))
+    return out
+
+
+def run(x, W, base, alpha, o=None, lse=None, rope_base=0.0):
+    """o, lse, dq, dk, dv, dalpha of the library on CPU inputs, on the CPU."""
+    g = {n: t.cuda() for n, t in x.items()}
+    fo, fl = F.fibattn_forward(g["q"], g["k"], g["v"], W, base, alpha)
+    res = {"o": fo, "lse": fl}
+    if "dO" in g:
+        o, lse = (fo if o is None else o.cuda()), (fl if lse is None else lse.cuda())
+        res["dq"], res["dk"], res["dv"], da = F.fibattn_backward(
+            g["q"], g["k"], g["v"], o, lse, g["dO"], W, base, alpha, rope_base=rope_base)
+        res["dalpha"] = da
+    torch.cuda.synchronize()
+    res = {n: t.cpu() for n, t in res.items()}
+    if "dalpha" in res:
+        res["dalpha"] = float(res["dalpha"])
+    return res
+
+
+def close(got, want, dtype, names=("o", "lse", "dq", "dk", "dv")):
+    """Finite elements near the reference's (1e-5, bfloat16 2e-2, of the largest; lse 1e-5 and
+    1e-3), the others NaN, inf or -inf as the reference's are."""
+    for n in names:
+        if n not in got:
+            continue
+        a, b = got[n].double(), want[n]
+        for what, f in (("nan", torch.isnan), ("inf", torch.isposinf), ("-inf", torch.isneginf)):
+            bad = f(a) != f(b)
+            assert not bad.any(), (n, what, bad.nonzero()[:4].tolist(), a[bad][:4].tolist(), b[bad][:4].tolist())
+        fin = torch.isfinite(b)
+        if fin.any():
+            tol = 1e-5 if dtype == "fp32" else 1e-3 if n == "lse" else 2e-2
+            err = (a - b)[fin].abs().max()
+            assert err <= tol * max(1.0, float(b[fin].abs().max())), (n, float(err))
+
+
+SHAPES = [
+    # (H, H_kv, T, D, dtype, W, base, alpha): every head size and storage type, windows of one
+    # chunk and of several, integer and interpolated offsets, grouped heads, the kernel of
+    # small float32 launches (few rows) and the one of large ones
+    (2, 2, 150, 64, "bf16", 20, FIB, 0.9),
+    (4, 1, 150, 64, "bf16", 40, FIB, 1.0),
+    (2, 2, 130, 128, "bf16", 8, FIB, 1.0),
+    (2, 1, 130, 128, "bf16", 17, POW2, 0.9),
+    (2, 2, 130, 32, "bf16", 10, POW2, 1.3),
+    (2, 2, 130, 32, "bf16", 3, FIB, 1.0),
+    (2, 1, 130, 64, "fp32", 9, FIB, 0.9),
+    (1, 1, 130, 128, "fp32", 40, FIB, 1.0),
+    (64, 64, 130, 32, "fp32", 8, FIB, 1.2),
+    (64, 64, 130, 64, "fp32", 40, FIB, 1.0),
+]
+
+
+@pytest.mark.parametrize("H,Hkv,T,D,dtype,W,base,alpha", SHAPES)
+def test_backward_on_another_lse(H, Hkv, T, D, dtype, W, base, alpha):
+    # an lse over more keys than these (0.75 to 1.5 larger), and +inf, which drops a query:
+    # dq, dk, dv and dalpha are those of p = exp(s - lse)
+    x = make(1, H, Hkv, T, D, dtype, 900)
+    lse = rows({n: x[n] for n in ("q", "k", "v")}, W, base, alpha)["lse"]
+    o = rows({n: x[n] for n in ("q", "k", "v")}, W, base, alpha)["o"].to(DT[dtype])
+    lse = (lse + 0.75 + 0.75 * (torch.arange(T) % 2)).float()
+    lse[:, :, 5::17] = INF
+    got, want = run(x, W, base, alpha, o, lse), rows(x, W, base, alpha, o, lse)
+    close(got, want, dtype, ("dq", "dk", "dv"))
+    assert (got["dq"][:, :, 5::17] == 0).all()
+    assert abs(got["dalpha"] - want["dalpha"]) <= (1e-5 if dtype == "fp32" else 1e-3) * max(1.0, want["l1"])
