@@ -16,8 +16,8 @@
 //
 // Precision: float32 rows are multiplied in float32.  bfloat16 rows are multiplied
 // exactly (bf16 products in float32 accumulators); the float32 weights they are scaled by
-// (probabilities, tau dS) are split into two bfloat16 parts, high and low (17 bits of the
-// weight), each with its own product, so no weight is rounded to 16 bits.
+// (probabilities, tau dS) keep their 24 bits: on the VALU they multiply the unpacked rows,
+// on the matrix cores they are three bfloat16 parts of 8 bits, each with its own product.
 #pragma once
 
 #include "mfma.h"
@@ -146,21 +146,14 @@ struct Tile {
                     acc.c[c][e] = fmaf(a, __uint_as_float(x.c[c][e]),
                                        fmaf(b, __uint_as_float(y.c[c][e]), acc.c[c][e]));
         } else {
-            const uint32_t h = pack_bf16(a, b);
-            const uint32_t l = pack_bf16(a - bf16_lo(h), b - bf16_hi(h));
 #pragma unroll
             for (int c = 0; c < NC; ++c)
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
-                    // pairs (x_d, y_d) of the word's two dims
-                    const uint32_t lo = __builtin_amdgcn_perm(y.c[c][w], x.c[c][w], 0x05040100u);
-                    const uint32_t hi = __builtin_amdgcn_perm(y.c[c][w], x.c[c][w], 0x07060302u);
                     f32x4 &d = acc.c[2 * c + (w >> 1)];
                     const int e = 2 * (w & 1);
-                    d[e] = __builtin_amdgcn_fdot2_f32_bf16(as_bf2(lo), as_bf2(l), d[e], false);
-                    d[e + 1] = __builtin_amdgcn_fdot2_f32_bf16(as_bf2(hi), as_bf2(l), d[e + 1], false);
-                    d[e] = __builtin_amdgcn_fdot2_f32_bf16(as_bf2(lo), as_bf2(h), d[e], false);
-                    d[e + 1] = __builtin_amdgcn_fdot2_f32_bf16(as_bf2(hi), as_bf2(h), d[e + 1], false);
+                    d[e] = fmaf(a, bf16_lo(x.c[c][w]), fmaf(b, bf16_lo(y.c[c][w]), d[e]));
+                    d[e + 1] = fmaf(a, bf16_hi(x.c[c][w]), fmaf(b, bf16_hi(y.c[c][w]), d[e + 1]));
                 }
         }
     }
@@ -271,8 +264,8 @@ struct Tile {
     // Weights of a 32-row chunk (two 16-row blocks of C-layout weights, p[4b + e] for row
     // 16b + 4g + e and the lane's column), as matrix operands.
     struct Weights {
-        u32x4 h, l;   // bfloat16: high and low parts
-        float f[8];   // float32
+        u32x4 h, m, l;  // bfloat16: the leading 8 bits, the next and the last
+        float f[8];     // float32
     };
     __device__ static __forceinline__ Weights weights(const float *p) {
         Weights w;
@@ -283,7 +276,9 @@ struct Tile {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 w.h[e] = pack_bf16(p[2 * e], p[2 * e + 1]);
-                w.l[e] = pack_bf16(p[2 * e] - bf16_lo(w.h[e]), p[2 * e + 1] - bf16_hi(w.h[e]));
+                const float a = p[2 * e] - bf16_lo(w.h[e]), b = p[2 * e + 1] - bf16_hi(w.h[e]);
+                w.m[e] = pack_bf16(a, b);
+                w.l[e] = pack_bf16(a - bf16_lo(w.m[e]), b - bf16_hi(w.m[e]));
             }
         }
         return w;
@@ -317,6 +312,7 @@ struct Tile {
                 }
                 const bf16x8 A = __builtin_bit_cast(bf16x8, t);
                 acc.c[b] = mfma(A, __builtin_bit_cast(bf16x8, w.l), acc.c[b]);
+                acc.c[b] = mfma(A, __builtin_bit_cast(bf16x8, w.m), acc.c[b]);
                 acc.c[b] = mfma(A, __builtin_bit_cast(bf16x8, w.h), acc.c[b]);
             }
         }

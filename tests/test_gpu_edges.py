@@ -165,3 +165,40 @@ def test_backward_on_another_lse(H, Hkv, T, D, dtype, W, base, alpha):
     close(got, want, dtype, ("dq", "dk", "dv"))
     assert (got["dq"][:, :, 5::17] == 0).all()
     assert abs(got["dalpha"] - want["dalpha"]) <= (1e-5 if dtype == "fp32" else 1e-3) * max(1.0, want["l1"])
+
+
+@pytest.mark.parametrize("what", ["o", "dq", "dk", "dv"])
+@pytest.mark.parametrize("D,W,alpha", [(64, 40, 1.0), (64, 20, 0.9), (128, 8, 1.0), (128, 8, 0.9), (32, 12, 0.9), (32, 5, 1.0)])
+def test_weights_of_24_bits(D, W, alpha, what):
+    # bfloat16 rows times float32 weights, two of the rows chosen so that the sum cancels to
+    # 2^-12 or less of its terms: what is left shows the error of the weights.  Rounded to 24
+    # bits they have 6e-8, and 1e-7 to 2e-7 from the logits and from lse log2 e; two bfloat16
+    # parts have up to 7.6e-6.  Bound: 4e-7 of the terms' sum.
+    H, T = 16, 160
+    x = {n: t.double() for n, t in make(1, H, H, T, D, "bf16", 940).items()}
+    if what in ("dq", "dk"):  # logits of 0: tau dS does not move with the rows that are chosen
+        x["k" if what == "dk" else "q"].zero_()
+    fwd = rows({n: x[n] for n in ("q", "k", "v")}, W, FIB, alpha)
+    o, lse = fwd["o"].bfloat16(), fwd["lse"].float()
+    var, at = {"o": "v", "dq": "k", "dk": "q", "dv": "dO"}[what], T - 1 if what in ("o", "dq") else 4
+    if what == "o":
+        del x["dO"]
+    # the weight of every row, as the derivative
+    x[var].requires_grad_()
+    rows(x, W, FIB, alpha, o, lse)[what][0, :, at, 0].sum().backward()
+    w = x[var].grad[0, :, :, 0]
+    x[var] = x[var].detach()
+    for h in range(H):
+        a, b = (int(n) for n in w[h].abs().argsort(descending=True)[:2])
+        y = x[var][0, h]
+        y[b] = 0.0
+        for n in (a, b):
+            y[n] = 0.0
+            y[n] = (-(w[h, :, None] * y).sum(0) / w[h, n]).bfloat16().double()
+    mass = (w[:, :, None] * x[var][0]).abs().sum(1)
+    g = {n: t.bfloat16() for n, t in x.items()}
+    want, got = rows(g, W, FIB, alpha, o, lse)[what][0, :, at], run(g, W, FIB, alpha, o, lse)[what][0, :, at].double()
+    assert (want.abs() <= 2.0 ** -12 * mass).all()
+    err = ((got - want).abs() - 2.0 ** -8 * want.abs()).clamp_min(0.0) / mass
+    print(f"{what} D{D} W{W} alpha {alpha}: error over the terms' sum {float(err.max()):.1e}", flush=True)
+    assert err.max() <= 4e-7
