@@ -36,6 +36,39 @@ constexpr float kFwdSlack = 8.f;  // log2 units a rung's logit may exceed the ru
 template <typename S, int D>
 constexpr int fwd_waves = Tile<S, D>::NC <= 2 ? 4 : Tile<S, D>::NC == 4 ? 3 : 2;
 
+// The softmax and the weighted values of query ic, its entries one by one and only those it
+// has, the maximum first (quad layout; nact rungs, the wave's).
+template <typename TL>
+__device__ __forceinline__ void forward_by_entry(const typename TL::Slice &qq, const void *K, const void *V, uint32_t sk,
+                                                 uint32_t sv, int ic, int gq, int W, const RungTable &rt, int nact,
+                                                 float sl2, typename TL::Acc &acc, float &m, float &l) {
+    float mx = -INFINITY;
+    for (int pass = 0; pass < 2; ++pass) {
+        if (pass) {
+            TL::zero(acc);
+            l = 0.f;
+            m = mx;
+        }
+        for (int e = 0; e <= W + nact; ++e) {
+            const int d = e <= W ? e : rt.d0[e - W - 1];
+            const float w = e <= W ? 0.f : rt.w[e - W - 1];
+            const bool in = ic >= d + (w != 0.f);
+            const int r0 = in ? ic - d : ic, r1 = in ? r0 - 1 : ic;
+            float s = quad_sum(TL::dot(qq, TL::load(K, r0, gq, sk)));
+            if (w != 0.f) s = (1.f - w) * s + w * quad_sum(TL::dot(qq, TL::load(K, r1, gq, sk)));
+            s *= sl2;
+            if (!pass) {
+                mx = in ? fmaxf(mx, s) : mx;
+            } else if (in) {
+                const float p = exp2f(s - mx);
+                l += p;
+                TL::axpy(acc, p * (1.f - w), TL::load(V, r0, gq, sv));
+                if (w != 0.f) TL::axpy(acc, p * w, TL::load(V, r1, gq, sv));
+            }
+        }
+    }
+}
+
 // INTERP: some rung has w != 0, so the second row r1 is read; otherwise two rungs are
 // taken together.  DEV: the rung table is the one at rtp, built on the device (rt_arg
 // unused).  rf.on: q holds unrotated rows; each is rotated where it is loaded (a query row
@@ -147,7 +180,7 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
             }
             mx = max4(mx) * sl2;
             if (c0 + c == 0) {
-                m = mx;  // finite: the first chunk holds key im itself
+                m = mx;  // -inf only where key im itself has a logit of -inf
             } else if (__builtin_amdgcn_ballot_w64(mx > m)) {
                 const float mn = fmaxf(m, mx), f = fast_exp2(m - mn);
                 m = mn;
@@ -169,16 +202,6 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     TL::to_quad_acc(acc, lane);
     m = to_quad(m, lane);
     l = to_quad(l, lane);
-    // Rows of the chunks outside a query's window were multiplied by weights of 0.  If that
-    // (or a value the query does attend) left anything that is not finite, the window's
-    // values are added again row by row, attended ones only.
-    if (__builtin_amdgcn_ballot_w64(!TL::finite(acc))) {
-        TL::zero(acc);
-        for (int key = max(t0 - W, 0); key < min(t0 + 16, T); ++key) {
-            const float s = quad_sum(TL::dot(qq, TL::load(K, key, gq, sk)));
-            if (key <= i && i - key <= W) TL::axpy(acc, fast_exp2(fmaf(s, sl2, -m)), TL::load(V, key, gq, sv));
-        }
-    }
 
     // ---- rungs (quad layout) ----
     float p[RB];
@@ -252,6 +275,11 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
             load_batch(nx, V, sv, vx[0]);
         }
     }
+    // Entries a query does not have took part with weights of 0: rows of the chunks outside
+    // its window, and its own row in the place of a rung's.  If that, or what the query does
+    // attend, left anything that is not finite, the entries are taken one by one instead.
+    if (__builtin_amdgcn_ballot_w64(!(TL::finite(acc) && l * 0.f == 0.f)))
+        forward_by_entry<TL>(qq, K, V, sk, sv, ic, gq, W, rt, nact, sl2, acc, m, l);
 
     if (i < T) {
         const bool bad = DEV && table_unusable(rt, W);  // bad device alpha, or another W
@@ -370,6 +398,19 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
         l += p;
         TL::axpy(acc, p * (1.f - w), x);
         if (w != 0.f) TL::axpy(acc, p * w, TL::load(V, in ? r0 - 1 : r0, gq, sv));
+    }
+    if (__builtin_amdgcn_ballot_w64(!TL::finite(acc))) {  // as in the tile kernel: 0 times its own row
+        TL::zero(acc);
+        for (int d = 0; d < nwin; ++d)
+            if (d <= reach) TL::axpy(acc, exp2f(sc[64 * d] - m), TL::load(V, ic - d, gq, sv));
+        for (int r = 0; r < nact; ++r) {
+            const int d0 = rt.d0[r];
+            const float w = rt.w[r], p = exp2f(sc[64 * (nwin + r)] - m);
+            if (ic >= d0 + (w != 0.f)) {
+                TL::axpy(acc, p * (1.f - w), TL::load(V, ic - d0, gq, sv));
+                if (w != 0.f) TL::axpy(acc, p * w, TL::load(V, ic - d0 - 1, gq, sv));
+            }
+        }
     }
     if (i < T) {
         const bool bad = DEV && table_unusable(rt, W);  // bad device alpha, or another W

@@ -167,6 +167,33 @@ def test_backward_on_another_lse(H, Hkv, T, D, dtype, W, base, alpha):
     assert abs(got["dalpha"] - want["dalpha"]) <= (1e-5 if dtype == "fp32" else 1e-3) * max(1.0, want["l1"])
 
 
+@pytest.mark.parametrize("H,Hkv,T,D,dtype,W,base,alpha", SHAPES)
+def test_infinite_values(H, Hkv, T, D, dtype, W, base, alpha):
+    # some elements of two value rows are +inf and -inf: they reach exactly the outputs of the
+    # queries that attend those rows, with their sign
+    x = make(1, H, Hkv, T, D, dtype, 910)
+    j = T // 2
+    x["v"][:, :, j, ::3] = INF
+    x["v"][:, :, j, 1::3] = -INF
+    x["v"][:, :, T // 3, 5] = -INF
+    del x["dO"]
+    close(run(x, W, base, alpha), rows(x, W, base, alpha), dtype)
+
+
+@pytest.mark.parametrize("H,Hkv,T,D,dtype,W,base,alpha", SHAPES + [
+    (2, 2, 130, 128, "bf16", 0, FIB, 0.9), (2, 2, 130, 32, "bf16", 0, FIB, 1.0), (2, 2, 130, 64, "fp32", 0, FIB, 1.0)])
+def test_logits_of_minus_infinity(H, Hkv, T, D, dtype, W, base, alpha):
+    # keys of -inf under queries that are positive have no weight: alone in the window, the whole
+    # window, or a rung's row; with no key left the query is NaN
+    x = make(1, H, Hkv, T, D, dtype, 920)
+    x["q"] = x["q"].abs() + 0.125
+    j = T // 2
+    x["k"][:, :, j] = -INF
+    x["k"][:, :, j + 10: j + 12 + W] = -INF
+    del x["dO"]
+    close(run(x, W, base, alpha), rows(x, W, base, alpha), dtype)
+
+
 @pytest.mark.parametrize("what", ["o", "dq", "dk", "dv"])
 @pytest.mark.parametrize("D,W,alpha", [(64, 40, 1.0), (64, 20, 0.9), (128, 8, 1.0), (128, 8, 0.9), (32, 12, 0.9), (32, 5, 1.0)])
 def test_weights_of_24_bits(D, W, alpha, what):
