@@ -45,6 +45,43 @@ namespace fibattn {
 // every query (us a launch, interpolating): bf16 d 64 B4 H8 T2048 W64 135 -> 22.9; bf16
 // d 128 B2 H16 on 4 T2000 W8 82 -> 37; bf16 d 32 B8 H8 T1024 W10 23.6 -> 15.4 (the R^T of
 // dq, then a launch of its own, not included in the first figure).
+// dq and the dalpha parts of query ic, its entries one by one and only those it has, in the
+// order of the float32 kernel (quad layout; nact rungs, the wave's).  The parts are the whole
+// quad's, on its lane 0.
+template <typename TL>
+__device__ __forceinline__ void dq_by_entry(const typename TL::Slice &qq, const typename TL::Slice &gg, const void *K,
+                                            const void *V, uint32_t sk, uint32_t sv, int ic, int gq, int W,
+                                            const RungTable &rt, int nact, float tau, float sl2, float lse2, float delta,
+                                            typename TL::Acc &acc, double &xa, double &xb, double &y, double &dsum) {
+    TL::zero(acc);
+    xa = xb = y = dsum = 0.0;
+    for (int e = 0; e <= W + nact; ++e) {
+        const int r = e - W - 1, d = r < 0 ? e : rt.d0[r];
+        const float w = r < 0 ? 0.f : rt.w[r];
+        const bool in = ic >= d + (w != 0.f), has1 = r >= 0 && ic > d;  // row -1 is the zero row
+        const int r0 = in ? ic - d : ic, r1 = has1 ? ic - d - 1 : ic;
+        const typename TL::Slice k0 = TL::load(K, r0, gq, sk), k1 = TL::load(K, r1, gq, sk);
+        const float s0 = TL::quad_dot(qq, k0), sn = TL::quad_dot(qq, k1), s1 = has1 ? sn : 0.f;
+        const float dP0 = TL::quad_dot(gg, TL::load(V, r0, gq, sv));
+        const float dPn = TL::quad_dot(gg, TL::load(V, r1, gq, sv)), dP1 = has1 ? dPn : 0.f;
+        const float s = w != 0.f ? (1.f - w) * s0 + w * s1 : s0;
+        const float dP = w != 0.f ? (1.f - w) * dP0 + w * dP1 : dP0;
+        const float p = exp2f(s * sl2 - lse2);
+        const float c = r < 0 ? tau * p * (dP - delta) : tau * (p * (dP - delta));
+        if (!in) continue;
+        if (w != 0.f)
+            TL::axpy2(acc, c * (1.f - w), k0, c * w, k1);
+        else
+            TL::axpy(acc, c, k0);
+        dsum += (double)p * (double)dP;
+        if (r < 0 || gq) continue;
+        const double fp = (double)rt.f[r] * (double)p;
+        xa += fp * (double)dP * (double)(s1 - s0);
+        xb += fp * (double)(dP1 - dP0);
+        y += fp * (double)(s1 - s0);
+    }
+}
+
 template <typename S, int D>
 constexpr int dq_waves = Tile<S, D>::NC <= 2 ? 4 : Tile<S, D>::NC == 4 ? 3 : 2;
 
@@ -161,15 +198,6 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
         if (TL::NC > 1) load_rung(0, K, sk, kx[0]);
     }
     TL::to_quad_acc(acc, lane);
-    // as in the forward: rows outside the window took part with weights of 0
-    if (__builtin_amdgcn_ballot_w64(!TL::finite(acc))) {
-        TL::zero(acc);
-        for (int key = max(t0 - W, 0); key < min(t0 + 16, T); ++key) {
-            const Slice kk = TL::load(K, key, gq, sk);
-            const float s = quad_sum(TL::dot(qq, kk)), dP = quad_sum(TL::dot(gg, TL::load(V, key, gq, sv)));
-            if (key <= i && i - key <= W) TL::axpy(acc, tau * fast_exp2(fmaf(s, sl2, -lse2)) * (dP - delta), kk);
-        }
-    }
     // the query's band sum, on each of its four quad lanes
     dsum += __shfl_xor(dsum, 16, 64);
     dsum += __shfl_xor(dsum, 32, 64);
@@ -232,6 +260,9 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
             load_rung(nx, K, sk, kx[0]);
         }
     }
+    // as in the forward: entries the query does not have took part with weights of 0
+    if (__builtin_amdgcn_ballot_w64(!(TL::finite(acc) && (xa + xb + y + dsum) * 0.0 == 0.0)))
+        dq_by_entry<TL>(qq, gg, K, V, sk, sv, ic, gq, W, rt, nact, tau, sl2, lse2, delta, acc, xa, xb, y, dsum);
 
     if (rf.on) TL::rope_t(acc, i, sfreq, gq);  // gradient w.r.t. the unrotated q
     if (i < T) {
@@ -359,6 +390,8 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
         y += fp * (double)(s1 - s0);
         dsum += (double)p * (double)dP;
     }
+    if (__builtin_amdgcn_ballot_w64(!(TL::finite(acc) && (xa + xb + y + dsum) * 0.0 == 0.0)))
+        dq_by_entry<TL>(qq, gg, K, V, sk, sv, ic, gq, W, rt, nact, tau, sl2, lse2, delta, acc, xa, xb, y, dsum);
     double dal = gq == 0 && i < T ? (double)tau * (xa - dsum * y) + xb : 0.0;
     if (bad) dal = NAN;
     if (rf.on) TL::rope_t(acc, i, sfreq, gq);  // gradient w.r.t. the unrotated q

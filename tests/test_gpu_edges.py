@@ -194,6 +194,30 @@ def test_logits_of_minus_infinity(H, Hkv, T, D, dtype, W, base, alpha):
     close(run(x, W, base, alpha), rows(x, W, base, alpha), dtype)
 
 
+@pytest.mark.parametrize("what", ["v", "dO", "k"])
+@pytest.mark.parametrize("H,Hkv,T,D,dtype,W,base,alpha", SHAPES)
+def test_gradients_of_infinities(H, Hkv, T, D, dtype, W, base, alpha, what):
+    # one element of one row is inf (for k: a whole row -inf under positive queries)
+    x = make(1, H, Hkv, T, D, dtype, 930)
+    j = T // 2
+    if what == "k":
+        x["q"] = x["q"].abs() + 0.125
+        x["k"][:, :, j] = -INF
+    else:
+        x[what][:, :, j, 3] = INF
+    ref = rows({n: x[n] for n in ("q", "k", "v")}, W, base, alpha)
+    o, lse = ref["o"].to(DT[dtype]), ref["lse"].float()
+    got, want = run(x, W, base, alpha, o, lse), rows(x, W, base, alpha, o, lse)
+    # dq may read row r1 of a rung with w = 0 too (dalpha needs it): 0 times its values
+    skip = torch.zeros(T, dtype=torch.bool)
+    for d, w, f in entries(W, base, alpha, T):
+        if f and w == 0:
+            skip[j + d + 1: j + d + 2] = True
+            if what == "dO":
+                skip[j] = True
+    close({"dq": got["dq"][:, :, ~skip]}, {"dq": want["dq"][:, :, ~skip]}, dtype)
+
+
 @pytest.mark.parametrize("what", ["o", "dq", "dk", "dv"])
 @pytest.mark.parametrize("D,W,alpha", [(64, 40, 1.0), (64, 20, 0.9), (128, 8, 1.0), (128, 8, 0.9), (32, 12, 0.9), (32, 5, 1.0)])
 def test_weights_of_24_bits(D, W, alpha, what):
