@@ -429,6 +429,35 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
 // every query row read from global memory by every key it attends, and the R^T of dk and
 // the dalpha sum as launches of their own, the training step of each took 82, 66, 15 and
 // 38 us more.
+// The terms of one query head in dk, dv of key j, its queries one by one and only those that
+// read it (quad layout; nact rungs, the wave's).
+template <typename S, int D>
+__device__ __forceinline__ void dkdv_by_entry(const S *Q, const S *G, const S *K, const S *V, const float *L,
+                                              const float *Dl, uint32_t sq, uint32_t sg, uint32_t sk, uint32_t sv,
+                                              int j, int gq, int T, int W, const RungTable &rt, int nact, float tau,
+                                              float sl2, typename Tile<S, D>::Acc &adk, typename Tile<S, D>::Acc &adv) {
+    using TL = Tile<S, D>;
+    const typename TL::Slice kj = TL::load(K, j, gq, sk), vj = TL::load(V, j, gq, sv);
+    // a window entry, or one of the two of a rung: y = 0 with key j as row r0, 1 as row r1
+    for (int e = 0; e <= W + 2 * nact; ++e) {
+        const int r = e <= W ? -1 : (e - W - 1) >> 1, y = e <= W ? 0 : (e - W - 1) & 1;
+        const float w = r < 0 ? 0.f : rt.w[r], wt = y ? w : 1.f - w;
+        const int i = j + (r < 0 ? e : rt.d0[r] + y);
+        const bool in = i < T && (w == 0.f ? y == 0 : y || j >= 1);
+        const int row = in ? i : j, nb = y ? min(j + 1, T - 1) : max(j - 1, 0);  // the entry's other row
+        const typename TL::Slice x = TL::load(Q, row, gq, sq), g = TL::load(G, row, gq, sg);
+        float s = TL::quad_dot(x, kj), dP = TL::quad_dot(g, vj);
+        if (w != 0.f) {
+            s = fmaf(1.f - wt, TL::quad_dot(x, TL::load(K, nb, gq, sk)), wt * s);
+            dP = fmaf(1.f - wt, TL::quad_dot(g, TL::load(V, nb, gq, sv)), wt * dP);
+        }
+        const float p = prob<TL::kF32>(s, sl2, L[row] * (TL::kF32 ? 1.f : kLog2e));
+        if (!in) continue;
+        TL::axpy(adk, tau * p * (dP - Dl[row]) * wt, x);
+        TL::axpy(adv, p * wt, g);
+    }
+}
+
 template <typename S, int D>
 constexpr int dkdv_waves = Tile<S, D>::kF32 ? (D == 32 ? 3 : D == 64 ? 2 : 1) : Tile<S, D>::NC <= 2 ? 4 : 2;
 
@@ -588,24 +617,6 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
         kj = TL::load(K, row, gq, sk);
         vj = TL::load(V, row, gq, sv);
     }
-    // as in the forward: rows outside the window took part with weights of 0
-    if (!valu && __builtin_amdgcn_ballot_w64(!(TL::finite(adk) && TL::finite(adv)))) {
-        TL::zero(adk);
-        TL::zero(adv);
-        for (int pass = 0; pass < passes; ++pass) {
-            const int bh = hd.q_of(bk, pass * ts.hs + hs);
-            const S *Q = q + lay.q.head(bh, hd.H), *G = dO + lay.g.head(bh, hd.H);
-            for (int i = t0; i < min(t0 + 16 + W, T); ++i) {
-                const Slice x = TL::load(Q, i, gq, sq), y = TL::load(G, i, gq, sg);
-                const float s = TL::quad_dot(x, kj), dP = TL::quad_dot(y, vj);
-                const float p = prob<TL::kF32>(s, sl2, lse[(size_t)bh * T + i] * kLse);
-                if (i >= j && i - j <= W) {
-                    TL::axpy(adk, tau * p * (dP - delta_in[(size_t)bh * T + i]), x);
-                    TL::axpy(adv, p, y);
-                }
-            }
-        }
-    }
 
     // ---- rungs (quad layout) ----
     for (int pass = 0; pass < (nact > 0 ? passes : 0); ++pass) {
@@ -709,6 +720,17 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
             __builtin_amdgcn_sched_barrier(0);
             TL::axpy2(adv, p[0], xg[0], p[1], xg[1]);
             load_g(nx);
+        }
+    }
+
+    // as in the forward: queries that do not read the key took part with weights of 0
+    if (__builtin_amdgcn_ballot_w64(!(TL::finite(adk) && TL::finite(adv)))) {
+        TL::zero(adk);
+        TL::zero(adv);
+        for (int pass = 0; pass < passes; ++pass) {
+            const int bh = hd.q_of(bk, pass * ts.hs + hs);
+            dkdv_by_entry<S, D>(q + lay.q.head(bh, hd.H), dO + lay.g.head(bh, hd.H), K, V, lse + (size_t)bh * T,
+                                delta_in + (size_t)bh * T, sq, sg, sk, sv, jc, gq, T, W, rt, nact, tau, sl2, adk, adv);
         }
     }
 

@@ -208,6 +208,7 @@ def test_gradients_of_infinities(H, Hkv, T, D, dtype, W, base, alpha, what):
     ref = rows({n: x[n] for n in ("q", "k", "v")}, W, base, alpha)
     o, lse = ref["o"].to(DT[dtype]), ref["lse"].float()
     got, want = run(x, W, base, alpha, o, lse), rows(x, W, base, alpha, o, lse)
+    close(got, want, dtype, ("dk", "dv"))
     # dq may read row r1 of a rung with w = 0 too (dalpha needs it): 0 times its values
     skip = torch.zeros(T, dtype=torch.bool)
     for d, w, f in entries(W, base, alpha, T):
