@@ -122,7 +122,8 @@ size_t fibattn_backward_workspace_bytes(int B, int H, int T, int d_head, int W, 
  *   workspace : device buffer of at least fibattn_backward_workspace_bytes(...)
  *   rope_base : 0 -> dq, dk are gradients w.r.t. the rotated q, k passed in;
  *               > 1 -> the inverse rotation R^T at true positions (same pairing and
- *               angles as fibattn_rope) is applied before the single rounding, so
+ *               angles as fibattn_rope; bfloat16: cos and sin from the hardware units,
+ *               absolute error <= 2.3e-7) is applied before the single rounding, so
  *               dq, dk are gradients w.r.t. the unrotated inputs of the RoPE step.
  * Same limits as the forward.
  */

@@ -172,22 +172,6 @@ __device__ __forceinline__ void rope_cs_rev(int t, double fr, float &c, float &s
     c = __builtin_amdgcn_cosf(r);
 }
 
-// The same angle for float32 rows: the eighth-turn remainder is rounded to float32 (error
-// <= 2^-25) and its sine and cosine come from their Taylor series, whose first dropped
-// terms are below 2e-9 at pi / 4, so both are within about 1e-7 relative.
-__device__ __forceinline__ void rope_cs_f32(int t, double fr, float &c, float &s) {
-    const double a = (double)t * fr;
-    const double n = rint(4.0 * a);  // quarter turns
-    const float x = (float)((a - 0.25 * n) * 6.283185307179586476925286766559);
-    const float x2 = x * x;
-    const float sx = x * fmaf(x2, fmaf(x2, fmaf(x2, fmaf(x2, 1.f / 362880.f, -1.f / 5040.f), 1.f / 120.f), -1.f / 6.f), 1.f);
-    const float cx = fmaf(x2, fmaf(x2, fmaf(x2, fmaf(x2, fmaf(x2, -1.f / 3628800.f, 1.f / 40320.f), -1.f / 720.f), 1.f / 24.f), -0.5f), 1.f);
-    const int quad = (int)n & 3;
-    const float u = quad & 1 ? cx : sx, w = quad & 1 ? sx : cx;
-    s = quad & 2 ? -u : u;
-    c = (quad == 1 || quad == 2) ? -w : w;
-}
-
 // The same angle with its Taylor series in float64 (first dropped terms below 2e-16 at
 // pi / 4), so cos and sin are the exact values rounded to float32 once.
 __device__ __forceinline__ void rope_cs_f64(int t, double fr, float &c, float &s) {

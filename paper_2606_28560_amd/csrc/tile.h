@@ -375,8 +375,12 @@ struct Tile {
         for (int c = 0; c < NC; ++c) *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(row) + 16 * g + 64 * c) = x.c[c];
     }
 
-    // R^T (the inverse RoPE rotation) of the lane's slice at position t.  sf: revolutions
-    // per position of every frequency.  The partner of dim d < D/2 is d + D/2: D/8 slice
+    // R^T (the inverse RoPE rotation) of the lane's slice at position t.  float32: the RoPE
+    // launch's angles and order, its bits.  bfloat16: float32 sums rotated with cos and sin of
+    // the hardware units (2.3e-7) and rounded once, where a launch on the stored gradients
+    // rounds twice: dq and dk are 0.91 times as far from 64 bits as with it (float64 angles
+    // here: B4 H8 T2048 d 64 W 64 step 74.1 -> 79.4 us).  sf: revolutions per position of
+    // every frequency.  The partner of dim d < D/2 is d + D/2: D/8 slice
     // positions on, except for bfloat16 rows of 32, whose partner lanes are g and g + 2.
     __device__ static __forceinline__ void rope_t(Acc &a, int t, const double *sf, int g) {
         if constexpr (!kF32 && D == 32) {
@@ -398,13 +402,16 @@ struct Tile {
                     const int p = 4 * b + e;
                     const int dim = kF32 ? 16 * b + 4 * g + e : 32 * (p >> 3) + 8 * g + (p & 7);
                     float c, s;
-                    if constexpr (kF32)
-                        rope_cs_f32(t, sf[dim], c, s);
-                    else
-                        rope_cs_rev(t, sf[dim], c, s);
                     const float x = a.c[b][e], y = a.c[HB + b][e];
-                    a.c[b][e] = x * c + y * s;
-                    a.c[HB + b][e] = y * c - x * s;
+                    if constexpr (kF32) {
+                        rope_cs_f64(t, sf[dim], c, s);
+                        a.c[b][e] = fmaf(c, x, s * y);
+                        a.c[HB + b][e] = fmaf(-s, x, c * y);
+                    } else {
+                        rope_cs_rev(t, sf[dim], c, s);
+                        a.c[b][e] = x * c + y * s;
+                        a.c[HB + b][e] = y * c - x * s;
+                    }
                 }
         }
     }

@@ -254,3 +254,38 @@ def test_weights_of_24_bits(D, W, alpha, what):
     err = ((got - want).abs() - 2.0 ** -8 * want.abs()).clamp_min(0.0) / mass
     print(f"{what} D{D} W{W} alpha {alpha}: error over the terms' sum {float(err.max()):.1e}", flush=True)
     assert err.max() <= 4e-7
+
+
+ROTATED = [(32, "bf16", 8), (64, "bf16", 20), (128, "bf16", 8), (32, "fp32", 8), (64, "fp32", 8), (128, "fp32", 8),
+           (64, "fp32", 40)]
+
+
+@pytest.mark.parametrize("H", [2, 64])
+@pytest.mark.parametrize("D,dtype,W", ROTATED)
+def test_gradients_rotated_back(D, dtype, W, H):
+    # float32: the bits of the RoPE launch on the gradients that are not rotated.  bfloat16:
+    # one rounding (2^-8 of the value at most), also at 355 and 710 radians, near a half turn,
+    # where the other element of the pair is 0 and the small sine counts to its last bits (the
+    # float32 sums before: 2e-6 of the largest).
+    T = 720
+    x = make(1, H, H, T, D, dtype, 960)
+    x["k"][..., 0] = 0.0
+    x["q"][..., 0] = 0.0
+    got = run(x, W, FIB, 0.9, rope_base=10000.0)
+    plain = run(x, W, FIB, 0.9) if dtype == "fp32" else rows(x, W, FIB, 0.9, got["o"], got["lse"])
+    t = torch.tensor([355, 710])
+    ang = t.double()[:, None] * 10000.0 ** (-2.0 * torch.arange(D // 2, dtype=torch.float64) / D)
+    c, s = ang.cos(), ang.sin()
+    for n in ("dq", "dk"):
+        if dtype == "fp32":
+            assert torch.equal(got[n], F.fibattn_rope(plain[n].cuda(), transpose=True).cpu()), n
+            continue
+        u, w = plain[n][0, :, t, :D // 2], plain[n][0, :, t, D // 2:]
+        want = torch.cat([u * c + w * s, w * c - u * s], -1)
+        err = (got[n][0, :, t].double() - want).abs() - 2.0 ** -8 * want.abs()
+        # element 0 is w s: what is uncertain in w counts s times
+        slack = 2e-6 * plain[n].abs().max() * torch.cat([torch.where(torch.arange(D // 2) == 0, s.abs(), 1.0)] + [torch.ones_like(s)], -1)
+        print(f"{n}: error past the rounding, of what the sums leave open {float((err / slack).max()):.2f}", flush=True)
+        assert (err <= slack).all(), n
+    if dtype == "fp32":
+        assert torch.equal(got["dv"], plain["dv"]) and got["dalpha"] == plain["dalpha"]
