@@ -174,10 +174,10 @@ fibattn_status_t fibattn_backward_gqa(const void *q, const void *k, const void *
  * A query row is read by its own query only, so it is rotated inside the forward at no
  * extra row traffic; a key row is read by up to 1 + W + K queries and is rotated once,
  * by the RoPE launch.  o and lse are those of fibattn_forward_gqa on (R q, k, v).
- * One launch.  bfloat16 takes cos and sin from the hardware units (absolute error
- * <= 2.3e-7 with the angle's float32 rounding, against ~1e-7 for fibattn_rope), so an
- * element of q_out can differ from fibattn_rope's by one bfloat16 rounding step where the
- * exact value lies that close to a rounding midpoint; float32 has fibattn_rope's angles.
+ * One launch.  q_out has the bits of fibattn_rope, except that bfloat16 with d_head 64 and
+ * W <= 16 takes cos and sin from the hardware units (absolute error <= 2.3e-7 with the
+ * angle's float32 rounding, against ~1e-7 for fibattn_rope): there an element can differ by
+ * one bfloat16 rounding step where the exact value lies that close to a rounding midpoint.
  * q_out NULL: bfloat16 with d_head 64 and W <= 16 only (else FIBATTN_ERR_UNSUPPORTED).
  */
 fibattn_status_t fibattn_forward_rope_q(const void *q, const void *k, const void *v,

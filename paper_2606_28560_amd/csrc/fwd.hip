@@ -72,11 +72,12 @@ __device__ __forceinline__ void forward_by_entry(const typename TL::Slice &qq, c
 // INTERP: some rung has w != 0, so the second row r1 is read; otherwise two rungs are
 // taken together.  DEV: the rung table is the one at rtp, built on the device (rt_arg
 // unused).  rf.on: q holds unrotated rows; each is rotated where it is loaded (a query row
-// is used by one query only) and written to qrot, placed by lay.dq, for the backward: 2 to 4
-// us more here against 5 to 7 us for a launch of its own.
+// is used by one query only, so qrot may be q itself: no restrict on q) and written to qrot,
+// placed by lay.dq, for the backward: 3 to 5 us more here against 5 to 7 us for a launch of
+// its own.
 template <typename S, int D, bool INTERP, bool DEV>
 __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
-    const S *__restrict__ q, const S *__restrict__ k, const S *__restrict__ v, S *__restrict__ o,
+    const S *q, const S *__restrict__ k, const S *__restrict__ v, S *__restrict__ o,
     float *__restrict__ lse, int T, int W, RungTable rt_arg, const RungTable *__restrict__ rtp, float sl2,
     TileShape ts, Heads hd, Layouts lay, S *qrot, RopeFreq rf) {
     using TL = Tile<S, D>;
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     const int i = t0 + nq, ic = min(i, T - 1);     // quad layout query
     Slice qq = TL::load(Q, ic, gq, (uint32_t)(lay.q.st * (int)sizeof(S)));
     if (rf.on) {
-        if (threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
+        if (threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * TL::kRopeUnit;
         __syncthreads();
     }
 
@@ -294,7 +295,7 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
 // ---------------------------------------------------------------------------
 template <int D, bool DEV>
 __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
-    const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, float *__restrict__ o,
+    const float *q, const float *__restrict__ k, const float *__restrict__ v, float *__restrict__ o,
     float *__restrict__ lse, int T, int W, RungTable rt_arg, const RungTable *__restrict__ rtp, float sl2, int tiles,
     int blocks, Heads hd, Layouts lay, float *qrot, RopeFreq rf) {
     using TL = Tile<float, D>;
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
     const int blk = xcd_remap(block_number(), blocks);
     const int bh = blk / tiles, t0 = (blk % tiles) * 64 + 16 * wave;
     if (rf.on) {
-        if (threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
+        if (threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * TL::kRopeUnit;
         __syncthreads();
     }
     if (t0 >= T) return;  // no barrier below

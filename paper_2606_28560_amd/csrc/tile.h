@@ -318,8 +318,11 @@ struct Tile {
         }
     }
 
-    // RoPE of the lane's slice of a row at position t, rounded to S (as the RoPE launch
-    // rounds it); partners as in rope_t.  float32: exact cos and sin, rounded once.
+    // What a frequency (radians per position) is multiplied with for rope: the RoPE launch of
+    // bfloat16 rows of 64 reduces the angle in radians, the others' in revolutions.
+    static constexpr double kRopeUnit = !kF32 && D == 64 ? 1.0 : 0.15915494309189533576888376337251;
+    // RoPE of the lane's slice of a row at position t, with the angles, the order of the
+    // products and the rounding of the RoPE launch: its bits.  Partners as in rope_t.
     __device__ static __forceinline__ void rope(Slice &x, int t, const double *sf, int g) {
         if constexpr (kF32) {
 #pragma unroll
@@ -328,7 +331,6 @@ struct Tile {
                 for (int e = 0; e < 4; ++e) {
                     float c, s, u, w;
                     rope_cs_f64(t, sf[16 * a + 4 * g + e], c, s);
-                    // in the order of the RoPE launch: the same bits
                     u = __uint_as_float(x.c[a][e]);
                     w = __uint_as_float(x.c[a + NC / 2][e]);
                     x.c[a][e] = __float_as_uint(fmaf(c, u, -(s * w)));
@@ -343,11 +345,10 @@ struct Tile {
                 float r[2];
 #pragma unroll
                 for (int z = 0; z < 2; ++z) {
-                    float c, s, u, w;
-                    rope_cs_rev(t, sf[8 * (g & 1) + 2 * e + z], c, s);
+                    float c, s;
+                    rope_cs_f64(t, sf[8 * (g & 1) + 2 * e + z], c, s);
                     const float a = z ? bf16_hi(own) : bf16_lo(own), b = z ? bf16_hi(oth) : bf16_lo(oth);
-                    rope_rotate(hi ? b : a, hi ? a : b, c, s, u, w);
-                    r[z] = hi ? w : u;
+                    r[z] = hi ? fmaf(s, b, c * a) : fmaf(c, a, -(s * b));
                 }
                 x.c[0][e] = pack_bf16(r[0], r[1]);
             }
@@ -356,16 +357,23 @@ struct Tile {
             for (int a = 0; a < NC / 2; ++a)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const uint32_t uw = x.c[a][e], vw = x.c[a + NC / 2][e];
-                    float u[2], w[2];
+                    const uint32_t uw = x.c[a][e], ww = x.c[a + NC / 2][e];
+                    float ox[2], oy[2];
 #pragma unroll
                     for (int z = 0; z < 2; ++z) {
                         float c, s;
-                        rope_cs_rev(t, sf[32 * a + 8 * g + 2 * e + z], c, s);
-                        rope_rotate(z ? bf16_hi(uw) : bf16_lo(uw), z ? bf16_hi(vw) : bf16_lo(vw), c, s, u[z], w[z]);
+                        const float u = z ? bf16_hi(uw) : bf16_lo(uw), w = z ? bf16_hi(ww) : bf16_lo(ww);
+                        if constexpr (D == 64) {
+                            rope_cs(t, sf[32 * a + 8 * g + 2 * e + z], c, s);
+                            rope_rotate(u, w, c, s, ox[z], oy[z]);
+                        } else {
+                            rope_cs_f64(t, sf[32 * a + 8 * g + 2 * e + z], c, s);
+                            ox[z] = fmaf(c, u, -(s * w));
+                            oy[z] = fmaf(s, u, c * w);
+                        }
                     }
-                    x.c[a][e] = pack_bf16(u[0], u[1]);
-                    x.c[a + NC / 2][e] = pack_bf16(w[0], w[1]);
+                    x.c[a][e] = pack_bf16(ox[0], ox[1]);
+                    x.c[a + NC / 2][e] = pack_bf16(oy[0], oy[1]);
                 }
         }
     }

@@ -289,3 +289,19 @@ def test_gradients_rotated_back(D, dtype, W, H):
         assert (err <= slack).all(), n
     if dtype == "fp32":
         assert torch.equal(got["dv"], plain["dv"]) and got["dalpha"] == plain["dalpha"]
+
+
+@pytest.mark.parametrize("H,T", [(2, 150), (64, 1500)])
+@pytest.mark.parametrize("D,dtype,W", ROTATED)
+def test_rotated_q_has_the_bits_of_the_rope_launch(D, dtype, W, H, T):
+    # also where the rotated rows take the place of q, for which they are written by the wave
+    # that has read them; and o and lse are those of the rotated q
+    x = {n: t.cuda() for n, t in make(1, H, H, T, D, dtype, 950).items()}
+    K, Q = F.fibattn_rope(x["k"]), F.fibattn_rope(x["q"])
+    o, lse, got = F.fibattn_forward_rope_q(x["q"], K, x["v"], W, FIB, 0.9)
+    want_o, want_lse = F.fibattn_forward(Q, K, x["v"], W, FIB, 0.9)
+    place = x["q"].clone()
+    o2, lse2, _ = F.fibattn_forward_rope_q(place, K, x["v"], W, FIB, 0.9, q_out=place)
+    torch.cuda.synchronize()
+    assert torch.equal(got, Q) and torch.equal(o, want_o) and torch.equal(lse, want_lse)
+    assert torch.equal(place, Q) and torch.equal(o2, o) and torch.equal(lse2, lse)
