@@ -38,7 +38,7 @@ namespace fibattn {
 // chunks' K and V rows are staged in LDS, S = K.Q^T and dP = V.dO^T taken on the matrix
 // cores, dq += K^T (tau dS) there; rungs are dot products of the rows r0 and r1 (r1 is
 // needed for dalpha even when w = 0) on the VALU, four lanes per row.  The dalpha parts are
-// float32 products added up in float64.
+// multiplied and added up in float64.
 //
 // What bounds it: as the forward, the latency of the rung gathers and their VALU work.
 // Against a kernel with one lane group per query, every row read from global memory by
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
             __syncthreads();
             for (int c = 0; c < n; ++c) {
                 const int base = 16 * wv + 32 * (n - 1 - c);
-                float ds[8], pd = 0.f;
+                float ds[8];
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
                     const f32x4 s = TL::scores(TL::staged(kr, base + 16 * b + nm, gm), qm);
@@ -178,10 +178,9 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
                         const bool in = (unsigned)(im - key) <= reach;
                         const float p = in ? fast_exp2(fmaf(s[e], sl2, -lse2_m)) : 0.f, dP = in ? dp[e] : 0.f;
                         ds[4 * b + e] = tau * p * (dP - delta_m);
-                        pd = fmaf(p, dP, pd);
+                        dsum = fma((double)p, (double)dP, dsum);
                     }
                 }
-                dsum += (double)pd;
                 TL::accumulate(acc, kr, base, TL::weights(ds), gm);
             }
         }
@@ -226,12 +225,11 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
             TL::axpy2(acc, c * (1.f - w), x[0], c * w, x[1]);
         else
             TL::axpy(acc, c, x[0]);
-        const float fp = (float)rt.f[r] * p;
-        const double ds = (double)(b - a);
-        xa = fma((double)(fp * dP), ds, xa);
-        xb = fma((double)fp, (double)dv, xb);
-        y = fma((double)fp, ds, y);
-        dsum += (double)(p * dP);
+        const double fp = (double)rt.f[r] * (double)p, ds = (double)(b - a);
+        xa = fma(fp * (double)dP, ds, xa);
+        xb = fma(fp, (double)dv, xb);
+        y = fma(fp, ds, y);
+        dsum = fma((double)p, (double)dP, dsum);
     };
     if constexpr (NBUF == 2) {
         for (int r = 0; r < nact; r += 2) {

@@ -256,6 +256,31 @@ def test_weights_of_24_bits(D, W, alpha, what):
     assert err.max() <= 4e-7
 
 
+def test_dalpha_adds_float64_products():
+    # bfloat16, logits of 0, lse 0 (p = 1): dP = +-(2^23 + 1) in the window, three of each sign,
+    # and two rungs whose f p dP need 31 bits, all of which cancel to a small exact number
+    T, D, W, base, alpha = 192, 64, 40, [101, 203], 0.5  # distances 50.5 and 101.5
+    x = {n: torch.zeros(1, 1, T, D, dtype=torch.bfloat16) for n in ("q", "k", "v", "dO")}
+    i = T - 1
+    x["q"][:, :, i, 0] = 1.0
+    x["dO"][:, :, i, 1], x["dO"][:, :, i, 2] = 4096.0, 1.0
+
+    def value(j, hi, lo):  # dP = 4096 hi + lo
+        x["v"][:, :, j, 1], x["v"][:, :, j, 2] = hi, lo
+
+    for j, sign in ((T - 32, 1), (T - 31, 1), (T - 30, 1), (T - 16, -1), (T - 15, -1), (T - 14, -1)):
+        value(j, sign * 2048.0, sign * 1.0)
+    value(i, 0.0, 5.0)
+    for d, hi, lo in ((50, 2048.0, 1.0), (101, -1016.0, 3.0)):
+        for y in (0, 1):
+            value(i - d - y, hi, lo)
+        x["k"][:, :, i - d, 0], x["k"][:, :, i - d - 1, 0] = 1.0, -1.0  # logit 0, <q, k1 - k0> = -2
+    lse, o = torch.zeros(1, 1, T), torch.zeros(1, 1, T, D, dtype=torch.bfloat16)
+    want = rows(x, W, base, alpha, o, lse)["dalpha"]
+    got = run(x, W, base, alpha, o, lse)["dalpha"]
+    assert abs(got - want) <= 2.0 ** -23 * abs(want), (got, want)
+
+
 ROTATED = [(32, "bf16", 8), (64, "bf16", 20), (128, "bf16", 8), (32, "fp32", 8), (64, "fp32", 8), (128, "fp32", 8),
            (64, "fp32", 40)]
 
