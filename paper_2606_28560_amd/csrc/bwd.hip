@@ -151,6 +151,7 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
     typename TL::Acc acc;
     TL::zero(acc);
     double dsum = 0.0;  // the entries' sum of p dP (this lane's part)
+    bool tiny = false;
     {
         const Slice qm = TL::from_quad(qq, lane), gmm = TL::from_quad(gg, lane);
         const float lse2_m = __shfl(lse2, 4 * nm, 64), delta_m = __shfl(delta, 4 * nm, 64);
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
             __syncthreads();
             for (int c = 0; c < n; ++c) {
                 const int base = 16 * wv + 32 * (n - 1 - c);
-                float ds[8];
+                float ds[8], x[8], least = INFINITY;
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
                     const f32x4 s = TL::scores(TL::staged(kr, base + 16 * b + nm, gm), qm);
@@ -176,11 +177,15 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
                     for (int e = 0; e < 4; ++e) {
                         const int key = rbeg + base + 16 * b + 4 * gm + e;
                         const bool in = (unsigned)(im - key) <= reach;
-                        const float p = in ? fast_exp2(fmaf(s[e], sl2, -lse2_m)) : 0.f, dP = in ? dp[e] : 0.f;
+                        const float xe = fmaf(s[e], sl2, -lse2_m);
+                        least = fminf(least, xe);
+                        x[4 * b + e] = in ? xe : -INFINITY;
+                        const float p = in ? fast_exp2(xe) : 0.f, dP = in ? dp[e] : 0.f;
                         ds[4 * b + e] = tau * p * (dP - delta_m);
                         dsum = fma((double)p, (double)dP, dsum);
                     }
                 }
+                tiny |= tiny_weight(x, least);
                 TL::accumulate(acc, kr, base, TL::weights(ds), gm);
             }
         }
@@ -219,7 +224,7 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
         const bool in = i < T && (INTERP ? d0 < i || (d0 == i && w == 0.f) : d0 <= i);
         const float a = TL::dot(qq, x[0]), t = TL::dot(qq, x[1]), b = i - d0 - 1 >= 0 ? t : 0.f;
         const float s = quad_sum(INTERP ? (1.f - w) * a + w * b : a);
-        const float p = in ? fast_exp2(fmaf(s, sl2, -lse2)) : 0.f;
+        const float p = in ? exp2f(fmaf(s, sl2, -lse2)) : 0.f;
         const float c = tau * p * (dP - delta);
         if constexpr (INTERP)
             TL::axpy2(acc, c * (1.f - w), x[0], c * w, x[1]);
@@ -259,7 +264,7 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
         }
     }
     // as in the forward: entries the query does not have took part with weights of 0
-    if (__builtin_amdgcn_ballot_w64(!(TL::finite(acc) && (xa + xb + y + dsum) * 0.0 == 0.0)))
+    if (tiny || __builtin_amdgcn_ballot_w64(!(TL::finite(acc) && (xa + xb + y + dsum) * 0.0 == 0.0)))
         dq_by_entry<TL>(qq, gg, K, V, sk, sv, ic, gq, W, rt, nact, tau, sl2, lse2, delta, acc, xa, xb, y, dsum);
 
     if (rf.on) TL::rope_t(acc, i, sfreq, gq);  // gradient w.r.t. the unrotated q
@@ -527,6 +532,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
     // further from 64 bits than the VALU's at W <= 16, nearer at W >= 79; B4 H8 T1024 d 64
     // W 12: 25.1 us with them, 25.6 here).
     const bool valu = TL::kF32 && W <= 16;
+    bool tiny = false;
     typename TL::Acc adk, adv;
     TL::zero(adk);
     TL::zero(adv);
@@ -582,7 +588,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                 }
                 for (int c = 0; c < n; ++c) {
                     const int base = 16 * wv + 32 * c;  // the chunk's first staged row
-                    float ds[8], p[8];
+                    float ds[8], p[8], xs[8], least = INFINITY;
 #pragma unroll
                     for (int b = 0; b < 2; ++b) {
                         constexpr int CH = TL::NC == 2 ? 4 : 8;
@@ -594,11 +600,20 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const bool in = jm < T && (unsigned)(rbeg + si + e - jm) <= reach;
-                            const float x = prob<TL::kF32>(s[e], sl2, l2[e]);
+                            float x;
+                            if constexpr (TL::kF32) {
+                                x = prob<true>(s[e], sl2, l2[e]);
+                            } else {
+                                const float xe = fmaf(s[e], sl2, -l2[e]);
+                                least = fminf(least, xe);
+                                xs[4 * b + e] = in ? xe : -INFINITY;
+                                x = fast_exp2(xe);
+                            }
                             p[4 * b + e] = in ? x : 0.f;
                             ds[4 * b + e] = in ? tau * x * (dp[e] - de[e]) : 0.f;
                         }
                     }
+                    if constexpr (!TL::kF32) tiny |= tiny_weight(xs, least);
                     TL::accumulate(adk, qb, base, TL::weights(ds), gm);
                     TL::accumulate(adv, gb, base, TL::weights(p), gm);
                 }
@@ -722,7 +737,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
     }
 
     // as in the forward: queries that do not read the key took part with weights of 0
-    if (__builtin_amdgcn_ballot_w64(!(TL::finite(adk) && TL::finite(adv)))) {
+    if (tiny || __builtin_amdgcn_ballot_w64(!(TL::finite(adk) && TL::finite(adv)))) {
         TL::zero(adk);
         TL::zero(adv);
         for (int pass = 0; pass < passes; ++pass) {

@@ -145,6 +145,7 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     // ---- window band (MFMA layout) ----
     Slice qm;
     float m = 0.f, l = 0.f;
+    bool tiny = false;
     typename TL::Acc acc;
     TL::zero(acc);
     const unsigned reach = (unsigned)min(W, im);  // 0 <= im - key <= W and key >= 0
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
         __syncthreads();
         for (int c = 0; c < n; ++c) {
             const int base = 16 * wv + 32 * (n - 1 - c);  // the chunk's first staged row
-            float p[8], mx = -INFINITY;
+            float p[8], mx = -INFINITY, least = INFINITY;
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 const f32x4 s = TL::template scores<TL::NC == 8 ? 8 : 4>(TL::staged(kr, base + 16 * b + nm, gm), qm);
@@ -177,20 +178,24 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
                     const int key = rbeg + base + 16 * b + 4 * gm + e;
                     p[4 * b + e] = (unsigned)(im - key) <= reach ? s[e] : -INFINITY;
                     mx = fmaxf(mx, p[4 * b + e]);
+                    least = fminf(least, s[e]);
                 }
             }
             mx = max4(mx) * sl2;
             if (c0 + c == 0) {
                 m = mx;  // -inf only where key im itself has a logit of -inf
             } else if (__builtin_amdgcn_ballot_w64(mx > m)) {
-                const float mn = fmaxf(m, mx), f = fast_exp2(m - mn);
+                const float mn = fmaxf(m, mx), f = exp2f(m - mn);
                 m = mn;
                 l *= f;
                 TL::scale(acc, f);
             }
 #pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = fmaf(p[e], sl2, -m);
+            tiny |= tiny_weight(p, fmaf(least, sl2, -m));
+#pragma unroll
             for (int e = 0; e < 8; ++e) {
-                p[e] = fast_exp2(fmaf(p[e], sl2, -m));
+                p[e] = fast_exp2(p[e]);
                 l += p[e];
             }
             TL::accumulate(acc, vr, base, TL::weights(p), gm);
@@ -229,14 +234,14 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
         // for any reference).
         const bool grow = mb > m + kFwdSlack;
         if (__builtin_amdgcn_ballot_w64(grow)) {
-            const float mn = grow ? mb : m, f = fast_exp2(m - mn);
+            const float mn = grow ? mb : m, f = exp2f(m - mn);
             m = mn;
             l *= f;
             TL::scale(acc, f);
         }
 #pragma unroll
         for (int y = 0; y < RB; ++y) {
-            p[y] = fast_exp2(fmaf(s[y], sl2, -m));
+            p[y] = exp2f(fmaf(s[y], sl2, -m));
             l += p[y];
         }
     };
@@ -278,8 +283,9 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     }
     // Entries a query does not have took part with weights of 0: rows of the chunks outside
     // its window, and its own row in the place of a rung's.  If that, or what the query does
-    // attend, left anything that is not finite, the entries are taken one by one instead.
-    if (__builtin_amdgcn_ballot_w64(!(TL::finite(acc) && l * 0.f == 0.f)))
+    // attend, left anything that is not finite, the entries are taken one by one instead;
+    // so are weights too small for the matrix cores.
+    if (tiny || __builtin_amdgcn_ballot_w64(!(TL::finite(acc) && l * 0.f == 0.f)))
         forward_by_entry<TL>(qq, K, V, sk, sv, ic, gq, W, rt, nact, sl2, acc, m, l);
 
     if (i < T) {

@@ -432,13 +432,25 @@ struct Tile {
 // lse (a query dropped by its caller) loses nothing.
 template <bool F32>
 __device__ __forceinline__ float prob(float s, float sl2, float l) {
-    if constexpr (!F32) return fast_exp2(fmaf(s, sl2, -l));
+    if constexpr (!F32) return exp2f(fmaf(s, sl2, -l));
     const float v = l * kLog2e;
     // kLog2e + 1.925963e-8 = log2(e)
     float low = fmaf(l, 1.925963033500e-8f, fmaf(l, kLog2e, -v)) * kLn2;
     low = __builtin_isfinite(v) ? low : 0.f;
-    const float p = fast_exp2(fmaf(s, sl2, -v));
+    const float p = exp2f(fmaf(s, sl2, -v));
     return fmaf(p, -low, p);
+}
+
+// Weights 2^x of a bfloat16 band that the matrix cores cannot take in full: three bfloat16
+// parts hold 24 bits from 2^-109 on (their last one is a multiple of 2^-133), and the exp2
+// instruction gives 0 below 2^-126.  Below 2^-150 a float32 is 0 either way.  `least`: the
+// least x of the lane's rows, in its window or not, which is all that is looked at otherwise.
+constexpr float kLeastWeight = -100.f;
+__device__ __forceinline__ bool tiny_weight(const float *x, float least) {
+    if (!__builtin_amdgcn_ballot_w64(least < kLeastWeight)) return false;
+    bool t = false;
+    for (int e = 0; e < 8; ++e) t |= x[e] < kLeastWeight && x[e] >= -150.f;
+    return __builtin_amdgcn_ballot_w64(t);
 }
 
 // Weight and lane bookkeeping of a launch: `nw` waves per workgroup are `hs` query heads

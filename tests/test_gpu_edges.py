@@ -220,6 +220,30 @@ def test_gradients_of_infinities(H, Hkv, T, D, dtype, W, base, alpha, what):
 
 
 @pytest.mark.parametrize("what", ["o", "dq", "dk", "dv"])
+@pytest.mark.parametrize("D,dtype,W", [(128, "bf16", 8), (64, "bf16", 20), (32, "bf16", 8), (64, "fp32", 8), (64, "fp32", 40)])
+@pytest.mark.parametrize("rung", [False, True])
+def test_probability_below_the_normal_range(D, dtype, W, rung, what):
+    # p = 2^-130 (a subnormal float32, which bfloat16 parts cannot hold) times a value or a dO
+    # of 2^127, or a dP of 2^110: results of ordinary size
+    T, d = 128, 55 if rung else 2
+    x = {n: torch.zeros(1, 1, T, D, dtype=DT[dtype]) for n in ("q", "k", "v", "dO")}
+    i = T - 5
+    x["q"][:, :, i, 0] = 1.0
+    x["k"][:, :, i - d, 0] = float(torch.tensor(-130.0 * math.log(2.0) * math.sqrt(D)).to(DT[dtype]))
+    if what == "o":
+        x["v"][:, :, i - d, 1] = 2.0 ** 127
+        del x["dO"]
+    elif what == "dv":
+        x["dO"][:, :, i, 1] = 2.0 ** 127
+    else:
+        x["v"][:, :, i - d, 1], x["dO"][:, :, i, 1] = 2.0 ** 55, 2.0 ** 55
+    o, lse = torch.zeros(1, 1, T, D, dtype=DT[dtype]), torch.zeros(1, 1, T)
+    row, dim = (i, 1 if what == "o" else 0) if what in ("o", "dq") else (i - d, 0 if what == "dk" else 1)
+    a, b = (float(r[what][0, 0, row, dim]) for r in (run(x, W, FIB, 1.0, o, lse), rows(x, W, FIB, 1.0, o, lse)))
+    assert abs(b) > 1e-8 and abs(a - b) <= 1e-2 * abs(b), (a, b)
+
+
+@pytest.mark.parametrize("what", ["o", "dq", "dk", "dv"])
 @pytest.mark.parametrize("D,W,alpha", [(64, 40, 1.0), (64, 20, 0.9), (128, 8, 1.0), (128, 8, 0.9), (32, 12, 0.9), (32, 5, 1.0)])
 def test_weights_of_24_bits(D, W, alpha, what):
     # bfloat16 rows times float32 weights, two of the rows chosen so that the sum cancels to
