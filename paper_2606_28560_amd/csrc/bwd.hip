@@ -156,9 +156,10 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
         const Slice qm = TL::from_quad(qq, lane), gmm = TL::from_quad(gg, lane);
         const float lse2_m = __shfl(lse2, 4 * nm, 64), delta_m = __shfl(delta, 4 * nm, 64);
         const unsigned reach = (unsigned)min(W, im);  // 0 <= im - key <= W and key >= 0
-        for (int c0 = 0; c0 < ts.nc; c0 += ts.cps) {
+        const int nc = min(ts.nc, (T0 + 16 * runs + 31) >> 5);
+        for (int c0 = 0; c0 < nc; c0 += ts.cps) {
             // chunks as in the forward
-            const int n = min(ts.cps, ts.nc - c0);
+            const int n = min(ts.cps, nc - c0);
             const int rbeg = T0 + 16 - 32 * (c0 + n), rows = 16 * (runs - 1) + 32 * n;
             char *kr = smem, *vr = smem + rows * TL::kRow;
             if (c0 > 0) __syncthreads();  // every wave is done with the rows staged before
@@ -167,6 +168,7 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
             wait_vmem();
             __syncthreads();
             for (int c = 0; c < n; ++c) {
+                if (t0 + 16 - 32 * (c0 + c) <= 0) break;
                 const int base = 16 * wv + 32 * (n - 1 - c);
                 float ds[8], x[8], least = INFINITY;
 #pragma unroll
@@ -540,11 +542,12 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
         const Slice km = TL::from_quad(kj, lane), vm = TL::from_quad(vj, lane);
         const unsigned reach = (unsigned)min(W, T - 1 - jm);  // 0 <= query - jm <= W and query < T
         bool first = true;
+        const int nc = min(ts.nc, (T - T0 + 31) >> 5);  // chunks with rows below T
         for (int pass = 0; pass < passes; ++pass)
-            for (int c0 = 0; c0 < ts.nc; c0 += ts.cps) {
+            for (int c0 = 0; c0 < nc; c0 += ts.cps) {
                 // chunks c0 .. c0 + n - 1 of every run: chunk c of run wv is the queries
                 // [T0 + 16 wv + 32 c, T0 + 16 wv + 32 (c + 1))
-                const int n = min(ts.cps, ts.nc - c0);
+                const int n = min(ts.cps, nc - c0);
                 const int rbeg = T0 + 32 * c0, rows = 16 * (runs - 1) + 32 * n;
                 char *qr = smem, *gr = smem + ts.hs * rows * TL::kRow;
                 float *sl = reinterpret_cast<float *>(gr + ts.hs * rows * TL::kRow), *sd = sl + ts.hs * rows;
@@ -587,6 +590,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                     continue;
                 }
                 for (int c = 0; c < n; ++c) {
+                    if (t0 + 32 * (c0 + c) >= T) break;
                     const int base = 16 * wv + 32 * c;  // the chunk's first staged row
                     float ds[8], p[8], xs[8], least = INFINITY;
 #pragma unroll

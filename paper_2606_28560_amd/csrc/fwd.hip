@@ -149,10 +149,11 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     typename TL::Acc acc;
     TL::zero(acc);
     const unsigned reach = (unsigned)min(W, im);  // 0 <= im - key <= W and key >= 0
-    for (int c0 = 0; c0 < ts.nc; c0 += ts.cps) {
+    const int nc = min(ts.nc, (T0 + 16 * runs + 31) >> 5);  // chunks with rows >= 0
+    for (int c0 = 0; c0 < nc; c0 += ts.cps) {
         // chunks c0 .. c0 + n - 1 of every run: chunk c of run wv is the rows
         // [T0 + 16 wv + 16 - 32 (c + 1), T0 + 16 wv + 16 - 32 c)
-        const int n = min(ts.cps, ts.nc - c0);
+        const int n = min(ts.cps, nc - c0);
         const int rbeg = T0 + 16 - 32 * (c0 + n), rows = 16 * (runs - 1) + 32 * n;
         char *kr = smem, *vr = smem + rows * TL::kRow;
         if (c0 > 0) __syncthreads();  // every wave is done with the rows staged before
@@ -168,6 +169,7 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
         wait_vmem();
         __syncthreads();
         for (int c = 0; c < n; ++c) {
+            if (t0 + 16 - 32 * (c0 + c) <= 0) break;  // rows before the start
             const int base = 16 * wv + 32 * (n - 1 - c);  // the chunk's first staged row
             float p[8], mx = -INFINITY, least = INFINITY;
 #pragma unroll
