@@ -61,9 +61,9 @@ __device__ __forceinline__ void dq_by_entry(const typename TL::Slice &qq, const 
         const bool in = ic >= d + (w != 0.f), has1 = r >= 0 && ic > d;  // row -1 is the zero row
         const int r0 = in ? ic - d : ic, r1 = has1 ? ic - d - 1 : ic;
         const typename TL::Slice k0 = TL::load(K, r0, gq, sk), k1 = TL::load(K, r1, gq, sk);
-        const float s0 = TL::quad_dot(qq, k0), sn = TL::quad_dot(qq, k1), s1 = has1 ? sn : 0.f;
-        const float dP0 = TL::quad_dot(gg, TL::load(V, r0, gq, sv));
-        const float dPn = TL::quad_dot(gg, TL::load(V, r1, gq, sv)), dP1 = has1 ? dPn : 0.f;
+        const float s0 = TL::row_dot(qq, k0), sn = TL::row_dot(qq, k1), s1 = has1 ? sn : 0.f;
+        const float dP0 = TL::row_dot(gg, TL::load(V, r0, gq, sv));
+        const float dPn = TL::row_dot(gg, TL::load(V, r1, gq, sv)), dP1 = has1 ? dPn : 0.f;
         const float s = w != 0.f ? (1.f - w) * s0 + w * s1 : s0;
         const float dP = w != 0.f ? (1.f - w) * dP0 + w * dP1 : dP0;
         const float p = exp2f(s * sl2 - lse2);
@@ -289,20 +289,20 @@ __global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// dq, Delta and dalpha partials in float32: as the forward's float32 kernel, four lanes per
+// dq, Delta and dalpha partials in float32: as the forward's float32 kernel, L lanes per
 // query on the VALU, every sum in the order that tile.h states.  The window's K and V rows
 // are shared by the queries of a tile; staged in LDS they take the launch
 // of B4 H8 T1024 d 64 W 12 from 26.1 to 22.3 us (the forward, which reads each tensor's
 // window once, gained nothing from it).
 // ---------------------------------------------------------------------------
-template <int D, bool DEV>
+template <int D, int L, bool DEV>
 __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
     const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
     const float *__restrict__ o, const float *__restrict__ lse, const float *__restrict__ dO,
     float *__restrict__ dq, float *__restrict__ delta_out, double *__restrict__ partials, int T, int W,
     RungTable rt_arg, const RungTable *__restrict__ rtp, RopeFreq rf, float tau, int tiles, int blocks, int rows,
     Heads hd, Layouts lay) {
-    using TL = Tile<float, D>;
+    using TL = Tile<float, D, L>;
     using Slice = typename TL::Slice;
     const RungTable &rt = DEV ? *rtp : rt_arg;
     const bool bad = DEV && table_unusable(rt, W);  // bad device alpha, or another W
@@ -311,21 +311,24 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int nq = lane >> 2, gq = lane & 3;  // quad layout
+    constexpr int RW = 64 / L, QPB = 4 * RW;  // queries per wave and workgroup
+    const int nq = lane / L, gq = lane % L;
     if (block_number() >= blocks) return;
     const int blk = xcd_remap(block_number(), blocks);
-    const int bh = blk / tiles, T0 = (blk % tiles) * 64, t0 = T0 + 16 * wave;
+    const int bh = blk / tiles, T0 = (blk % tiles) * QPB, t0 = T0 + RW * wave;
     const int bk = hd.kv_of(bh);
     const float *K = k + lay.k.head(bk, hd.kv_heads());
     const float *V = v + lay.v.head(bk, hd.kv_heads());
     const uint32_t sk = (uint32_t)(4 * lay.k.st), sv = (uint32_t)(4 * lay.v.st);
-    const int i = t0 + nq, ic = min(i, T - 1), last = min(t0 + 15, T - 1);
+    const int i = t0 + nq, ic = min(i, T - 1), last = min(t0 + RW - 1, T - 1);
     const float sl2 = tau * kLog2e;
     const Slice qq = TL::load(q + lay.q.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.q.st));
     const Slice gg = TL::load(dO + lay.g.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.g.st));
-    const float delta = TL::quad_dot(gg, TL::load(o + lay.o.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.o.st)));
+    const float delta = TL::row_dot(gg, TL::load(o + lay.o.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.o.st)));
     const float lse2 = lse[(size_t)bh * T + ic] * kLog2e;
     // the window's rows of the workgroup, [T0 + 64 - rows, T0 + 64), where they are staged
+    // (four lanes per query only)
+    if constexpr (L != 4) rows = 0;
     const int rbeg = T0 + 64 - rows;
     char *kr = smem, *vr = smem + rows * TL::kRow;
     if (rows > 0) {
@@ -355,8 +358,8 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const float s = TL::quad_dot(qq, kk[u]);
-            const float dP = TL::quad_dot(gg, vv[u]);
+            const float s = TL::row_dot(qq, kk[u]);
+            const float dP = TL::row_dot(gg, vv[u]);
             const float p = d + u <= reach ? exp2f(s * sl2 - lse2) : 0.f;
             const float c = tau * p * (dP - delta);
             dsum += (double)p * (double)dP;
@@ -379,9 +382,9 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
         const int d0 = rt.d0[r], nx = min(r + 1, nact - 1);
         const float w = rt.w[r];
         const bool in = ic >= d0 + (w != 0.f), has1 = ic > d0;  // row -1 is the zero row
-        const float dP0 = TL::quad_dot(gg, vx[0]), dPn = TL::quad_dot(gg, vx[1]), dP1 = has1 ? dPn : 0.f;
+        const float dP0 = TL::row_dot(gg, vx[0]), dPn = TL::row_dot(gg, vx[1]), dP1 = has1 ? dPn : 0.f;
         load_rung(nx, V, sv, vx);
-        const float s0 = TL::quad_dot(qq, kx[0]), sn = TL::quad_dot(qq, kx[1]), s1 = has1 ? sn : 0.f;
+        const float s0 = TL::row_dot(qq, kx[0]), sn = TL::row_dot(qq, kx[1]), s1 = has1 ? sn : 0.f;
         const float s = (1.f - w) * s0 + w * s1;
         const float dP = (1.f - w) * dP0 + w * dP1;
         const float p = in ? exp2f(s * sl2 - lse2) : 0.f;
@@ -436,12 +439,11 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
 // 38 us more.
 // The terms of one query head in dk, dv of key j, its queries one by one and only those that
 // read it (quad layout; nact rungs, the wave's).
-template <typename S, int D>
-__device__ __forceinline__ void dkdv_by_entry(const S *Q, const S *G, const S *K, const S *V, const float *L,
+template <typename TL>
+__device__ __forceinline__ void dkdv_by_entry(const void *Q, const void *G, const void *K, const void *V, const float *L,
                                               const float *Dl, uint32_t sq, uint32_t sg, uint32_t sk, uint32_t sv,
                                               int j, int gq, int T, int W, const RungTable &rt, int nact, float tau,
-                                              float sl2, typename Tile<S, D>::Acc &adk, typename Tile<S, D>::Acc &adv) {
-    using TL = Tile<S, D>;
+                                              float sl2, typename TL::Acc &adk, typename TL::Acc &adv) {
     const typename TL::Slice kj = TL::load(K, j, gq, sk), vj = TL::load(V, j, gq, sv);
     // a window entry, or one of the two of a rung: y = 0 with key j as row r0, 1 as row r1
     for (int e = 0; e <= W + 2 * nact; ++e) {
@@ -451,16 +453,38 @@ __device__ __forceinline__ void dkdv_by_entry(const S *Q, const S *G, const S *K
         const bool in = i < T && (w == 0.f ? y == 0 : y || j >= 1);
         const int row = in ? i : j, nb = y ? min(j + 1, T - 1) : max(j - 1, 0);  // the entry's other row
         const typename TL::Slice x = TL::load(Q, row, gq, sq), g = TL::load(G, row, gq, sg);
-        float s = TL::quad_dot(x, kj), dP = TL::quad_dot(g, vj);
+        float s = TL::row_dot(x, kj), dP = TL::row_dot(g, vj);
         if (w != 0.f) {
-            s = fmaf(1.f - wt, TL::quad_dot(x, TL::load(K, nb, gq, sk)), wt * s);
-            dP = fmaf(1.f - wt, TL::quad_dot(g, TL::load(V, nb, gq, sv)), wt * dP);
+            s = fmaf(1.f - wt, TL::row_dot(x, TL::load(K, nb, gq, sk)), wt * s);
+            dP = fmaf(1.f - wt, TL::row_dot(g, TL::load(V, nb, gq, sv)), wt * dP);
         }
         const float p = prob<TL::kF32>(s, sl2, L[row] * (TL::kF32 ? 1.f : kLog2e));
         if (!in) continue;
         TL::axpy(adk, tau * p * (dP - Dl[row]) * wt, x);
         TL::axpy(adv, p * wt, g);
     }
+}
+
+// dalpha: the partials of the dq kernel, which has completed, in a fixed order (by the whole
+// workgroup; red: a value per thread).
+template <bool DEV>
+__device__ __forceinline__ void sum_partials(double *red, const double *partials, int n, float *dalpha, float *dtheta,
+                                             const RungTable &rt) {
+    double s = 0.0;
+    for (int t = threadIdx.x; t < n; t += blockDim.x) s += partials[t];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int st = blockDim.x >> 1; st >= 1; st >>= 1) {
+        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        const float da = (float)red[0];
+        *dalpha = da;
+        // a table built from theta: d L / d theta = dalpha * d alpha / d theta
+        if (DEV && dtheta) *dtheta = (float)((double)da * rt.dadtheta);
+    }
+    __syncthreads();
 }
 
 template <typename S, int D>
@@ -497,25 +521,8 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
     const uint32_t sk = (uint32_t)(lay.k.st * es), sv = (uint32_t)(lay.v.st * es);
     if (rf.on && threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
 
-    // dalpha: the partials of the dq kernel, which has completed, in a fixed order
-    if (block_number() == 0) {
-        double *red = reinterpret_cast<double *>(smem);
-        double s = 0.0;
-        for (int t = threadIdx.x; t < n_partials; t += blockDim.x) s += partials[t];
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int st = blockDim.x >> 1; st >= 1; st >>= 1) {
-            if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            const float da = (float)red[0];
-            *dalpha = da;
-            // a table built from theta: d L / d theta = dalpha * d alpha / d theta
-            if (DEV && dtheta) *dtheta = (float)((double)da * rt.dadtheta);
-        }
-        __syncthreads();
-    }
+    if (block_number() == 0)
+        sum_partials<DEV>(reinterpret_cast<double *>(smem), partials, n_partials, dalpha, dtheta, rt);
 
     const int t0 = T0 + 16 * wv;
     const int jm = t0 + nm;                     // MFMA layout key
@@ -574,7 +581,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                         const int r = 16 * wv + nq + d;
                         const bool in = j + d < T;
                         Slice x = TL::staged(qb, r, gq), y = TL::staged(gb, r, gq);
-                        const float s = TL::quad_dot(x, ka), dP = TL::quad_dot(y, va);
+                        const float s = TL::row_dot(x, ka), dP = TL::row_dot(y, va);
                         const float pr = prob<TL::kF32>(s, sl2, sl[hs * rows + r]);
                         const float c = in ? tau * pr * (dP - sd[hs * rows + r]) : 0.f;
                         if (__builtin_amdgcn_ballot_w64(!in)) {  // clamped rows: 0 times them must be 0
@@ -685,8 +692,8 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                     if (16 * h < nact) {
                         const int i = tp + 16 * u + rt.d0[min(nq + 16 * h, nact - 1)];
                         const int key = u ? min(tp + 16, T - 1) : max(tp - 1, 0), row = i < T ? i : key;
-                        es_[h][u] = TL::quad_dot(TL::load(Q, row, gq, sq), TL::load(K, key, gq, sk));
-                        ep_[h][u] = TL::quad_dot(TL::load(G, row, gq, sg), TL::load(V, key, gq, sv));
+                        es_[h][u] = TL::row_dot(TL::load(Q, row, gq, sq), TL::load(K, key, gq, sk));
+                        ep_[h][u] = TL::row_dot(TL::load(G, row, gq, sg), TL::load(V, key, gq, sv));
                     }
                 }
         }
@@ -699,8 +706,8 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
             float s[2], dP[2], c[2], p[2];
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
-                s[y] = TL::quad_dot(xq[y], kj);
-                dP[y] = TL::quad_dot(xg[y], vj);
+                s[y] = TL::row_dot(xq[y], kj);
+                dP[y] = TL::row_dot(xg[y], vj);
             }
             if constexpr (INTERP) {
                 // query i0 with key j - 1 is query i0 + 1 of the key four lanes before,
@@ -746,7 +753,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
         TL::zero(adv);
         for (int pass = 0; pass < passes; ++pass) {
             const int bh = hd.q_of(bk, pass * ts.hs + hs);
-            dkdv_by_entry<S, D>(q + lay.q.head(bh, hd.H), dO + lay.g.head(bh, hd.H), K, V, lse + (size_t)bh * T,
+            dkdv_by_entry<TL>(q + lay.q.head(bh, hd.H), dO + lay.g.head(bh, hd.H), K, V, lse + (size_t)bh * T,
                                 delta_in + (size_t)bh * T, sq, sg, sk, sv, jc, gq, T, W, rt, nact, tau, sl2, adk, adv);
         }
     }
@@ -780,6 +787,137 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
         const float sc = DEV && table_unusable(rt, W) ? NAN : 1.f;  // bad device alpha, or another W
         TL::store(dk + lay.dk.head(bk, hd.kv_heads()) + j * lay.dk.st, gq, adk, sc);
         TL::store(dv + lay.dv.head(bk, hd.kv_heads()) + j * lay.dv.st, gq, adv, sc);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// dk, dv in float32 where 16 keys a wave would leave the chip idle (f32_wide): one key per
+// D / 4 lanes, the query heads of its group one after another.
+// ---------------------------------------------------------------------------
+template <int D, bool DEV>
+__global__ __launch_bounds__(256) void bwd_dkdv_f32_kernel(
+    const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
+    const float *__restrict__ lse, const float *__restrict__ dO, const float *__restrict__ delta_in,
+    float *__restrict__ dk, float *__restrict__ dv, const double *__restrict__ partials, int n_partials,
+    float *__restrict__ dalpha, float *__restrict__ dtheta, int T, int W, RungTable rt_arg,
+    const RungTable *__restrict__ rtp, RopeFreq rf, float tau, float sl2, int tiles, int blocks, Heads hd, Layouts lay) {
+    constexpr int L = D / 4, RW = 64 / L;
+    using TL = Tile<float, D, L>;
+    using Slice = typename TL::Slice;
+    const RungTable &rt = DEV ? *rtp : rt_arg;
+    __shared__ double sfreq[D / 2], red[256];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nk = lane / L, g = lane % L;
+    if (block_number() >= blocks) return;
+    const int blk = xcd_remap(block_number(), blocks);
+    const int bk = blk / tiles, t0 = ((blk % tiles) * 4 + wave) * RW;
+    if (rf.on && threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
+    if (block_number() == 0)
+        sum_partials<DEV>(red, partials, n_partials, dalpha, dtheta, rt);
+    else if (rf.on)
+        __syncthreads();
+    if (t0 >= T) return;  // no barrier below
+    const float *K = k + lay.k.head(bk, hd.kv_heads()), *V = v + lay.v.head(bk, hd.kv_heads());
+    const uint32_t sq = (uint32_t)(4 * lay.q.st), sg = (uint32_t)(4 * lay.g.st);
+    const uint32_t sk = (uint32_t)(4 * lay.k.st), sv = (uint32_t)(4 * lay.v.st);
+    const int j = t0 + nk, jc = min(j, T - 1);
+    const int before = max(jc - 1, 0), after = min(jc + 1, T - 1);
+    const Slice kj = TL::load(K, jc, g, sk), vj = TL::load(V, jc, g, sv);
+    // the rows beside the key's: the other row of a rung entry
+    const Slice kb = TL::load(K, before, g, sk), vb = TL::load(V, before, g, sv);
+    const Slice ka = TL::load(K, after, g, sk), va = TL::load(V, after, g, sv);
+    int nact = 0;  // rungs through which a query reads some key of this wave: a prefix
+#pragma unroll
+    for (int r = 0; r < kMaxRungs; ++r) nact += ((r < rt.n) & (rt.d0[r] < T - t0)) ? 1 : 0;
+    nact = __builtin_amdgcn_readfirstlane(nact);
+    const int wmax = min(W, T - 1 - t0);
+
+    typename TL::Acc adk, adv;
+    TL::zero(adk);
+    TL::zero(adv);
+    // per-lane products of a logit or a dP, blended before the sum over the lanes
+    auto dots = [&](const Slice &x, const Slice &y) {
+        float t[TL::NC];
+#pragma unroll
+        for (int c = 0; c < TL::NC; ++c) t[c] = chunk_dot(x.c[c], y.c[c]);
+        return t[0];
+    };
+    auto sum = [&](float t) { return chunk_sum<1, L>(&t); };
+    for (int hg = 0; hg < hd.G; ++hg) {
+        const int bh = hd.q_of(bk, hg);
+        const float *Q = q + lay.q.head(bh, hd.H), *G = dO + lay.g.head(bh, hd.H);
+        const float *Le = lse + (size_t)bh * T, *De = delta_in + (size_t)bh * T;
+        // a query that does not read the key is replaced by the key's own, with weight 0
+        for (int d = 0; d <= wmax; d += 2) {
+            Slice x[2], y[2];
+            float l[2], dl[2];
+            bool in[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                in[u] = j + d + u < T && d + u <= W;
+                const int row = in[u] ? j + d + u : jc;
+                x[u] = TL::load(Q, row, g, sq);
+                y[u] = TL::load(G, row, g, sg);
+                l[u] = Le[row];
+                dl[u] = De[row];
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float s = sum(dots(x[u], kj)), dP = sum(dots(y[u], vj));
+                const float p = prob<true>(s, sl2, l[u]);
+                TL::axpy(adk, in[u] ? tau * p * (dP - dl[u]) : 0.f, x[u]);
+                TL::axpy(adv, in[u] ? p : 0.f, y[u]);
+            }
+        }
+        // a rung's two queries: i0 has the key as row r0, i0 + 1 as row r1
+        for (int r = 0; r < nact; ++r) {
+            const int d0 = rt.d0[r];
+            const float w = rt.w[r];
+            Slice x[2], y[2];
+            float l[2], dl[2];
+            bool in[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                in[u] = j + d0 + u < T && (w == 0.f ? u == 0 : u || j >= 1);
+                if (u && w == 0.f) break;
+                const int row = in[u] ? j + d0 + u : jc;
+                x[u] = TL::load(Q, row, g, sq);
+                y[u] = TL::load(G, row, g, sg);
+                l[u] = Le[row];
+                dl[u] = De[row];
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (u && w == 0.f) break;
+                const float wt = u ? w : 1.f - w;
+                float s = wt * dots(x[u], kj), dP = wt * dots(y[u], vj);
+                if (w != 0.f) {
+                    s = fmaf(1.f - wt, dots(x[u], u ? ka : kb), s);
+                    dP = fmaf(1.f - wt, dots(y[u], u ? va : vb), dP);
+                }
+                const float p = prob<true>(sum(s), sl2, l[u]);
+                TL::axpy(adk, in[u] ? tau * p * (sum(dP) - dl[u]) * wt : 0.f, x[u]);
+                TL::axpy(adv, in[u] ? p * wt : 0.f, y[u]);
+            }
+        }
+    }
+    // as in the forward: queries that do not read the key took part with weights of 0
+    if (__builtin_amdgcn_ballot_w64(!(TL::finite(adk) && TL::finite(adv)))) {
+        TL::zero(adk);
+        TL::zero(adv);
+        for (int hg = 0; hg < hd.G; ++hg) {
+            const int bh = hd.q_of(bk, hg);
+            dkdv_by_entry<TL>(q + lay.q.head(bh, hd.H), dO + lay.g.head(bh, hd.H), K, V, lse + (size_t)bh * T,
+                              delta_in + (size_t)bh * T, sq, sg, sk, sv, jc, g, T, W, rt, nact, tau, sl2, adk, adv);
+        }
+    }
+    if (rf.on) TL::rope_t(adk, j, sfreq, g);  // gradient w.r.t. the unrotated k
+    if (j < T) {
+        const float sc = DEV && table_unusable(rt, W) ? NAN : 1.f;  // bad device alpha, or another W
+        TL::store(dk + lay.dk.head(bk, hd.kv_heads()) + j * lay.dk.st, g, adk, sc);
+        TL::store(dv + lay.dv.head(bk, hd.kv_heads()) + j * lay.dv.st, g, adv, sc);
     }
 }
 
@@ -821,14 +959,31 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
     for (int r = 0; r < rt.n && !interp; ++r) interp = rt.w[r] != 0.f;
     hipError_t e;
     if constexpr (TL::kF32) {
-        const int tiles = (T + 63) / 64;
+        const bool wide = f32_wide(BH, T);
+        const int per = wide ? 1024 / D : 64, tiles = T / per + (T % per != 0);
         // the window's rows are staged where two workgroups still share a CU's LDS
         int rows = 64 + ((W + 15) & ~15);
-        if (2 * (size_t)rows * TL::kRow > 78 * 1024) rows = 0;
+        if (wide || 2 * (size_t)rows * TL::kRow > 78 * 1024) rows = 0;
         nb = tiles * BH;
-        e = launch(kBwdDq, rtp ? bwd_dq_f32_kernel<D, true> : bwd_dq_f32_kernel<D, false>, grid_of(nb), dim3(256),
-                   (unsigned)(2 * rows * TL::kRow), s, (const S *)q, (const S *)k, (const S *)v, (const S *)o, lse,
-                   (const S *)dO, (S *)dq, delta_ws, partials, T, W, rt, rtp, rf, tau, tiles, nb, rows, hd, lay);
+        auto dqk = wide ? (rtp ? bwd_dq_f32_kernel<D, D / 4, true> : bwd_dq_f32_kernel<D, D / 4, false>)
+                        : (rtp ? bwd_dq_f32_kernel<D, 4, true> : bwd_dq_f32_kernel<D, 4, false>);
+        e = launch(kBwdDq, dqk, grid_of(nb), dim3(256), (unsigned)(2 * rows * TL::kRow), s, (const S *)q,
+                   (const S *)k, (const S *)v, (const S *)o, lse, (const S *)dO, (S *)dq, delta_ws, partials, T, W, rt,
+                   rtp, rf, tau, tiles, nb, rows, hd, lay);
+        if (e != hipSuccess) return e;
+        // dk, dv of as few rows: one key per D / 4 lanes unless the tile kernel has the heads
+        // of a group side by side (d 128: at most two of them) or a long window of d 32 on
+        // the matrix cores.  Against the tile kernel at 4096 queries, W 3 to 16, d 32 / 64 /
+        // 128: groups of one 0.80 to 0.94 / 0.71 to 0.79 / 0.48 to 0.55 times, of three 0.75 /
+        // 0.61 / 0.37, of two 1.2 / 1.0 / 0.65 to 0.86, of four 1.8 / 1.5 / 0.62 to 0.75; d 32
+        // and W 64 1.1 to 1.2; at 16000 queries and W 64 1.1 to 1.3.
+        if (wide && (D == 128 || (ts.hs == 1 && (D == 64 || W <= 32)))) {
+            const int kper = 1024 / D, ktiles = T / kper + (T % kper != 0), kb = ktiles * (BH / hd.G);
+            return launch(kBwdDkDv, rtp ? bwd_dkdv_f32_kernel<D, true> : bwd_dkdv_f32_kernel<D, false>, grid_of(kb),
+                          dim3(256), 0, s, (const S *)q, (const S *)k, (const S *)v, lse, (const S *)dO, delta_ws,
+                          (S *)dk, (S *)dv, partials, nb, dalpha, dtheta, T, W, rt, rtp, rf, tau,
+                          kLog2e / sqrtf((float)D), ktiles, kb, hd, lay);
+        }
     } else {
         auto dqk = rtp ? bwd_dq_tile_kernel<S, D, true, true>
                        : interp ? bwd_dq_tile_kernel<S, D, true, false> : bwd_dq_tile_kernel<S, D, false, false>;

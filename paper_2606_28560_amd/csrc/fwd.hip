@@ -298,27 +298,28 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// float32: the same set on the VALU, four lanes per query, every sum in the order that
-// tile.h states.
+// float32: the same set on the VALU, L lanes per query, every sum in the order that tile.h
+// states, whatever L is.  Four lanes, or D / 4 of one 16-byte chunk each where 16 queries a
+// wave would leave the chip idle (f32_wide).
 // ---------------------------------------------------------------------------
-template <int D, bool DEV>
+template <int D, int L, bool DEV>
 __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
     const float *q, const float *__restrict__ k, const float *__restrict__ v, float *__restrict__ o,
     float *__restrict__ lse, int T, int W, RungTable rt_arg, const RungTable *__restrict__ rtp, float sl2, int tiles,
     int blocks, Heads hd, Layouts lay, float *qrot, RopeFreq rf) {
-    using TL = Tile<float, D>;
+    using TL = Tile<float, D, L>;
     using Slice = typename TL::Slice;
-    constexpr int NC = TL::NC;
+    constexpr int NC = TL::NC, RW = 64 / L, QPB = 4 * RW;  // queries per wave and workgroup
     const RungTable &rt = DEV ? *rtp : rt_arg;
     extern __shared__ __align__(16) char smem[];
     __shared__ double sfreq[D / 2];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int nq = lane >> 2, gq = lane & 3;  // quad layout
+    const int nq = lane / L, gq = lane % L;
     if (block_number() >= blocks) return;
     const int blk = xcd_remap(block_number(), blocks);
-    const int bh = blk / tiles, t0 = (blk % tiles) * 64 + 16 * wave;
+    const int bh = blk / tiles, t0 = (blk % tiles) * QPB + RW * wave;
     if (rf.on) {
         if (threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * TL::kRopeUnit;
         __syncthreads();
@@ -328,7 +329,7 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
     const float *K = k + lay.k.head(bk, hd.kv_heads());
     const float *V = v + lay.v.head(bk, hd.kv_heads());
     const uint32_t sk = (uint32_t)(4 * lay.k.st), sv = (uint32_t)(4 * lay.v.st);
-    const int i = t0 + nq, ic = min(i, T - 1), last = min(t0 + 15, T - 1);
+    const int i = t0 + nq, ic = min(i, T - 1), last = min(t0 + RW - 1, T - 1);
     Slice qq = TL::load(q + lay.q.head(bh, hd.H), ic, gq, (uint32_t)(4 * lay.q.st));
     if (rf.on) {  // as in the tile kernel
         TL::rope(qq, i, sfreq, gq);
@@ -340,13 +341,13 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
     nact = __builtin_amdgcn_readfirstlane(nact);
     const int nwin = (min(W, last) + 4) & ~3;  // window entries, in fours
     // the wave's logits, entry by entry (LDS accesses of one wave keep their order)
-    float *sc = reinterpret_cast<float *>(smem) + 16 * wave + nq;
+    float *sc = reinterpret_cast<float *>(smem) + RW * wave + nq;
 
     // logits and their maximum; an entry the query does not have reads its own row
     float m = -INFINITY;
     auto keep = [&](int e, bool in, float s) {
         s = in ? s * sl2 : -INFINITY;
-        if (gq == 0) sc[64 * e] = s;
+        if (gq == 0) sc[QPB * e] = s;
         m = fmaxf(m, s);
     };
     const int reach = min(W, ic);
@@ -355,7 +356,7 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
 #pragma unroll
         for (int y = 0; y < 4; ++y) x[y] = TL::load(K, d + y <= reach ? ic - d - y : ic, gq, sk);
 #pragma unroll
-        for (int y = 0; y < 4; ++y) keep(d + y, d + y <= reach, TL::quad_dot(qq, x[y]));
+        for (int y = 0; y < 4; ++y) keep(d + y, d + y <= reach, TL::row_dot(qq, x[y]));
     }
     // two rungs together (the second clamped to an active one and masked)
     for (int r = 0; r < nact; r += 2) {
@@ -380,7 +381,7 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
 #pragma unroll
                 for (int c = 0; c < NC; ++c) t[c] = fmaf(w[y], chunk_dot(qq.c[c], x1[y].c[c]), t[c]);
             }
-            keep(nwin + r + y, in[y], chunk_sum<NC>(t));
+            keep(nwin + r + y, in[y], chunk_sum<NC, L>(t));
         }
     }
     __builtin_amdgcn_wave_barrier();
@@ -392,7 +393,7 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
 #pragma unroll 4
     for (int d = 0; d < nwin; ++d) {
         const Slice x = TL::load(V, d <= reach ? ic - d : ic, gq, sv);
-        const float p = exp2f(sc[64 * d] - m);
+        const float p = exp2f(sc[QPB * d] - m);
         l += p;
         TL::axpy(acc, p, x);
     }
@@ -403,7 +404,7 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
         const bool in = ic >= d0 + (w != 0.f);
         const int r0 = in ? ic - d0 : ic;
         const Slice x = TL::load(V, r0, gq, sv);
-        const float p = exp2f(sc[64 * (nwin + r)] - m);
+        const float p = exp2f(sc[QPB * (nwin + r)] - m);
         l += p;
         TL::axpy(acc, p * (1.f - w), x);
         if (w != 0.f) TL::axpy(acc, p * w, TL::load(V, in ? r0 - 1 : r0, gq, sv));
@@ -411,10 +412,10 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
     if (__builtin_amdgcn_ballot_w64(!TL::finite(acc))) {  // as in the tile kernel: 0 times its own row
         TL::zero(acc);
         for (int d = 0; d < nwin; ++d)
-            if (d <= reach) TL::axpy(acc, exp2f(sc[64 * d] - m), TL::load(V, ic - d, gq, sv));
+            if (d <= reach) TL::axpy(acc, exp2f(sc[QPB * d] - m), TL::load(V, ic - d, gq, sv));
         for (int r = 0; r < nact; ++r) {
             const int d0 = rt.d0[r];
-            const float w = rt.w[r], p = exp2f(sc[64 * (nwin + r)] - m);
+            const float w = rt.w[r], p = exp2f(sc[QPB * (nwin + r)] - m);
             if (ic >= d0 + (w != 0.f)) {
                 TL::axpy(acc, p * (1.f - w), TL::load(V, ic - d0, gq, sv));
                 if (w != 0.f) TL::axpy(acc, p * w, TL::load(V, ic - d0 - 1, gq, sv));
@@ -428,15 +429,24 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(
     }
 }
 
-template <int D>
-static hipError_t launch_fwd_f32(const void *q, const void *k, const void *v, void *o, float *lse, int BH,
+template <int D, int L>
+static hipError_t launch_fwd_f32_lanes(const void *q, const void *k, const void *v, void *o, float *lse, int BH,
                                  const Heads &hd, int T, int W, const RungTable &rt, const RungTable *rtp,
                                  const Layouts &lay, hipStream_t s, const RopeFreq &rf, void *q_rot) {
-    const int tiles = (T + 63) / 64;
-    const size_t lds = 64 * sizeof(float) * (size_t)(W + 4 + (rtp ? kMaxRungs : rt.n + 1));
-    return launch(kForward, rtp ? fwd_f32_kernel<D, true> : fwd_f32_kernel<D, false>, grid_of((long long)tiles * BH), dim3(256),
-                  (unsigned)lds, s, (const float *)q, (const float *)k, (const float *)v, (float *)o, lse, T, W, rt,
-                  rtp, kLog2e / sqrtf((float)D), tiles, tiles * BH, hd, lay, (float *)q_rot, rf);
+    constexpr int QPB = 256 / L;
+    const int tiles = T / QPB + (T % QPB != 0);
+    const size_t lds = QPB * sizeof(float) * (size_t)(W + 4 + (rtp ? kMaxRungs : rt.n + 1));
+    return launch(kForward, rtp ? fwd_f32_kernel<D, L, true> : fwd_f32_kernel<D, L, false>,
+                  grid_of((long long)tiles * BH), dim3(256), (unsigned)lds, s, (const float *)q, (const float *)k,
+                  (const float *)v, (float *)o, lse, T, W, rt, rtp, kLog2e / sqrtf((float)D), tiles, tiles * BH, hd,
+                  lay, (float *)q_rot, rf);
+}
+
+template <int D, typename... A>
+static hipError_t launch_fwd_f32(const void *q, const void *k, const void *v, void *o, float *lse, int BH,
+                                 const Heads &hd, int T, A... a) {
+    return f32_wide(BH, T) ? launch_fwd_f32_lanes<D, D / 4>(q, k, v, o, lse, BH, hd, T, a...)
+                                        : launch_fwd_f32_lanes<D, 4>(q, k, v, o, lse, BH, hd, T, a...);
 }
 
 // Query heads side by side in a workgroup of nw waves, for G heads per key/value head:

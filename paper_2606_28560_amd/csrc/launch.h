@@ -52,6 +52,14 @@ hipError_t launch_forward(int dtype, int D, const void *q, const void *k, const 
 int tile_heads(int G, int nw);
 int tile_chunks(int nc, size_t fixed, size_t per, int slice_pieces);
 
+// float32 forward and dq: D / 4 lanes per query in the place of 4 up to 12288 queries, where
+// 4 lanes make at most 768 waves for the 1024 SIMDs and a launch is the latency of one
+// wave's chain of rows.  Measured against 4 lanes over batches of 128 to 65536 queries, d 32
+// / 64 / 128, W 3 to 64: forward at 4096 queries 0.92 to 0.99 / 0.73 to 0.87 / 0.47 to 0.72
+// times, at 12000 0.97 to 1.02 / 0.94 to 0.98 / 0.84 to 1.03, at 16000 0.97 to 1.02 / 1.05 to
+// 1.11 / 1.03 to 1.20; dq the same within 0.1.
+inline bool f32_wide(int BH, int T) { return (long long)BH * T <= 12288; }
+
 // dalpha partials the workspace holds: at least one per workgroup of the dq kernel.
 size_t bwd_num_partials(int dtype, int D, int BH, int T);
 

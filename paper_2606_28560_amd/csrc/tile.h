@@ -35,23 +35,37 @@ __device__ __forceinline__ float chunk_dot(const u32x4 &x, const u32x4 &y) {
     for (int e = 0; e < 4; ++e) s = fmaf(__uint_as_float(x[e]), __uint_as_float(y[e]), s);
     return s;
 }
-// Sum of a row's chunk values, this lane's at positions 4x + g; quad layout.
-template <int NC>
+// A value of lane l ^ M (M < 64, a power of two).
+template <int M>
+__device__ __forceinline__ float lane_xor(float x) {
+    const int i = __float_as_int(x);
+    if constexpr (M == 1) return __int_as_float(__builtin_amdgcn_update_dpp(0, i, 0xB1, 0xF, 0xF, true));
+    if constexpr (M == 2) return __int_as_float(__builtin_amdgcn_update_dpp(0, i, 0x4E, 0xF, 0xF, true));
+    if constexpr (M == 8) return __int_as_float(__builtin_amdgcn_update_dpp(0, i, 0x128, 0xF, 0xF, true));  // row_ror:8
+    return __shfl_xor(x, M, 64);
+}
+// Sum of a row's chunk values, this lane's at positions L x + g of the row's L lanes.
+template <int NC, int L = 4>
 __device__ __forceinline__ float chunk_sum(float *t) {
 #pragma unroll
     for (int h = NC / 2; h >= 1; h >>= 1)
 #pragma unroll
         for (int x = 0; x < h; ++x) t[x] += t[x + h];
     float s = t[0];
-    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x4E, 0xF, 0xF, true));
-    s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0xB1, 0xF, 0xF, true));
+    if constexpr (L > 16) s += lane_xor<16>(s);
+    if constexpr (L > 8) s += lane_xor<8>(s);
+    if constexpr (L > 4) s += lane_xor<4>(s);
+    s += lane_xor<2>(s);
+    s += lane_xor<1>(s);
     return s;
 }
-template <typename S, int D>
+// L: lanes per row in the quad layout, 4 (neighbouring lanes L n + g), or D / 4 for float32
+// rows of one 16-byte chunk a lane, which take the VALU functions alone.
+template <typename S, int D, int L = 4>
 struct Tile {
     static constexpr int kRow = D * (int)sizeof(S);  // bytes of a row
-    static constexpr int NC = kRow / 64;             // 16-byte pieces of a slice
-    static constexpr int NB = D / 16;                // accumulator blocks of a slice
+    static constexpr int NC = kRow / (16 * L);       // 16-byte pieces of a slice
+    static constexpr int NB = D / (4 * L);           // accumulator blocks of a slice
     static constexpr bool kF32 = sizeof(S) == 4;
 
     struct Slice {
@@ -86,7 +100,7 @@ struct Tile {
         const uint32_t off = (uint32_t)row * st + (uint32_t)g * 16u;
         Slice s;
 #pragma unroll
-        for (int x = 0; x < NC; ++x) s.c[x] = *reinterpret_cast<const u32x4 *>(p + off + 64 * x);
+        for (int x = 0; x < NC; ++x) s.c[x] = *reinterpret_cast<const u32x4 *>(p + off + 16 * L * x);
         return s;
     }
     // The lane's slice of an output row: a.c times `scale`, rounded to S.
@@ -104,7 +118,7 @@ struct Tile {
                     v[w] = pack_bf16(h[2 * (w & 1)] * scale, h[2 * (w & 1) + 1] * scale);
                 }
             }
-            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(p + 64 * x));
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(p + 16 * L * x));
         }
     }
 
@@ -124,13 +138,13 @@ struct Tile {
         return (s[0] + s[1]) + (s[2] + s[3]);
     }
 
-    // The same over the four lanes of a quad; float32 rows in the fixed order above.
-    __device__ static __forceinline__ float quad_dot(const Slice &x, const Slice &y) {
+    // The same over the row's lanes; float32 rows in the fixed order above.
+    __device__ static __forceinline__ float row_dot(const Slice &x, const Slice &y) {
         if constexpr (kF32) {
             float t[NC];
 #pragma unroll
             for (int c = 0; c < NC; ++c) t[c] = chunk_dot(x.c[c], y.c[c]);
-            return chunk_sum<NC>(t);
+            return chunk_sum<NC, L>(t);
         } else {
             return quad_sum(dot(x, y));
         }
@@ -324,13 +338,22 @@ struct Tile {
     // RoPE of the lane's slice of a row at position t, with the angles, the order of the
     // products and the rounding of the RoPE launch: its bits.  Partners as in rope_t.
     __device__ static __forceinline__ void rope(Slice &x, int t, const double *sf, int g) {
-        if constexpr (kF32) {
+        if constexpr (NC == 1 && kF32) {
+            const bool hi = g >= L / 2;  // this lane holds the second halves of its pairs
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float c, s;
+                rope_cs_f64(t, sf[4 * (g & (L / 2 - 1)) + e], c, s);
+                const float u = __uint_as_float(x.c[0][e]), o = lane_xor<L / 2>(u);
+                x.c[0][e] = __float_as_uint(hi ? fmaf(s, o, c * u) : fmaf(c, u, -(s * o)));
+            }
+        } else if constexpr (kF32) {
 #pragma unroll
             for (int a = 0; a < NC / 2; ++a)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float c, s, u, w;
-                    rope_cs_f64(t, sf[16 * a + 4 * g + e], c, s);
+                    rope_cs_f64(t, sf[4 * (L * a + g) + e], c, s);
                     u = __uint_as_float(x.c[a][e]);
                     w = __uint_as_float(x.c[a + NC / 2][e]);
                     x.c[a][e] = __float_as_uint(fmaf(c, u, -(s * w)));
@@ -380,7 +403,7 @@ struct Tile {
     // The lane's slice written to a row (read again by the backward: ordinary stores).
     __device__ static __forceinline__ void put(void *row, int g, const Slice &x) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(row) + 16 * g + 64 * c) = x.c[c];
+        for (int c = 0; c < NC; ++c) *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(row) + 16 * g + 16 * L * c) = x.c[c];
     }
 
     // R^T (the inverse RoPE rotation) of the lane's slice at position t.  float32: the RoPE
@@ -391,7 +414,16 @@ struct Tile {
     // every frequency.  The partner of dim d < D/2 is d + D/2: D/8 slice
     // positions on, except for bfloat16 rows of 32, whose partner lanes are g and g + 2.
     __device__ static __forceinline__ void rope_t(Acc &a, int t, const double *sf, int g) {
-        if constexpr (!kF32 && D == 32) {
+        if constexpr (NC == 1 && kF32) {
+            const bool hi = g >= L / 2;  // this lane holds the second halves of its pairs
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float c, s;
+                rope_cs_f64(t, sf[4 * (g & (L / 2 - 1)) + e], c, s);
+                const float x = a.c[0][e], o = lane_xor<L / 2>(x);
+                a.c[0][e] = hi ? fmaf(-s, o, c * x) : fmaf(c, x, s * o);
+            }
+        } else if constexpr (!kF32 && D == 32) {
             const bool hi = g & 2;  // this lane holds the second halves of its pairs
 #pragma unroll
             for (int p = 0; p < 8; ++p) {
@@ -408,7 +440,7 @@ struct Tile {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int p = 4 * b + e;
-                    const int dim = kF32 ? 16 * b + 4 * g + e : 32 * (p >> 3) + 8 * g + (p & 7);
+                    const int dim = kF32 ? 4 * (L * b + g) + e : 32 * (p >> 3) + 8 * g + (p & 7);
                     float c, s;
                     const float x = a.c[b][e], y = a.c[HB + b][e];
                     if constexpr (kF32) {

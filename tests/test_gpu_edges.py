@@ -147,8 +147,8 @@ SHAPES = [
     (2, 2, 130, 32, "bf16", 3, FIB, 1.0),
     (2, 1, 130, 64, "fp32", 9, FIB, 0.9),
     (1, 1, 130, 128, "fp32", 40, FIB, 1.0),
-    (64, 64, 130, 32, "fp32", 8, FIB, 1.2),
-    (64, 64, 130, 64, "fp32", 40, FIB, 1.0),
+    (100, 100, 130, 32, "fp32", 8, FIB, 1.2),
+    (100, 100, 130, 64, "fp32", 40, FIB, 1.0),
 ]
 
 

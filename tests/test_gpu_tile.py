@@ -131,3 +131,37 @@ def test_float32_rotated_q_has_the_bits_of_the_rope_launch(B, H, T, D):
     want_o, want_lse = F.fibattn_forward(Q, K, v, 12, FIB, 0.9)
     torch.cuda.synchronize()
     assert torch.equal(got, Q) and torch.equal(o, want_o) and torch.equal(lse, want_lse)
+
+
+@pytest.mark.parametrize("G,T,D,W,base,alpha", [
+    (1, 15, 32, 8, FIB, 0.9), (2, 64, 32, 40, FIB, 1.0), (1, 129, 32, 16, POW2, 1.2), (3, 17, 32, 0, FIB, 0.8),
+    (1, 16, 64, 17, FIB, 1.0), (3, 65, 64, 12, FIB, 0.9), (2, 130, 64, 8, POW2, 0.8), (1, 100, 64, 128, FIB, 1.0),
+    (1, 33, 128, 8, FIB, 0.9), (4, 63, 128, 16, FIB, 1.0), (2, 200, 128, 40, FIB, 1.1), (1, 1, 128, 3, FIB, 1.0)])
+def test_float32_lanes(G, T, D, W, base, alpha):
+    # float32 of few rows (D / 4 lanes a row) and of many (4 lanes): heads of the large call that
+    # hold the same rows as the small one's have the same bits of o, lse and dq (rotated back),
+    # from a host and from a device table, and dk, dv within the parity bound
+    n = 12288 // (2 * G * T) + 1  # the small call n times over is past the line
+    assert 2 * G * T <= 12288 < 2 * G * T * n
+    x = inputs.attention_inputs(1, 2 * G, T, D, "fp32", 890, 0, names=("q", "dO"))
+    x.update(inputs.attention_inputs(1, 2, T, D, "fp32", 890, 0, names=("k", "v")))
+    table = F.fibattn_device_table(torch.tensor([alpha], device="cuda"), base, W)
+    res = []
+    for r in (1, n):
+        q, k, v, dO = (x[m].cuda().repeat(r, 1, 1, 1) for m in ("q", "k", "v", "dO"))
+        o, lse, Q = F.fibattn_forward_rope_q(q, k, v, W, base, alpha)
+        od, ld = F.fibattn_forward_dt(Q, k, v, W, table)
+        g = F.fibattn_backward(Q, k, v, o, lse, dO, W, base, alpha, rope_base=10000.0)
+        gd = F.fibattn_backward_dt(Q, k, v, o, lse, dO, W, table, rope_base=10000.0)
+        torch.cuda.synchronize()
+        assert torch.equal(od, o) and torch.equal(ld, lse)
+        assert torch.equal(g[0], gd[0]) and torch.equal(g[3], gd[3])
+        for a, b in zip(g[1:3], gd[1:3]):  # (a device table has the interpolating order of rungs)
+            assert (a - b).abs().max() <= 1e-5 * max(1.0, float(a.abs().max()))
+        res.append((o, lse, Q, *g))
+    for name, a, b in zip(("o", "lse", "Q", "dq"), *res):
+        assert torch.equal(a.expand(n, *a.shape[1:]), b), name
+    for name, a, b in zip(("dk", "dv"), res[0][4:], res[1][4:]):
+        assert (a - b).abs().max() <= 1e-5 * max(1.0, float(a.abs().max())), name
+    # n times the same terms
+    assert abs(float(res[1][6]) - n * float(res[0][6])) <= 1e-5 * n * max(1.0, T * abs(float(res[0][6])))
