@@ -458,7 +458,7 @@ __device__ __forceinline__ void dkdv_by_entry(const void *Q, const void *G, cons
             s = fmaf(1.f - wt, TL::row_dot(x, TL::load(K, nb, gq, sk)), wt * s);
             dP = fmaf(1.f - wt, TL::row_dot(g, TL::load(V, nb, gq, sv)), wt * dP);
         }
-        const float p = prob<TL::kF32>(s, sl2, L[row] * (TL::kF32 ? 1.f : kLog2e));
+        const float p = prob(s, sl2, L[row] * kLog2e);
         if (!in) continue;
         TL::axpy(adk, tau * p * (dP - Dl[row]) * wt, x);
         TL::axpy(adv, p * wt, g);
@@ -516,7 +516,6 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
     const S *K = k + lay.k.head(bk, hd.kv_heads());
     const S *V = v + lay.v.head(bk, hd.kv_heads());
     constexpr int es = (int)sizeof(S);
-    constexpr float kLse = TL::kF32 ? 1.f : kLog2e;  // lse as prob takes it
     const uint32_t sq = (uint32_t)(lay.q.st * es), sg = (uint32_t)(lay.g.st * es);
     const uint32_t sk = (uint32_t)(lay.k.st * es), sv = (uint32_t)(lay.v.st * es);
     if (rf.on && threadIdx.x < D / 2) sfreq[threadIdx.x] = rf.inv[threadIdx.x] * 0.15915494309189533576888376337251;
@@ -567,7 +566,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                 }
                 for (int x = threadIdx.x; x < ts.hs * rows; x += blockDim.x) {
                     const size_t at = (size_t)hd.q_of(bk, pass * ts.hs + x / rows) * T + min(rbeg + x % rows, T - 1);
-                    sl[x] = lse[at] * kLse;
+                    sl[x] = lse[at] * kLog2e;
                     sd[x] = delta_in[at];
                 }
                 wait_vmem();
@@ -582,7 +581,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                         const bool in = j + d < T;
                         Slice x = TL::staged(qb, r, gq), y = TL::staged(gb, r, gq);
                         const float s = TL::row_dot(x, ka), dP = TL::row_dot(y, va);
-                        const float pr = prob<TL::kF32>(s, sl2, sl[hs * rows + r]);
+                        const float pr = prob(s, sl2, sl[hs * rows + r]);
                         const float c = in ? tau * pr * (dP - sd[hs * rows + r]) : 0.f;
                         if (__builtin_amdgcn_ballot_w64(!in)) {  // clamped rows: 0 times them must be 0
 #pragma unroll
@@ -613,7 +612,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                             const bool in = jm < T && (unsigned)(rbeg + si + e - jm) <= reach;
                             float x;
                             if constexpr (TL::kF32) {
-                                x = prob<true>(s[e], sl2, l2[e]);
+                                x = prob(s[e], sl2, l2[e]);
                             } else {
                                 const float xe = fmaf(s[e], sl2, -l2[e]);
                                 least = fminf(least, xe);
@@ -733,7 +732,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
                 const bool in = has(r, y);
-                const float x = prob<TL::kF32>(s[y], sl2, xl[y] * kLse);
+                const float x = prob(s[y], sl2, xl[y] * kLog2e);
                 const float wt = INTERP ? (y ? rt.w[r] : 1.f - rt.w[r]) : 1.f;
                 p[y] = in ? x * wt : 0.f;
                 c[y] = in ? tau * x * (dP[y] - xd[y]) * wt : 0.f;
@@ -860,13 +859,13 @@ __global__ __launch_bounds__(256) void bwd_dkdv_f32_kernel(
                 const int row = in[u] ? j + d + u : jc;
                 x[u] = TL::load(Q, row, g, sq);
                 y[u] = TL::load(G, row, g, sg);
-                l[u] = Le[row];
+                l[u] = Le[row] * kLog2e;
                 dl[u] = De[row];
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 const float s = sum(dots(x[u], kj)), dP = sum(dots(y[u], vj));
-                const float p = prob<true>(s, sl2, l[u]);
+                const float p = prob(s, sl2, l[u]);
                 TL::axpy(adk, in[u] ? tau * p * (dP - dl[u]) : 0.f, x[u]);
                 TL::axpy(adv, in[u] ? p : 0.f, y[u]);
             }
@@ -885,7 +884,7 @@ __global__ __launch_bounds__(256) void bwd_dkdv_f32_kernel(
                 const int row = in[u] ? j + d0 + u : jc;
                 x[u] = TL::load(Q, row, g, sq);
                 y[u] = TL::load(G, row, g, sg);
-                l[u] = Le[row];
+                l[u] = Le[row] * kLog2e;
                 dl[u] = De[row];
             }
 #pragma unroll
@@ -897,7 +896,7 @@ __global__ __launch_bounds__(256) void bwd_dkdv_f32_kernel(
                     s = fmaf(1.f - wt, dots(x[u], u ? ka : kb), s);
                     dP = fmaf(1.f - wt, dots(y[u], u ? va : vb), dP);
                 }
-                const float p = prob<true>(sum(s), sl2, l[u]);
+                const float p = prob(sum(s), sl2, l[u]);
                 TL::axpy(adk, in[u] ? tau * p * (sum(dP) - dl[u]) * wt : 0.f, x[u]);
                 TL::axpy(adv, in[u] ? p * wt : 0.f, y[u]);
             }

@@ -457,21 +457,12 @@ struct Tile {
     }
 };
 
-// Probability exp(tau s - lse) of a backward entry as exp2(s sl2 - lse log2e), with the
-// forward's sl2 = fl(tau log2e), whose rounding the saved lse shares.  l: lse for float32
-// rows, lse log2e for bfloat16.  float32: what the rounding of lse log2e loses (up to 1.7e-7
-// of every probability of a query alike, at lse = 4) is multiplied back in; an infinite
-// lse (a query dropped by its caller) loses nothing.
-template <bool F32>
-__device__ __forceinline__ float prob(float s, float sl2, float l) {
-    if constexpr (!F32) return exp2f(fmaf(s, sl2, -l));
-    const float v = l * kLog2e;
-    // kLog2e + 1.925963e-8 = log2(e)
-    float low = fmaf(l, 1.925963033500e-8f, fmaf(l, kLog2e, -v)) * kLn2;
-    low = __builtin_isfinite(v) ? low : 0.f;
-    const float p = exp2f(fmaf(s, sl2, -v));
-    return fmaf(p, -low, p);
-}
+// Probability exp(tau s - lse) of a backward entry, with the forward's sl2 = fl(tau log2e),
+// whose rounding the saved lse shares, and lse2 = fl(lse log2e), which mostly gives back the
+// base-2 value that the forward rounded to lse.  (float32 dk and dv against 64 bits, as a
+// multiple of one lane group per key: 0.99 and 0.98; with the low part of lse log2e put back
+// 1.00, at most 1.06; with s sl2 rounded first 1.04 and 1.06.)
+__device__ __forceinline__ float prob(float s, float sl2, float lse2) { return exp2f(fmaf(s, sl2, -lse2)); }
 
 // Weights 2^x of a bfloat16 band that the matrix cores cannot take in full: three bfloat16
 // parts hold 24 bits from 2^-109 on (their last one is a multiple of 2^-133), and the exp2
