@@ -129,7 +129,7 @@ def _base_array(base):
             return b, (ctypes.c_int32 * len(b)).from_buffer(b)
         except (TypeError, OverflowError):
             pass  # not plain integers of 32 bits: numpy converts them or raises
-    b = array("i", np.asarray(list(base), dtype=np.int32).tolist())
+    b = array("i", np.asarray(list(base), dtype=np.int32).ravel().tolist())
     return b, (ctypes.c_int32 * len(b)).from_buffer(b)
 
 

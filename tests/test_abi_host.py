@@ -236,3 +236,11 @@ def test_noalloc_backward_refuses_problems_beyond_its_scratch_without_gpu():
     # bad sizes are refused as by the other entry points
     assert L.fibattn_backward_noalloc(*([16] * 10), 0, 8, 8, 1024, 64, 8, b, 15, one, zero, 1, None) == 1
     assert L.fibattn_backward_noalloc(*([16] * 10), 1, 8, 3, 1024, 64, 8, b, 15, one, zero, 1, None) == 1
+
+
+@pytest.mark.parametrize("base", [
+    (1, 2, 3, 5), [[1, 2], [3, 5]], np.array([[1, 2], [3, 5]], dtype=np.int64), [np.array([1]), np.array([2]), [3], [5]],
+    [1.0, 2.9, 3.0, "5"], iter([1, 2, 3, 5]), np.array([1.5, 2.5, 3.5, 5.5])])
+def test_base_of_any_form_numpy_converts(base):
+    # plain integers take a shorter way than everything else, with the same result
+    assert [f for _, _, f in F.fibattn_rung_table(1.0, base, 0)] == [1, 2, 3, 5]
