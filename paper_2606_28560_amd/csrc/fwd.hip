@@ -457,10 +457,11 @@ int tile_heads(int G, int nw) {
     return 1;
 }
 
-// Chunks staged at a time: as many as keep `fixed` + `per` bytes a chunk within the LDS of
-// a workgroup when four (slices of up to 32 bytes) or three workgroups share a CU.
+// Chunks staged at a time: as many as keep `fixed` + `per` bytes a chunk, next to a kernel's
+// static LDS (frequencies and sums, under 1 KB), within the LDS of a workgroup when four
+// (slices of up to 32 bytes) or three workgroups share a CU.
 int tile_chunks(int nc, size_t fixed, size_t per, int slice_pieces) {
-    const size_t budget = slice_pieces <= 2 ? 40 * 1024 : 53 * 1024;
+    const size_t budget = slice_pieces <= 2 ? 39 * 1024 : 52 * 1024;
     int c = 1;
     while (c < nc && fixed + (size_t)(c + 1) * per <= budget) ++c;
     return c;
