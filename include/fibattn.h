@@ -371,7 +371,8 @@ const char *fibattn_status_string(fibattn_status_t status);
  * `capacity` launches of kernel `id` made by the calling thread with a HIP event
  * pair that takes the dispatch's
  * own start and end timestamps on the launch stream (0 rope, 1 forward, 2 backward
- * dq+dalpha, 3 backward dk/dv, 4 dalpha reduce, 5 device-alpha kernels).
+ * dq+dalpha, 3 backward dk/dv, which also sums dalpha, 4 unused: no launch has it, 5
+ * device-alpha kernels).
  * fibattn_timing_end(&avg_ms, &count) synchronises on the last event, returns
  * the mean launch duration and the number of launches timed, and stops timing.
  */

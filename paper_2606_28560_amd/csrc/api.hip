@@ -205,7 +205,7 @@ static fibattn_status_t forward_rope_q_impl(const void *q, const void *k, const 
     if (!(rope_base > 1.f) || !isfinite(rope_base)) return FIBATTN_ERR_INVALID_ARG;
     // the rotated rows need a home, except on the path that keeps none for the backward
     const bool no_copy = forward_mfma_supported((int)dtype, d_head, W);
-    if (!no_copy && (!q_out || (long long)B * H > 65535ll * 16)) return FIBATTN_ERR_UNSUPPORTED;
+    if (!no_copy && !q_out) return FIBATTN_ERR_UNSUPPORTED;
     // one launch: each query row is rotated where the forward loads it
     const RopeFreq rf = make_rope_freq((double)rope_base, d_head);
     const hipError_t e = launch_forward((int)dtype, d_head, q, k, v, o, lse, B * H, Heads{H, H / H_kv}, T, W, rt, rtp,
@@ -484,9 +484,7 @@ fibattn_status_t fibattn_rope(const void *x, void *y, int B, int H, int T, int d
     if (!(rope_base > 1.f) || !isfinite(rope_base)) return FIBATTN_ERR_INVALID_ARG;
     if (d_head != 32 && d_head != 64 && d_head != 128) return FIBATTN_ERR_UNSUPPORTED;
     if ((long long)B * H > 65535ll * 16) return FIBATTN_ERR_UNSUPPORTED;
-    const Layout l = Layout::packed(H, T, d_head);
-    hipError_t e = launch_rope((int)dtype, d_head, x, y, l, l, nullptr, nullptr, l, l, B * H, H, T,
-                               rope_base, transpose, stream);
+    hipError_t e = launch_rope((int)dtype, d_head, x, y, nullptr, nullptr, B * H, 0, T, rope_base, transpose, stream);
     return e == hipSuccess ? FIBATTN_OK : FIBATTN_ERR_HIP;
 }
 
@@ -500,9 +498,7 @@ fibattn_status_t fibattn_rope_qk(const void *q, const void *k, void *q_out, void
     if (!(rope_base > 1.f) || !isfinite(rope_base)) return FIBATTN_ERR_INVALID_ARG;
     if (d_head != 32 && d_head != 64 && d_head != 128) return FIBATTN_ERR_UNSUPPORTED;
     if ((long long)B * H > 65535ll * 16) return FIBATTN_ERR_UNSUPPORTED;
-    const Layout l = Layout::packed(H, T, d_head);
-    hipError_t e = launch_rope((int)dtype, d_head, q, q_out, l, l, k, k_out, l, l, B * H, H, T, rope_base,
-                               0, stream);
+    hipError_t e = launch_rope((int)dtype, d_head, q, q_out, k, k_out, B * H, B * H, T, rope_base, 0, stream);
     return e == hipSuccess ? FIBATTN_OK : FIBATTN_ERR_HIP;
 }
 
@@ -529,11 +525,10 @@ fibattn_status_t fibattn_rope_qk_table(const void *q, const void *k, void *q_out
         job.out = (RungTable *)table;
         job.W = W;
     }
-    const Layout lq = Layout::packed(H, T, d_head), lk = Layout::packed(H_kv, T, d_head);
-    hipError_t e = q ? launch_rope((int)dtype, d_head, q, q_out, lq, lq, k, k_out, lk, lk, B * H, H, T, rope_base,
-                                   0, stream, B * H_kv, H_kv, theta ? &job : nullptr)
-                     : launch_rope((int)dtype, d_head, k, k_out, lk, lk, nullptr, nullptr, lk, lk, B * H_kv, H_kv, T,
-                                   rope_base, 0, stream, 0, 0, theta ? &job : nullptr);
+    const TableJob *tj = theta ? &job : nullptr;
+    hipError_t e = q ? launch_rope((int)dtype, d_head, q, q_out, k, k_out, B * H, B * H_kv, T, rope_base, 0, stream, tj)
+                     : launch_rope((int)dtype, d_head, k, k_out, nullptr, nullptr, B * H_kv, 0, T, rope_base, 0, stream,
+                                   tj);
     return e == hipSuccess ? FIBATTN_OK : FIBATTN_ERR_HIP;
 }
 

@@ -82,17 +82,18 @@ __device__ __forceinline__ void dq_by_entry(const typename TL::Slice &qq, const 
     }
 }
 
-template <typename S, int D>
-constexpr int dq_waves = Tile<S, D>::NC <= 2 ? 4 : Tile<S, D>::NC == 4 ? 3 : 2;
+template <int D>
+constexpr int dq_waves = D <= 64 ? 4 : 3;
 
 // DEV: the rung table is the one at rtp, built on the device (rt_arg unused).
-template <typename S, int D, bool INTERP, bool DEV>
-__global__ __launch_bounds__(256, (dq_waves<S, D>)) void bwd_dq_tile_kernel(
-    const S *__restrict__ q, const S *__restrict__ k, const S *__restrict__ v,
-    const S *__restrict__ o, const float *__restrict__ lse, const S *__restrict__ dO,
-    S *__restrict__ dq, float *__restrict__ delta_out, double *__restrict__ partials, int T,
+template <int D, bool INTERP, bool DEV>
+__global__ __launch_bounds__(256, (dq_waves<D>)) void bwd_dq_tile_kernel(
+    const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
+    const uint16_t *__restrict__ o, const float *__restrict__ lse, const uint16_t *__restrict__ dO,
+    uint16_t *__restrict__ dq, float *__restrict__ delta_out, double *__restrict__ partials, int T,
     int W, RungTable rt_arg, const RungTable *__restrict__ rtp, RopeFreq rf, float tau, float sl2, TileShape ts, Heads hd,
     Layouts lay) {
+    using S = uint16_t;
     using TL = Tile<S, D>;
     using Slice = typename TL::Slice;
     const RungTable &rt = DEV ? *rtp : rt_arg;
@@ -943,7 +944,7 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
                                const Heads &hd, int T, int W, const RungTable &rt,
                                const RungTable *rtp, const RopeFreq &rf, const Layouts &lay, hipStream_t s) {
     using TL = Tile<S, D>;
-    constexpr int nw = TL::kRow == 512 ? 2 : 4;  // as the forward
+    constexpr int nw = TL::kRow == 512 ? 2 : 4;  // waves per workgroup (float32 d 128: its rows' LDS)
     const float tau = 1.f / sqrtf((float)D);
     TileShape ts;
     ts.hs = tile_heads(hd.G, nw);
@@ -984,8 +985,8 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
                           kLog2e / sqrtf((float)D), ktiles, kb, hd, lay);
         }
     } else {
-        auto dqk = rtp ? bwd_dq_tile_kernel<S, D, true, true>
-                       : interp ? bwd_dq_tile_kernel<S, D, true, false> : bwd_dq_tile_kernel<S, D, false, false>;
+        auto dqk = rtp ? bwd_dq_tile_kernel<D, true, true>
+                       : interp ? bwd_dq_tile_kernel<D, true, false> : bwd_dq_tile_kernel<D, false, false>;
         e = launch(kBwdDq, dqk, grid_of(nb), dim3(64 * nw), (unsigned)(fixed + per * ts.cps), s, (const S *)q,
                    (const S *)k, (const S *)v, (const S *)o, lse, (const S *)dO, (S *)dq, delta_ws, partials, T, W,
                    rt, rtp, rf, tau, kLog2e / sqrtf((float)D), ts, hd, lay);

@@ -33,8 +33,8 @@ constexpr float kFwdSlack = 8.f;  // log2 units a rung's logit may exceed the ru
 
 // Waves per SIMD the registers are budgeted for: a slice is NC 16-byte pieces, and a rung
 // holds four of them in flight (rows r0, r1 of K and V) next to q's slice and D / 4 sums.
-template <typename S, int D>
-constexpr int fwd_waves = Tile<S, D>::NC <= 2 ? 4 : Tile<S, D>::NC == 4 ? 3 : 2;
+template <int D>
+constexpr int fwd_waves = D <= 64 ? 4 : 3;
 
 // The softmax and the weighted values of query ic, its entries one by one and only those it
 // has, the maximum first (quad layout; nact rungs, the wave's).
@@ -75,11 +75,12 @@ __device__ __forceinline__ void forward_by_entry(const typename TL::Slice &qq, c
 // is used by one query only, so qrot may be q itself: no restrict on q) and written to qrot,
 // placed by lay.dq, for the backward: 3 to 5 us more here against 5 to 7 us for a launch of
 // its own.
-template <typename S, int D, bool INTERP, bool DEV>
-__global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
-    const S *q, const S *__restrict__ k, const S *__restrict__ v, S *__restrict__ o,
+template <int D, bool INTERP, bool DEV>
+__global__ __launch_bounds__(256, (fwd_waves<D>)) void fwd_tile_kernel(
+    const uint16_t *q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, uint16_t *__restrict__ o,
     float *__restrict__ lse, int T, int W, RungTable rt_arg, const RungTable *__restrict__ rtp, float sl2,
-    TileShape ts, Heads hd, Layouts lay, S *qrot, RopeFreq rf) {
+    TileShape ts, Heads hd, Layouts lay, uint16_t *qrot, RopeFreq rf) {
+    using S = uint16_t;
     using TL = Tile<S, D>;
     using Slice = typename TL::Slice;
     const RungTable &rt = DEV ? *rtp : rt_arg;
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
     };
     Slice kx[NBUF][2], vx[NBUF][2];
     // in flight during the band phase, as far as the registers go
-    if (TL::NC <= 4 && nact > 0) load_batch(0, K, sk, kx[0]);
+    if (nact > 0) load_batch(0, K, sk, kx[0]);
     if (TL::NC <= 2 && nact > 0) load_batch(0, V, sv, vx[0]);
 
     // ---- window band (MFMA layout) ----
@@ -174,7 +175,7 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
             float p[8], mx = -INFINITY, least = INFINITY;
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
-                const f32x4 s = TL::template scores<TL::NC == 8 ? 8 : 4>(TL::staged(kr, base + 16 * b + nm, gm), qm);
+                const f32x4 s = TL::scores(TL::staged(kr, base + 16 * b + nm, gm), qm);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int key = rbeg + base + 16 * b + 4 * gm + e;
@@ -203,7 +204,6 @@ __global__ __launch_bounds__(256, (fwd_waves<S, D>)) void fwd_tile_kernel(
             TL::accumulate(acc, vr, base, TL::weights(p), gm);
         }
     }
-    if (TL::NC > 4 && nact > 0) load_batch(0, K, sk, kx[0]);
     if (TL::NC > 2 && nact > 0) load_batch(0, V, sv, vx[0]);
     l = sum4(l);
     // hand the band results to the quad layout
@@ -467,13 +467,14 @@ int tile_chunks(int nc, size_t fixed, size_t per, int slice_pieces) {
     return c;
 }
 
-template <typename S, int D>
-static hipError_t launch_fwd_t(const void *q, const void *k, const void *v, void *o, float *lse,
+template <int D>
+static hipError_t launch_fwd_tile(const void *q, const void *k, const void *v, void *o, float *lse,
                                int BH, const Heads &hd, int T, int W, const RungTable &rt,
                                const RungTable *rtp, const Layouts &lay, hipStream_t s, const RopeFreq &rf,
                                void *q_rot) {
+    using S = uint16_t;
     using TL = Tile<S, D>;
-    constexpr int nw = TL::kRow == 512 ? 2 : 4;  // rows of 512 bytes: 32 queries' band in 48 KB
+    constexpr int nw = 4;
     TileShape ts;
     ts.hs = tile_heads(hd.G, nw);
     const int runs = nw / ts.hs;
@@ -485,8 +486,8 @@ static hipError_t launch_fwd_t(const void *q, const void *k, const void *v, void
     bool interp = false;
     for (int r = 0; r < rt.n && !interp; ++r) interp = rt.w[r] != 0.f;
     const float sl2 = kLog2e / sqrtf((float)D);
-    auto kern = rtp ? fwd_tile_kernel<S, D, true, true>
-                    : interp ? fwd_tile_kernel<S, D, true, false> : fwd_tile_kernel<S, D, false, false>;
+    auto kern = rtp ? fwd_tile_kernel<D, true, true>
+                    : interp ? fwd_tile_kernel<D, true, false> : fwd_tile_kernel<D, false, false>;
     return launch(kForward, kern, grid_of(ts.blocks), dim3(64 * nw), (unsigned)(fixed + per * ts.cps), s,
                   (const S *)q, (const S *)k, (const S *)v, (S *)o, lse, T, W, rt, rtp, sl2, ts, hd, lay,
                   (S *)q_rot, rf);
@@ -501,10 +502,10 @@ hipError_t launch_forward(int dtype, int D, const void *q, const void *k, const 
     const RopeFreq rf = rq ? *rq : RopeFreq{};
     if (dtype == 0 && D == 32) return launch_fwd_f32<32>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
     if (dtype == 0 && D == 64) return launch_fwd_f32<64>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
-    if (dtype == 1 && D == 32) return launch_fwd_t<uint16_t, 32>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
-    if (dtype == 1 && D == 64) return launch_fwd_t<uint16_t, 64>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
+    if (dtype == 1 && D == 32) return launch_fwd_tile<32>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
+    if (dtype == 1 && D == 64) return launch_fwd_tile<64>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
     if (dtype == 0 && D == 128) return launch_fwd_f32<128>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
-    if (dtype == 1 && D == 128) return launch_fwd_t<uint16_t, 128>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
+    if (dtype == 1 && D == 128) return launch_fwd_tile<128>(q, k, v, o, lse, BH, hd, T, W, rt, rtp, lay, s, rf, q_rot);
     return hipErrorInvalidValue;
 }
 

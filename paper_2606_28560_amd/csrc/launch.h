@@ -9,8 +9,8 @@
 
 namespace fibattn {
 
-enum KernelId { kRope = 0, kForward = 1, kBwdDq = 2, kBwdDkDv = 3, kDalphaReduce = 4, kAlpha = 5,
-                kNumKernels = 6 };
+// 4: the dalpha sum, which the dk/dv launch carries
+enum KernelId { kRope = 0, kForward = 1, kBwdDq = 2, kBwdDkDv = 3, kAlpha = 5, kNumKernels = 6 };
 
 // The start/stop event pair for the next launch of kernel `id` while kernel timing is
 // active for it; false otherwise.
@@ -100,13 +100,9 @@ hipError_t launch_rung_table_theta(const float *theta, float *alpha_out, const B
 hipError_t launch_alpha_from_theta(const float *theta, float *alpha, int n, hipStream_t s);
 hipError_t launch_dtheta(const float *theta, const float *dalpha, float *dtheta, int n, hipStream_t s);
 
-// RoPE of one tensor (x1 == nullptr) or of two tensors in one launch: BH = batch * heads
-// rows of the first, BH1 rows of heads1 heads of the second (BH1 <= 0: same as the first);
-// inputs and outputs placed by their layouts.  A table job (may be null) is carried by
-// the first launch.
-hipError_t launch_rope(int dtype, int D, const void *x0, void *y0, const Layout &lx0, const Layout &ly0,
-                       const void *x1, void *y1, const Layout &lx1, const Layout &ly1, int BH, int heads,
-                       int T, float rope_base, int transpose, hipStream_t s, int BH1 = 0, int heads1 = 0,
-                       const TableJob *job = nullptr);
+// RoPE of one tensor (x1 == nullptr) or of two tensors in one launch: BH0 and BH1 rows
+// (batch * heads), packed.  A table job (may be null) is carried by the launch.
+hipError_t launch_rope(int dtype, int D, const void *x0, void *y0, const void *x1, void *y1, int BH0, int BH1, int T,
+                       float rope_base, int transpose, hipStream_t s, const TableJob *job = nullptr);
 
 }  // namespace fibattn

@@ -11,12 +11,8 @@
 
 namespace fibattn {
 
-// blockIdx.z selects the tensor: (x0 -> y0) or (x1 -> y1), each with its own row count
-// (batch * heads) and head count (k may have fewer heads than q) and placed by its io.
-struct RopeIO {
-    Layout x, y;
-    int BH, heads;
-};
+// blockIdx.z selects the tensor: (x0 -> y0) of BH0 rows (batch * heads) or (x1 -> y1) of BH1
+// (k may have fewer heads than q), each packed [BH, T, D].
 
 // Any storage type and head size (bfloat16 with d_head 64 has the kernel below): a lane
 // rotates the pairs of a 16-byte piece of the row's first half and the matching piece of
@@ -29,7 +25,7 @@ struct RopeIO {
 // B2 H16 T2000 20.2 -> 5.0; bf16 d 32 B8 H8 T1024 8.0 -> 4.9; fp32 d 64 B4 H8 T1024 11.4 -> 5.8.
 template <typename S, int D, int NP>
 __global__ __launch_bounds__(256) void rope_kernel(const S *x0, S *y0, const S *x1, S *y1, int T, RopeFreq rf,
-                                                   int transpose, RopeIO io0, RopeIO io1, TableJob job) {
+                                                   int transpose, int BH0, int BH1, TableJob job) {
     constexpr int HALF = D / 2, TP = 256 / HALF, VN = Vec<S>::N;
     constexpr int LPR = HALF / VN;              // lanes per row
     constexpr int HR = 256 / (LPR * TP);        // heads per pass
@@ -38,16 +34,16 @@ __global__ __launch_bounds__(256) void rope_kernel(const S *x0, S *y0, const S *
         table_from_theta(job.theta, job.alpha, job.b, job.W, job.out);
     const S *x = blockIdx.z ? x1 : x0;
     S *y = blockIdx.z ? y1 : y0;
-    const RopeIO &io = blockIdx.z ? io1 : io0;
+    const int BH = blockIdx.z ? BH1 : BH0;
     const int col = VN * (threadIdx.x % LPR), tt = threadIdx.x / LPR % TP, hh = threadIdx.x / (LPR * TP);
     // one pass each unless the grid had to be cut to its limits
     for (long long t0 = (long long)blockIdx.x * TP; t0 < T; t0 += (long long)gridDim.x * TP)
-        for (int b = blockIdx.y; b * HR * NP < io.BH; b += gridDim.y) {
+        for (int b = blockIdx.y; b * HR * NP < BH; b += gridDim.y) {
             const int t = (int)min(t0 + tt, (long long)T - 1), bh0 = b * HR * NP + hh;
             float u[NP][VN], w[NP][VN];
 #pragma unroll
             for (int n = 0; n < NP; ++n) {
-                const S *p = x + io.x.head(min(bh0 + n * HR, io.BH - 1), io.heads) + t * io.x.st + col;
+                const S *p = x + ((size_t)min(bh0 + n * HR, BH - 1) * T + t) * D + col;
                 Vec<S>::load(p, u[n]);
                 Vec<S>::load(p + HALF, w[n]);
             }
@@ -63,7 +59,7 @@ __global__ __launch_bounds__(256) void rope_kernel(const S *x0, S *y0, const S *
             if (t0 + tt >= T) continue;
 #pragma unroll
             for (int n = 0; n < NP; ++n) {
-                if (bh0 + n * HR >= io.BH) continue;
+                if (bh0 + n * HR >= BH) continue;
                 float ox[VN], oy[VN];
 #pragma unroll
                 for (int e = 0; e < VN; ++e) {
@@ -71,7 +67,7 @@ __global__ __launch_bounds__(256) void rope_kernel(const S *x0, S *y0, const S *
                     ox[e] = fmaf(c, u[n][e], -(s * w[n][e]));
                     oy[e] = fmaf(s, u[n][e], c * w[n][e]);
                 }
-                S *p = y + io.y.head(bh0 + n * HR, io.heads) + t * io.y.st + col;
+                S *p = y + ((size_t)(bh0 + n * HR) * T + t) * D + col;
                 Vec<S>::store(p, ox);
                 Vec<S>::store(p + HALF, oy);
             }
@@ -97,18 +93,16 @@ __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((rope_f32x2){lo, hi}, rope_bf16x2));
 }
 
-// STRIDED: rows placed by the io's layouts (else every tensor is packed [BH, T, 64]).
-template <bool STRIDED, int NP>
+template <int NP>
 __global__ __launch_bounds__(256) void rope_bf16_d64_kernel(const uint16_t *x0, uint16_t *y0,
                                                             const uint16_t *x1, uint16_t *y1,
                                                             int T, RopeFreq rf, int transpose,
-                                                            RopeIO io0, RopeIO io1, TableJob job) {
+                                                            int BH0, int BH1, TableJob job) {
     constexpr int kRope64TP = 4 * NP;  // positions per workgroup
     __shared__ float cs[kRope64TP * 32], sn[kRope64TP * 32];
     const uint16_t *x = blockIdx.z ? x1 : x0;
     uint16_t *y = blockIdx.z ? y1 : y0;
-    const RopeIO &io = blockIdx.z ? io1 : io0;
-    const int BH = io.BH, heads = io.heads;
+    const int BH = blockIdx.z ? BH1 : BH0;
     if (job.out && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0)
         table_from_theta(job.theta, job.alpha, job.b, job.W, job.out);
     if (blockIdx.y * kRope64RB >= BH) return;  // the tensor with fewer heads
@@ -123,9 +117,9 @@ __global__ __launch_bounds__(256) void rope_bf16_d64_kernel(const uint16_t *x0, 
 #pragma unroll
     for (int h = 0; h < NP; ++h) {  // positions t0 + (rr & 3) (and t0 + (rr & 3) + 4)
         const int tc = min(t0 + (rr & 3) + 4 * h, T - 1);
-        const size_t packed = ((size_t)bhc * T + tc) * 64;
-        xr[h] = x + (STRIDED ? io.x.head(bhc, heads) + (long long)tc * io.x.st : packed);
-        yr[h] = y + (STRIDED ? io.y.head(bhc, heads) + (long long)tc * io.y.st : packed);
+        const size_t row = ((size_t)bhc * T + tc) * 64;
+        xr[h] = x + row;
+        yr[h] = y + row;
         a[h] = *reinterpret_cast<const uint4 *>(xr[h] + 8 * g);
         b[h] = *reinterpret_cast<const uint4 *>(xr[h] + 32 + 8 * g);
     }
@@ -167,50 +161,34 @@ RopeFreq make_rope_freq(double rope_base, int D) {
 
 template <typename S, int D>
 static hipError_t launch_rope_t(const void *x0, void *y0, const void *x1, void *y1, int T, const RopeFreq &rf,
-                                int transpose, const RopeIO &io0, const RopeIO &io1, const TableJob &job,
+                                int transpose, int BH0, int BH1, const TableJob &job,
                                 hipStream_t s) {
     constexpr int TP = 512 / D, HR = 256 * Vec<S>::N / (D / 2 * TP);
-    const int rows = x1 ? std::max(io0.BH, io1.BH) : io0.BH, nt = T / TP + (T % TP != 0), z = x1 ? 2 : 1;
+    const int rows = x1 ? std::max(BH0, BH1) : BH0, nt = T / TP + (T % TP != 0), z = x1 ? 2 : 1;
     const int np = (long long)nt * ((rows + 2 * HR - 1) / (2 * HR)) * z >= 1024 ? 2 : 1;
     return launch(kRope, np == 2 ? rope_kernel<S, D, 2> : rope_kernel<S, D, 1>,
                   dim3(std::min(nt, 1 << 22), std::min((rows + np * HR - 1) / (np * HR), 65535), z), dim3(256), 0, s, (const S *)x0, (S *)y0,
-                  (const S *)x1, (S *)y1, T, rf, transpose, io0, io1, job);
+                  (const S *)x1, (S *)y1, T, rf, transpose, BH0, BH1, job);
 }
 
-// One launch for one tensor (x1 == nullptr) or two tensors (BH1 rows of heads1 heads for
-// the second); BH = batch * heads rows; each input and output placed by its layout.  The
-// table job (job.out set) rides on the first launch.
-hipError_t launch_rope(int dtype, int D, const void *x0, void *y0, const Layout &lx0, const Layout &ly0,
-                       const void *x1, void *y1, const Layout &lx1, const Layout &ly1, int BH, int heads,
-                       int T, float rope_base, int transpose, hipStream_t s, int BH1, int heads1,
-                       const TableJob *job) {
-    const double lb = (double)rope_base;
+// One launch for one tensor (x1 == nullptr) or two tensors of BH0 and BH1 rows (batch *
+// heads), packed.  The table job (job.out set) rides on it.
+hipError_t launch_rope(int dtype, int D, const void *x0, void *y0, const void *x1, void *y1, int BH0, int BH1, int T,
+                       float rope_base, int transpose, hipStream_t s, const TableJob *job) {
+    const RopeFreq rf = make_rope_freq((double)rope_base, D);
     TableJob nojob{};
     const TableJob &tj = job ? *job : nojob;
-    if (BH1 <= 0) { BH1 = BH; heads1 = heads; }
     if (dtype == 1 && D == 64) {
-        const RopeFreq rf = make_rope_freq(lb, 64);
-        auto same = [&](const Layout &l, int hs) {
-            const Layout p = Layout::packed(hs, T, 64);
-            return l.sb == p.sb && l.sh == p.sh && l.st == p.st;
-        };
-        const bool strided = !same(lx0, heads) || !same(ly0, heads) ||
-                             (x1 && (!same(lx1, heads1) || !same(ly1, heads1)));
-        const int rows = x1 ? max(BH, BH1) : BH;
-        const bool np2 = x1 || (long long)BH * T >= (1ll << 17);
+        const int rows = x1 ? std::max(BH0, BH1) : BH0;
+        const bool np2 = x1 || (long long)BH0 * T >= (1ll << 17);
         const int tp = np2 ? 8 : 4;  // positions per workgroup
-        auto kern = np2 ? (strided ? rope_bf16_d64_kernel<true, 2> : rope_bf16_d64_kernel<false, 2>)
-                        : (strided ? rope_bf16_d64_kernel<true, 1> : rope_bf16_d64_kernel<false, 1>);
-        return launch(kRope, kern,
-                      dim3((T + tp - 1) / tp, (rows + kRope64RB - 1) / kRope64RB, x1 ? 2 : 1),
-                      dim3(256), 0, s, x0, y0, x1, y1, T, rf, transpose, RopeIO{lx0, ly0, BH, heads},
-                      RopeIO{lx1, ly1, BH1, heads1}, tj);
+        return launch(kRope, np2 ? rope_bf16_d64_kernel<2> : rope_bf16_d64_kernel<1>,
+                      dim3((T + tp - 1) / tp, (rows + kRope64RB - 1) / kRope64RB, x1 ? 2 : 1), dim3(256), 0, s, x0,
+                      y0, x1, y1, T, rf, transpose, BH0, BH1, tj);
     }
-    const RopeFreq rf = make_rope_freq(lb, D);
-    const RopeIO io0{lx0, ly0, BH, heads}, io1{lx1, ly1, BH1, heads1};
 #define FIBATTN_ROPE(S, DD)                                                    \
     if ((dtype == 0) == (sizeof(S) == 4) && D == DD)                           \
-        return launch_rope_t<S, DD>(x0, y0, x1, y1, T, rf, transpose, io0, io1, tj, s);
+        return launch_rope_t<S, DD>(x0, y0, x1, y1, T, rf, transpose, BH0, BH1, tj, s);
     FIBATTN_ROPE(float, 32)
     FIBATTN_ROPE(float, 64)
     FIBATTN_ROPE(float, 128)
