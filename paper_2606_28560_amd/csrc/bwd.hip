@@ -257,13 +257,16 @@ __global__ __launch_bounds__(256, (dq_waves<D>)) void bwd_dq_tile_kernel(
             }
         }
     } else {
-        // one buffer each: the next rung's values load while this one's keys are used
+        // one buffer each: the next rung's values load while this one's keys are used (held
+        // there: loads moved across spill 2 to 24 registers at d 128)
         for (int r = 0; r < nact; ++r) {
             const int nx = min(r + 1, nact - 1);
             value_dots(r, vx[0]);
             load_rung(nx, V, sv, vx[0]);
+            __builtin_amdgcn_sched_barrier(0);
             key_terms(r, kx[0]);
             load_rung(nx, K, sk, kx[0]);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
     // as in the forward: entries the query does not have took part with weights of 0
