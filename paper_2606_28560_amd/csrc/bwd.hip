@@ -794,18 +794,18 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// dk, dv in float32 where 16 keys a wave would leave the chip idle (f32_wide): one key per
-// D / 4 lanes, the query heads of its group one after another.
+// dk, dv where 16 keys a wave would leave the chip idle: one key per lanes of one 16-byte
+// chunk each, the query heads of its group one after another.
 // ---------------------------------------------------------------------------
-template <int D, bool DEV>
-__global__ __launch_bounds__(256) void bwd_dkdv_f32_kernel(
-    const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
-    const float *__restrict__ lse, const float *__restrict__ dO, const float *__restrict__ delta_in,
-    float *__restrict__ dk, float *__restrict__ dv, const double *__restrict__ partials, int n_partials,
+template <typename S, int D, bool DEV>
+__global__ __launch_bounds__(256) void bwd_dkdv_rows_kernel(
+    const S *__restrict__ q, const S *__restrict__ k, const S *__restrict__ v,
+    const float *__restrict__ lse, const S *__restrict__ dO, const float *__restrict__ delta_in,
+    S *__restrict__ dk, S *__restrict__ dv, const double *__restrict__ partials, int n_partials,
     float *__restrict__ dalpha, float *__restrict__ dtheta, int T, int W, RungTable rt_arg,
     const RungTable *__restrict__ rtp, RopeFreq rf, float tau, float sl2, int tiles, int blocks, Heads hd, Layouts lay) {
-    constexpr int L = D / 4, RW = 64 / L;
-    using TL = Tile<float, D, L>;
+    constexpr int es = (int)sizeof(S), L = D * es / 16, RW = 64 / L;
+    using TL = Tile<S, D, L>;
     using Slice = typename TL::Slice;
     const RungTable &rt = DEV ? *rtp : rt_arg;
     __shared__ double sfreq[D / 2], red[256];
@@ -822,9 +822,9 @@ __global__ __launch_bounds__(256) void bwd_dkdv_f32_kernel(
     else if (rf.on)
         __syncthreads();
     if (t0 >= T) return;  // no barrier below
-    const float *K = k + lay.k.head(bk, hd.kv_heads()), *V = v + lay.v.head(bk, hd.kv_heads());
-    const uint32_t sq = (uint32_t)(4 * lay.q.st), sg = (uint32_t)(4 * lay.g.st);
-    const uint32_t sk = (uint32_t)(4 * lay.k.st), sv = (uint32_t)(4 * lay.v.st);
+    const S *K = k + lay.k.head(bk, hd.kv_heads()), *V = v + lay.v.head(bk, hd.kv_heads());
+    const uint32_t sq = (uint32_t)(es * lay.q.st), sg = (uint32_t)(es * lay.g.st);
+    const uint32_t sk = (uint32_t)(es * lay.k.st), sv = (uint32_t)(es * lay.v.st);
     const int j = t0 + nk, jc = min(j, T - 1);
     const int before = max(jc - 1, 0), after = min(jc + 1, T - 1);
     const Slice kj = TL::load(K, jc, g, sk), vj = TL::load(V, jc, g, sv);
@@ -842,15 +842,15 @@ __global__ __launch_bounds__(256) void bwd_dkdv_f32_kernel(
     TL::zero(adv);
     // per-lane products of a logit or a dP, blended before the sum over the lanes
     auto dots = [&](const Slice &x, const Slice &y) {
-        float t[TL::NC];
-#pragma unroll
-        for (int c = 0; c < TL::NC; ++c) t[c] = chunk_dot(x.c[c], y.c[c]);
-        return t[0];
+        if constexpr (TL::kF32)
+            return chunk_dot(x.c[0], y.c[0]);
+        else
+            return TL::dot(x, y);
     };
     auto sum = [&](float t) { return chunk_sum<1, L>(&t); };
     for (int hg = 0; hg < hd.G; ++hg) {
         const int bh = hd.q_of(bk, hg);
-        const float *Q = q + lay.q.head(bh, hd.H), *G = dO + lay.g.head(bh, hd.H);
+        const S *Q = q + lay.q.head(bh, hd.H), *G = dO + lay.g.head(bh, hd.H);
         const float *Le = lse + (size_t)bh * T, *De = delta_in + (size_t)bh * T;
         // a query that does not read the key is replaced by the key's own, with weight 0
         for (int d = 0; d <= wmax; d += 2) {
@@ -973,20 +973,6 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
         e = launch(kBwdDq, dqk, grid_of(nb), dim3(256), (unsigned)(2 * rows * TL::kRow), s, (const S *)q,
                    (const S *)k, (const S *)v, (const S *)o, lse, (const S *)dO, (S *)dq, delta_ws, partials, T, W, rt,
                    rtp, rf, tau, tiles, nb, rows, hd, lay);
-        if (e != hipSuccess) return e;
-        // dk, dv of as few rows: one key per D / 4 lanes unless the tile kernel has the heads
-        // of a group side by side (d 128: at most two of them) or a long window of d 32 on
-        // the matrix cores.  Against the tile kernel at 4096 queries, W 3 to 16, d 32 / 64 /
-        // 128: groups of one 0.80 to 0.94 / 0.71 to 0.79 / 0.48 to 0.55 times, of three 0.75 /
-        // 0.61 / 0.37, of two 1.2 / 1.0 / 0.65 to 0.86, of four 1.8 / 1.5 / 0.62 to 0.75; d 32
-        // and W 64 1.1 to 1.2; at 16000 queries and W 64 1.1 to 1.3.
-        if (wide && (D == 128 || (ts.hs == 1 && (D == 64 || W <= 32)))) {
-            const int kper = 1024 / D, ktiles = T / kper + (T % kper != 0), kb = ktiles * (BH / hd.G);
-            return launch(kBwdDkDv, rtp ? bwd_dkdv_f32_kernel<D, true> : bwd_dkdv_f32_kernel<D, false>, grid_of(kb),
-                          dim3(256), 0, s, (const S *)q, (const S *)k, (const S *)v, lse, (const S *)dO, delta_ws,
-                          (S *)dk, (S *)dv, partials, nb, dalpha, dtheta, T, W, rt, rtp, rf, tau,
-                          kLog2e / sqrtf((float)D), ktiles, kb, hd, lay);
-        }
     } else {
         auto dqk = rtp ? bwd_dq_tile_kernel<D, true, true>
                        : interp ? bwd_dq_tile_kernel<D, true, false> : bwd_dq_tile_kernel<D, false, false>;
@@ -995,6 +981,26 @@ static hipError_t launch_bwd_t(const void *q, const void *k, const void *v, cons
                    rt, rtp, rf, tau, kLog2e / sqrtf((float)D), ts, hd, lay);
     }
     if (e != hipSuccess) return e;
+    // dk, dv of few rows: one key per lanes of one 16-byte chunk, unless the tile kernel has
+    // the heads of a group side by side or a long window on the matrix cores.  Against the
+    // tile kernel, W 3 to 17: float32 d 32 / 64 / 128 at 4096 queries and groups of one 0.80
+    // to 0.94 / 0.71 to 0.79 / 0.48 to 0.55 times, of three 0.75 / 0.61 / 0.37, of two 1.2 /
+    // 1.0 / 0.65 to 0.86, of four 1.8 / 1.5 / 0.62 to 0.75; d 32 and W 64 1.1 to 1.2; at
+    // 16000 queries and W 64 1.1 to 1.3.  bfloat16 d 128, groups of one, up to 8192 queries
+    // 0.71 to 1.02, at 16000 1.15 to 1.34, W 64 1.2 to 1.7, groups of two 1.05 to 1.27;
+    // d 32 and 64 0.91 to 1.3.
+    if constexpr (TL::kF32 || D == 128) {
+        const bool few = TL::kF32 ? f32_wide(BH, T) && (D == 128 || (ts.hs == 1 && (D == 64 || W <= 32)))
+                                  : (long long)BH * T <= 8192 && ts.hs == 1 && W <= 24;
+        if (few) {
+            constexpr int kper = 4096 / TL::kRow;  // keys per workgroup
+            const int ktiles = T / kper + (T % kper != 0), kb = ktiles * (BH / hd.G);
+            return launch(kBwdDkDv, rtp ? bwd_dkdv_rows_kernel<S, D, true> : bwd_dkdv_rows_kernel<S, D, false>,
+                          grid_of(kb), dim3(256), 0, s, (const S *)q, (const S *)k, (const S *)v, lse, (const S *)dO,
+                          delta_ws, (S *)dk, (S *)dv, partials, nb, dalpha, dtheta, T, W, rt, rtp, rf, tau,
+                          kLog2e / sqrtf((float)D), ktiles, kb, hd, lay);
+        }
+    }
     // dk, dv: a head slot's q and dO rows of the staged chunks, their lse and Delta; the
     // sums of the slots past the first take their place at the end
     TileShape tk = ts;

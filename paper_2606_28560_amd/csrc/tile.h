@@ -59,8 +59,8 @@ __device__ __forceinline__ float chunk_sum(float *t) {
     s += lane_xor<1>(s);
     return s;
 }
-// L: lanes per row in the quad layout, 4 (neighbouring lanes L n + g), or D / 4 for float32
-// rows of one 16-byte chunk a lane, which take the VALU functions alone.
+// L: lanes per row in the quad layout, 4 (neighbouring lanes L n + g), or one per 16-byte
+// chunk of the row, which take the VALU functions alone.
 template <typename S, int D, int L = 4>
 struct Tile {
     static constexpr int kRow = D * (int)sizeof(S);  // bytes of a row
@@ -146,7 +146,8 @@ struct Tile {
             for (int c = 0; c < NC; ++c) t[c] = chunk_dot(x.c[c], y.c[c]);
             return chunk_sum<NC, L>(t);
         } else {
-            return quad_sum(dot(x, y));
+            float t = dot(x, y);
+            return chunk_sum<1, L>(&t);
         }
     }
 
@@ -414,24 +415,21 @@ struct Tile {
     // every frequency.  The partner of dim d < D/2 is d + D/2: D/8 slice
     // positions on, except for bfloat16 rows of 32, whose partner lanes are g and g + 2.
     __device__ static __forceinline__ void rope_t(Acc &a, int t, const double *sf, int g) {
-        if constexpr (NC == 1 && kF32) {
+        if constexpr (NC == 1) {
+            constexpr int PV = 16 / (int)sizeof(S);
             const bool hi = g >= L / 2;  // this lane holds the second halves of its pairs
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+            for (int p = 0; p < PV; ++p) {
                 float c, s;
-                rope_cs_f64(t, sf[4 * (g & (L / 2 - 1)) + e], c, s);
-                const float x = a.c[0][e], o = lane_xor<L / 2>(x);
-                a.c[0][e] = hi ? fmaf(-s, o, c * x) : fmaf(c, x, s * o);
-            }
-        } else if constexpr (!kF32 && D == 32) {
-            const bool hi = g & 2;  // this lane holds the second halves of its pairs
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                float c, s;
-                rope_cs_rev(t, sf[8 * (g & 1) + p], c, s);
-                const float x = a.c[p >> 2][p & 3];
-                const float o = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xF, 0xF, true));
-                a.c[p >> 2][p & 3] = hi ? x * c - o * s : x * c + o * s;
+                const double f = sf[PV * (g & (L / 2 - 1)) + p];
+                const float x = a.c[p >> 2][p & 3], o = lane_xor<L / 2>(x);
+                if constexpr (kF32) {
+                    rope_cs_f64(t, f, c, s);
+                    a.c[p >> 2][p & 3] = hi ? fmaf(-s, o, c * x) : fmaf(c, x, s * o);
+                } else {
+                    rope_cs_rev(t, f, c, s);
+                    a.c[p >> 2][p & 3] = hi ? x * c - o * s : x * c + o * s;
+                }
             }
         } else {
             constexpr int HB = NB / 2;

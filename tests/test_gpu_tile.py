@@ -165,3 +165,22 @@ def test_float32_lanes(G, T, D, W, base, alpha):
         assert (a - b).abs().max() <= 1e-5 * max(1.0, float(a.abs().max())), name
     # n times the same terms
     assert abs(float(res[1][6]) - n * float(res[0][6])) <= 1e-5 * n * max(1.0, T * abs(float(res[0][6])))
+
+
+@pytest.mark.parametrize("G,T,W,base,alpha", [(1, 65, 8, FIB, 0.9), (3, 33, 24, POW2, 1.0), (1, 1, 0, FIB, 1.0),
+                                              (1, 200, 17, FIB, 1.0)])
+def test_bfloat16_d128_dkdv_of_few_rows(G, T, W, base, alpha):
+    # the kernel of few rows and the tile kernel give dk, dv (rotated back) of the same heads
+    # within the rounding of the stored values and of the bfloat16 Delta they share
+    n = 8192 // (2 * G * T) + 1
+    x = inputs.attention_inputs(1, 2 * G, T, 128, "bf16", 895, 0, names=("q", "dO"))
+    x.update(inputs.attention_inputs(1, 2, T, 128, "bf16", 895, 0, names=("k", "v")))
+    res = []
+    for r in (1, n):
+        q, k, v, dO = (x[m].cuda().repeat(r, 1, 1, 1) for m in ("q", "k", "v", "dO"))
+        o, lse = F.fibattn_forward(q, k, v, W, base, alpha)
+        res.append(F.fibattn_backward(q, k, v, o, lse, dO, W, base, alpha, rope_base=10000.0)[1:3])
+    torch.cuda.synchronize()
+    for name, a, b in zip(("dk", "dv"), *res):
+        a, b = a.double().expand(n, *a.shape[1:]), b.double()
+        assert ((a - b).abs() <= 2.0 ** -7 * a.abs() + 1e-5 * a.abs().max()).all(), name
