@@ -127,7 +127,7 @@ def test_invalid_arguments_return_codes_without_gpu():
     assert ws(8, 8, 1024, 64, 8, 15) >= 4 * n + 8 * (n // 64) + 4 * 15 * n
     assert ws(8, 8, 1024, 64, 8, 0) >= 4 * n + 8 * (n // 64) + 4 * 32 * n
     assert ws(8, 8, 1024, 64, 8, 15) - ws(8, 8, 1024, 64, 8, 11) == 4 * 4 * n
-    assert ws(8, 8, 1024, 32, 8, 15) < 4 * n + 4 * 15 * n   # generic kernels: no terms
+    assert ws(8, 8, 1024, 32, 8, 15) < 4 * n + 4 * 15 * n   # tile and float32 kernels: no terms
     assert ws(8, 8, 1024, 64, 17, 15) < 4 * n + 4 * 15 * n
     # rope
     assert L.fibattn_rope(None, None, 1, 1, 8, 64, ctypes.c_float(1e4), 0, 1, None) == 1

@@ -103,7 +103,7 @@ def test_invalid_device_alpha_gives_nan(alpha):
                                                ("fp32", 32, 8, 6)])
 def test_table_used_with_another_window_gives_nan(dtype, D, table_W, W):
     # a table records its W: with another W its in-window rule would have dropped or
-    # kept the wrong rungs, so every output is NaN (matrix-core and generic kernels)
+    # kept the wrong rungs, so every output is NaN (matrix-core and tile and float32 kernels)
     x = inputs.attention_inputs(1, 2, 150, D, dtype, 451, 0)
     got = _dev_run(x, W, FIB, 0.9, poison=False, table_W=table_W)
     for name in ("o", "lse", "dq", "dk", "dv"):
@@ -142,7 +142,7 @@ def test_table_from_theta_equals_table_from_alpha(base, W):
 
 @pytest.mark.parametrize("dtype,D,W", [("bf16", 64, 8), ("fp32", 32, 8), ("bf16", 64, 20)])
 def test_backward_dtheta_equals_separate_dtheta(dtype, D, W):
-    # dtheta written by the backward (matrix-core and generic kernels) is bitwise the
+    # dtheta written by the backward (matrix-core and tile and float32 kernels) is bitwise the
     # value fibattn_dtheta computes from the stored dalpha; a table built from alpha
     # gives NaN
     x = inputs.attention_inputs(1, 4, 200, D, dtype, 452, 0)

@@ -344,13 +344,16 @@ def test_gradients_rotated_back(D, dtype, W, H):
 @pytest.mark.parametrize("D,dtype,W", ROTATED)
 def test_rotated_q_has_the_bits_of_the_rope_launch(D, dtype, W, H, T):
     # also where the rotated rows take the place of q, for which they are written by the wave
-    # that has read them; and o and lse are those of the rotated q
+    # that has read them, and with a device table; o and lse are those of the rotated q
     x = {n: t.cuda() for n, t in make(1, H, H, T, D, dtype, 950).items()}
     K, Q = F.fibattn_rope(x["k"]), F.fibattn_rope(x["q"])
     o, lse, got = F.fibattn_forward_rope_q(x["q"], K, x["v"], W, FIB, 0.9)
     want_o, want_lse = F.fibattn_forward(Q, K, x["v"], W, FIB, 0.9)
     place = x["q"].clone()
     o2, lse2, _ = F.fibattn_forward_rope_q(place, K, x["v"], W, FIB, 0.9, q_out=place)
+    table = F.fibattn_device_table(torch.tensor([0.9], device="cuda"), FIB, W)
+    od, ld, Qd = F.fibattn_forward_rope_q_dt(x["q"], K, x["v"], W, table)
     torch.cuda.synchronize()
+    assert torch.equal(Qd, Q) and torch.equal(od, o) and torch.equal(ld, lse)
     assert torch.equal(got, Q) and torch.equal(o, want_o) and torch.equal(lse, want_lse)
     assert torch.equal(place, Q) and torch.equal(o2, o) and torch.equal(lse2, lse)

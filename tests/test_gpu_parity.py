@@ -50,7 +50,7 @@ SMALL = [
     (1, 5, 4096, 64, "bf16", 8, FIB, 1.0),
     (1, 5, 4096, 64, "bf16", 8, FIB, 0.9),
     # the matrix-core kernels' window limit: their band tile reaches exactly 16 keys
-    # back (W = 16), one below the first W the generic kernels take (W = 17); W = 0 with
+    # back (W = 16), one below the first W the tile and float32 kernels take (W = 17); W = 0 with
     # alpha = 0.9 has a rung at d = 0.9 whose row r0 is the query itself
     (1, 2, 300, 64, "bf16", 16, FIB, 1.0),
     (1, 2, 300, 64, "bf16", 16, FIB, 0.7310586),
@@ -150,7 +150,7 @@ def test_rope_in_place():
 
 PIPE = [
     # (dtype, D, W, alpha): bf16/64/W<=16 applies R^T in the backward kernels' epilogue;
-    # the others run the generic kernels followed by an R^T launch
+    # so do the tile and float32 kernels of the others
     ("bf16", 64, 8, 0.85),
     ("bf16", 64, 8, 1.0),
     ("fp32", 64, 8, 0.85),
@@ -191,8 +191,8 @@ def test_pipeline_with_rope(dtype, D, W, alpha):
 ROPE_Q = [
     # (B, H, H_kv, T, D, dtype, W, alpha): bf16 with d_head 64 and W <= 16 rotates q inside
     # the forward (1, 2 or 4 query heads per workgroup, integer and interpolated offsets,
-    # ragged tails, a single position, the window limit); the other shapes run the RoPE
-    # launch on q, then the forward
+    # ragged tails, a single position, the window limit); the tile and float32 forward do the
+    # same and need a place for the rotated rows
     (2, 2, 2, 300, 64, "bf16", 8, 1.0),
     (1, 3, 3, 333, 64, "bf16", 8, 0.85),
     (1, 8, 2, 300, 64, "bf16", 12, 1.0),
@@ -201,6 +201,13 @@ ROPE_Q = [
     (1, 2, 2, 200, 64, "fp32", 8, 0.85),
     (1, 2, 1, 150, 128, "bf16", 8, 1.0),
     (1, 2, 2, 150, 64, "bf16", 20, 0.9),  # past the matrix-core window limit
+    # bf16 d 32, whose pairs lie in two lanes (integer, interpolated, grouped heads), and
+    # float32 d 128
+    (1, 2, 2, 200, 32, "bf16", 10, 1.0),
+    (1, 3, 3, 150, 32, "bf16", 8, 0.85),
+    (1, 4, 1, 130, 32, "bf16", 12, 0.9),
+    (1, 2, 2, 150, 128, "fp32", 8, 0.85),
+    (1, 4, 2, 100, 128, "fp32", 40, 1.0),
 ]
 
 
@@ -271,7 +278,7 @@ def test_forward_rotating_q_on_load_full_size(name, ci):
 
 
 HEAD128 = [
-    # (B, H, H_kv, T, D, dtype, W, base, alpha): d_head = 128 runs the generic kernels
+    # (B, H, H_kv, T, D, dtype, W, base, alpha): d_head = 128 runs the tile and float32 kernels
     (1, 2, 2, 260, 128, "fp32", 8, FIB, 0.7310586),
     (2, 2, 1, 200, 128, "bf16", 8, FIB, 1.0),
     (1, 4, 4, 150, 128, "bf16", 12, POW2, 1.3),
@@ -469,7 +476,7 @@ STRIDED = [
     (2, 4, 4, 300, 64, "bf16", 8, 1.0, "bthd", "packed"),     # matrix-core kernels, integer
     (2, 4, 4, 300, 64, "bf16", 8, 0.85, "qkv", "bthd"),       # interpolating, fused-qkv inputs
     (1, 8, 2, 257, 64, "bf16", 8, 1.0, "bthd", "bthd"),       # grouped heads
-    (2, 3, 3, 200, 32, "fp32", 6, 0.7310586, "qkv", "bthd"),  # generic kernels
+    (2, 3, 3, 200, 32, "fp32", 6, 0.7310586, "qkv", "bthd"),  # float32 kernels
     (1, 4, 2, 130, 128, "bf16", 10, 1.2, "bthd", "qkv"),      # d_head 128, outputs in a qkv buffer
     # packed rows with non-packed head strides: the matrix-core kernels' strided instances
     (2, 4, 4, 300, 64, "bf16", 8, 1.0, "tslice", "tslice"),
@@ -516,9 +523,8 @@ ROPE_Q_STRIDED = [
     (2, 4, 4, 300, 64, "bf16", 8, 1.0, "qkv", "bthd"),
     (1, 8, 2, 257, 64, "bf16", 12, 0.85, "tslice", "tslice"),
     (1, 4, 4, 200, 64, "bf16", 16, 1.0, "bthd", "packed"),
-    (1, 2, 2, 200, 64, "fp32", 8, 0.85, "qkv", "bthd"),  # the RoPE launch, then the forward
-    # the same past the matrix-core window, on 2^17+ rows of q: the RoPE launch of one
-    # strided tensor with two positions per lane group, a ragged last position block
+    (1, 2, 2, 200, 64, "fp32", 8, 0.85, "qkv", "bthd"),  # float32 kernels
+    # the tile forward past the matrix-core window, on 2^17+ rows of q with a ragged last tile
     (1, 33, 33, 3999, 64, "bf16", 20, 0.9, "bthd", "bthd"),
 ]
 

@@ -1,8 +1,9 @@
 """GPU parity of the tile kernels (every shape outside the bfloat16, d_head 64, W <= 16
 path) where they can go wrong: windows at the edges of the 32-row band chunks and of the
 chunks staged together, lengths around the 16- and 64-row tiles, each storage type and head
-size (the float32 d_head 128 launch has two waves per workgroup), one, two, three and four
-query heads side by side, more rungs than a wave has row groups, and strided placements."""
+size, one, two, three and four query heads side by side, both kernels of float32 rows (few
+rows and many; the d_head 128 dk/dv launch of many has two waves per workgroup), more rungs
+than a wave has row groups, and strided placements."""
 import pytest
 import torch
 
@@ -32,7 +33,7 @@ CASES = [
     (1, 2, 2, 200, 32, "bf16", 0, MANY, 0.9),     # 32 rungs
     (1, 2, 2, 200, 64, "fp32", 16, MANY, 1.0),
     (1, 2, 1, 130, 32, "fp32", 17, FIB, 0.9),
-    (1, 4, 2, 97, 128, "fp32", 8, FIB, 1.2),      # two waves per workgroup
+    (1, 4, 2, 97, 128, "fp32", 8, FIB, 1.2),
     (1, 3, 3, 33, 128, "fp32", 128, FIB, 1.0),
     (1, 1, 1, 1, 128, "fp32", 8, FIB, 1.0),
     (1, 1, 1, 15, 128, "bf16", 0, FIB, 0.9),

@@ -3,7 +3,7 @@
 Same kernels, so the outputs must be bitwise those of fibattn_backward_gqa on the same
 inputs; three calls in a row on the library's one static scratch array, each smaller
 than the one before (the later calls find the earlier calls' contents in it), over
-the matrix-core and the generic kernels.  The smallest call is also checked against
+the matrix-core and the tile and float32 kernels.  The smallest call is also checked against
 the fp64 oracle.
 """
 import pytest
