@@ -152,7 +152,7 @@ __global__ __launch_bounds__(256, (dq_waves<D>)) void bwd_dq_tile_kernel(
     typename TL::Acc acc;
     TL::zero(acc);
     double dsum = 0.0;  // the entries' sum of p dP (this lane's part)
-    bool tiny = false;
+    bool weak = false, tiny = false;  // weights that tiny_weight names, and large rows beside them
     {
         const Slice qm = TL::from_quad(qq, lane), gmm = TL::from_quad(gg, lane);
         const float lse2_m = __shfl(lse2, 4 * nm, 64), delta_m = __shfl(delta, 4 * nm, 64);
@@ -168,10 +168,11 @@ __global__ __launch_bounds__(256, (dq_waves<D>)) void bwd_dq_tile_kernel(
             TL::stage(vr, V, rbeg, rows, T, lay.v.st, wave, nw);
             wait_vmem();
             __syncthreads();
+            float least = INFINITY;
             for (int c = 0; c < n; ++c) {
                 if (t0 + 16 - 32 * (c0 + c) <= 0) break;
                 const int base = 16 * wv + 32 * (n - 1 - c);
-                float ds[8], x[8], least = INFINITY;
+                float ds[8];
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
                     const f32x4 s = TL::scores(TL::staged(kr, base + 16 * b + nm, gm), qm);
@@ -182,15 +183,15 @@ __global__ __launch_bounds__(256, (dq_waves<D>)) void bwd_dq_tile_kernel(
                         const bool in = (unsigned)(im - key) <= reach;
                         const float xe = fmaf(s[e], sl2, -lse2_m);
                         least = fminf(least, xe);
-                        x[4 * b + e] = in ? xe : -INFINITY;
                         const float p = in ? fast_exp2(xe) : 0.f, dP = in ? dp[e] : 0.f;
                         ds[4 * b + e] = tau * p * (dP - delta_m);
                         dsum = fma((double)p, (double)dP, dsum);
                     }
                 }
-                tiny |= tiny_weight(x, least);
                 TL::accumulate(acc, kr, base, TL::weights(ds), gm);
             }
+            if (tiny_weight(least))
+                tiny |= TL::large_rows(kr, 16 * wv, 32 * n) || TL::large_rows(vr, 16 * wv, 32 * n), weak = true;
         }
     }
     if constexpr (TL::NC > 2) {
@@ -204,6 +205,7 @@ __global__ __launch_bounds__(256, (dq_waves<D>)) void bwd_dq_tile_kernel(
         if (TL::NC > 2) load_rung(0, V, sv, vx[0]);
         if (TL::NC > 1) load_rung(0, K, sk, kx[0]);
     }
+    if (weak) tiny |= TL::large_rows(gg);
     TL::to_quad_acc(acc, lane);
     // the query's band sum, on each of its four quad lanes
     dsum += __shfl_xor(dsum, 16, 64);
@@ -599,10 +601,11 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                     }
                     continue;
                 }
+                float least = INFINITY;
                 for (int c = 0; c < n; ++c) {
                     if (t0 + 32 * (c0 + c) >= T) break;
                     const int base = 16 * wv + 32 * c;  // the chunk's first staged row
-                    float ds[8], p[8], xs[8], least = INFINITY;
+                    float ds[8], p[8];
 #pragma unroll
                     for (int b = 0; b < 2; ++b) {
                         constexpr int CH = TL::NC == 2 ? 4 : 8;
@@ -620,17 +623,23 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                             } else {
                                 const float xe = fmaf(s[e], sl2, -l2[e]);
                                 least = fminf(least, xe);
-                                xs[4 * b + e] = in ? xe : -INFINITY;
                                 x = fast_exp2(xe);
                             }
                             p[4 * b + e] = in ? x : 0.f;
                             ds[4 * b + e] = in ? tau * x * (dp[e] - de[e]) : 0.f;
                         }
                     }
-                    if constexpr (!TL::kF32) tiny |= tiny_weight(xs, least);
                     TL::accumulate(adk, qb, base, TL::weights(ds), gm);
                     TL::accumulate(adv, gb, base, TL::weights(p), gm);
                 }
+                if constexpr (!TL::kF32)
+                    if (tiny_weight(least)) {
+                        tiny |= TL::large_rows(qb, 16 * wv, 32 * n) || TL::large_rows(gb, 16 * wv, 32 * n) ||
+                                TL::large_rows(vm);
+                        for (int x = lane; x < 32 * n; x += 64)  // Delta, which is as large as o
+                            tiny |= fabsf(sd[hs * rows + 16 * wv + x]) >= 0x1p40f;
+                        tiny = __builtin_amdgcn_ballot_w64(tiny);
+                    }
             }
     }
     if (!valu) {

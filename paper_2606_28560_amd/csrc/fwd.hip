@@ -169,10 +169,11 @@ __global__ __launch_bounds__(256, (fwd_waves<D>)) void fwd_tile_kernel(
         }
         wait_vmem();
         __syncthreads();
+        float least = INFINITY;
         for (int c = 0; c < n; ++c) {
             if (t0 + 16 - 32 * (c0 + c) <= 0) break;  // rows before the start
             const int base = 16 * wv + 32 * (n - 1 - c);  // the chunk's first staged row
-            float p[8], mx = -INFINITY, least = INFINITY;
+            float p[8], mx = -INFINITY, low = INFINITY;
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 const f32x4 s = TL::scores(TL::staged(kr, base + 16 * b + nm, gm), qm);
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(256, (fwd_waves<D>)) void fwd_tile_kernel(
                     const int key = rbeg + base + 16 * b + 4 * gm + e;
                     p[4 * b + e] = (unsigned)(im - key) <= reach ? s[e] : -INFINITY;
                     mx = fmaxf(mx, p[4 * b + e]);
-                    least = fminf(least, s[e]);
+                    low = fminf(low, s[e]);
                 }
             }
             mx = max4(mx) * sl2;
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(256, (fwd_waves<D>)) void fwd_tile_kernel(
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) p[e] = fmaf(p[e], sl2, -m);
-            tiny |= tiny_weight(p, fmaf(least, sl2, -m));
+            least = fminf(least, fmaf(low, sl2, -m));
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 p[e] = fast_exp2(p[e]);
@@ -203,6 +204,7 @@ __global__ __launch_bounds__(256, (fwd_waves<D>)) void fwd_tile_kernel(
             }
             TL::accumulate(acc, vr, base, TL::weights(p), gm);
         }
+        if (tiny_weight(least)) tiny |= TL::large_rows(vr, 16 * wv, 32 * n);
     }
     if (TL::NC > 2 && nact > 0) load_batch(0, V, sv, vx[0]);
     l = sum4(l);
@@ -286,7 +288,7 @@ __global__ __launch_bounds__(256, (fwd_waves<D>)) void fwd_tile_kernel(
     // Entries a query does not have took part with weights of 0: rows of the chunks outside
     // its window, and its own row in the place of a rung's.  If that, or what the query does
     // attend, left anything that is not finite, the entries are taken one by one instead;
-    // so are weights too small for the matrix cores.
+    // so are weights too small for the matrix cores, where they count.
     if (tiny || __builtin_amdgcn_ballot_w64(!(TL::finite(acc) && l * 0.f == 0.f)))
         forward_by_entry<TL>(qq, K, V, sk, sv, ic, gq, W, rt, nact, sl2, acc, m, l);
 

@@ -59,6 +59,11 @@ __device__ __forceinline__ float chunk_sum(float *t) {
     s += lane_xor<1>(s);
     return s;
 }
+// Either bfloat16 of a word at least 2^16, or not finite.
+constexpr uint32_t kLargeRow = 0x4780;
+__device__ __forceinline__ bool large_pair(uint32_t w) {
+    return (w & 0x7fff0000u) >= kLargeRow << 16 || (w & 0x7fffu) >= kLargeRow;
+}
 // L: lanes per row in the quad layout, 4 (neighbouring lanes L n + g), or one per 16-byte
 // chunk of the row, which take the VALU functions alone.
 template <typename S, int D, int L = 4>
@@ -333,6 +338,27 @@ struct Tile {
         }
     }
 
+    // Whether `rows` staged bfloat16 rows from `base` on, or the wave's rows x, hold a large
+    // element.
+    __device__ static __forceinline__ bool large_rows(const char *buf, int base, int rows) {
+        bool t = false;
+#pragma unroll 1
+        for (int i = threadIdx.x & 63; i < rows * (kRow / 16); i += 64) {
+            const u32x4 w = *reinterpret_cast<const u32x4 *>(buf + base * kRow + 16 * i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t |= large_pair(w[e]);
+        }
+        return __builtin_amdgcn_ballot_w64(t);
+    }
+    __device__ static __forceinline__ bool large_rows(const Slice &x) {
+        bool t = false;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t |= large_pair(x.c[c][e]);
+        return __builtin_amdgcn_ballot_w64(t);
+    }
+
     // What a frequency (radians per position) is multiplied with for rope: the RoPE launch of
     // bfloat16 rows of 64 reduces the angle in radians, the others' in revolutions.
     static constexpr double kRopeUnit = !kF32 && D == 64 ? 1.0 : 0.15915494309189533576888376337251;
@@ -464,15 +490,12 @@ __device__ __forceinline__ float prob(float s, float sl2, float lse2) { return e
 
 // Weights 2^x of a bfloat16 band that the matrix cores cannot take in full: three bfloat16
 // parts hold 24 bits from 2^-109 on (their last one is a multiple of 2^-133), and the exp2
-// instruction gives 0 below 2^-126.  Below 2^-150 a float32 is 0 either way.  `least`: the
-// least x of the lane's rows, in its window or not, which is all that is looked at otherwise.
+// instruction gives 0 below 2^-126.  They count only next to large rows: where every element
+// is below 2^16 what is lost of a sum is below 2^-70 (rows of weights times dP: 2^-126 2^39
+// 2^16).  Heads whose logits spread by more than 69 in a window are ordinary: their waves look
+// at the staged rows (least: the least x of the lane's rows, in the window or not) and go on.
 constexpr float kLeastWeight = -100.f;
-__device__ __forceinline__ bool tiny_weight(const float *x, float least) {
-    if (!__builtin_amdgcn_ballot_w64(least < kLeastWeight)) return false;
-    bool t = false;
-    for (int e = 0; e < 8; ++e) t |= x[e] < kLeastWeight && x[e] >= -150.f;
-    return __builtin_amdgcn_ballot_w64(t);
-}
+__device__ __forceinline__ bool tiny_weight(float least) { return __builtin_amdgcn_ballot_w64(least < kLeastWeight); }
 
 // Weight and lane bookkeeping of a launch: `nw` waves per workgroup are `hs` query heads
 // of one group (all reading the same rows) times nw / hs runs of 16 rows.

@@ -357,3 +357,14 @@ def test_rotated_q_has_the_bits_of_the_rope_launch(D, dtype, W, H, T):
     assert torch.equal(Qd, Q) and torch.equal(od, o) and torch.equal(ld, lse)
     assert torch.equal(got, Q) and torch.equal(o, want_o) and torch.equal(lse, want_lse)
     assert torch.equal(place, Q) and torch.equal(o2, o) and torch.equal(lse2, lse)
+
+
+@pytest.mark.parametrize("H,Hkv,T,D,dtype,W,base,alpha", [c for c in SHAPES if c[4] == "bf16"])
+def test_logits_far_apart(H, Hkv, T, D, dtype, W, base, alpha):
+    # logits of +-60: most weights are below what the matrix cores take in full, with rows of
+    # ordinary size beside them
+    x = make(1, H, Hkv, T, D, dtype, 970)
+    x["q"] = (20.0 * x["q"].float()).bfloat16()
+    ref = rows({n: x[n] for n in ("q", "k", "v")}, W, base, alpha)
+    got = run(x, W, base, alpha, ref["o"].bfloat16(), ref["lse"].float())
+    close(got, rows(x, W, base, alpha, ref["o"].bfloat16(), ref["lse"].float()), dtype)
