@@ -543,7 +543,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
     // float32 with a window of one chunk: on the VALU, every product in the forward's order.
     // The rounding of a logit is then the one that lse holds too, and cancels in the
     // probability; logits from the matrix cores have errors of their own (dk, dv 5 to 25 %
-    // further from 64 bits than the VALU's at W <= 16, nearer at W >= 79; B4 H8 T1024 d 64
+    // further from 64 bits than the VALU's at W <= 16, nearer at W >= 24; B4 H8 T1024 d 64
     // W 12: 25.1 us with them, 25.6 here).
     const bool valu = TL::kF32 && W <= 16;
     bool tiny = false;
@@ -572,7 +572,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                 }
                 for (int x = threadIdx.x; x < ts.hs * rows; x += blockDim.x) {
                     const size_t at = (size_t)hd.q_of(bk, pass * ts.hs + x / rows) * T + min(rbeg + x % rows, T - 1);
-                    sl[x] = lse[at] * kLog2e;
+                    sl[x] = TL::kF32 && !valu ? lse[at] : lse[at] * kLog2e;  // as prob and prob_low take it
                     sd[x] = delta_in[at];
                 }
                 wait_vmem();
@@ -619,7 +619,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
                             const bool in = jm < T && (unsigned)(rbeg + si + e - jm) <= reach;
                             float x;
                             if constexpr (TL::kF32) {
-                                x = prob(s[e], sl2, l2[e]);
+                                x = prob_low(s[e], sl2, l2[e]);
                             } else {
                                 const float xe = fmaf(s[e], sl2, -l2[e]);
                                 least = fminf(least, xe);
@@ -745,7 +745,7 @@ __global__ __launch_bounds__(256, (dkdv_waves<S, D>)) void bwd_dkdv_tile_kernel(
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
                 const bool in = has(r, y);
-                const float x = prob(s[y], sl2, xl[y] * kLog2e);
+                const float x = TL::kF32 && !valu ? prob_low(s[y], sl2, xl[y]) : prob(s[y], sl2, xl[y] * kLog2e);
                 const float wt = INTERP ? (y ? rt.w[r] : 1.f - rt.w[r]) : 1.f;
                 p[y] = in ? x * wt : 0.f;
                 c[y] = in ? tau * x * (dP[y] - xd[y]) * wt : 0.f;
@@ -864,7 +864,7 @@ __global__ __launch_bounds__(256) void bwd_dkdv_rows_kernel(
         // a query that does not read the key is replaced by the key's own, with weight 0
         for (int d = 0; d <= wmax; d += 2) {
             Slice x[2], y[2];
-            float l[2], dl[2];
+            float l[2], dl[2], p[2], c[2];
             bool in[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -878,17 +878,18 @@ __global__ __launch_bounds__(256) void bwd_dkdv_rows_kernel(
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 const float s = sum(dots(x[u], kj)), dP = sum(dots(y[u], vj));
-                const float p = prob(s, sl2, l[u]);
-                TL::axpy(adk, in[u] ? tau * p * (dP - dl[u]) : 0.f, x[u]);
-                TL::axpy(adv, in[u] ? p : 0.f, y[u]);
+                p[u] = in[u] ? prob(s, sl2, l[u]) : 0.f;
+                c[u] = in[u] ? tau * p[u] * (dP - dl[u]) : 0.f;
             }
+            TL::add2(adk, c[0], x[0], c[1], x[1]);
+            TL::add2(adv, p[0], y[0], p[1], y[1]);
         }
         // a rung's two queries: i0 has the key as row r0, i0 + 1 as row r1
         for (int r = 0; r < nact; ++r) {
             const int d0 = rt.d0[r];
             const float w = rt.w[r];
             Slice x[2], y[2];
-            float l[2], dl[2];
+            float l[2], dl[2], p[2], c[2];
             bool in[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -909,9 +910,16 @@ __global__ __launch_bounds__(256) void bwd_dkdv_rows_kernel(
                     s = fmaf(1.f - wt, dots(x[u], u ? ka : kb), s);
                     dP = fmaf(1.f - wt, dots(y[u], u ? va : vb), dP);
                 }
-                const float p = prob(sum(s), sl2, l[u]);
-                TL::axpy(adk, in[u] ? tau * p * (sum(dP) - dl[u]) * wt : 0.f, x[u]);
-                TL::axpy(adv, in[u] ? p * wt : 0.f, y[u]);
+                const float x0 = prob(sum(s), sl2, l[u]);
+                p[u] = in[u] ? x0 * wt : 0.f;
+                c[u] = in[u] ? tau * x0 * (sum(dP) - dl[u]) * wt : 0.f;
+            }
+            if (w != 0.f) {
+                TL::add2(adk, c[0], x[0], c[1], x[1]);
+                TL::add2(adv, p[0], y[0], p[1], y[1]);
+            } else {
+                TL::axpy(adk, c[0], x[0]);
+                TL::axpy(adv, p[0], y[0]);
             }
         }
     }

@@ -177,6 +177,23 @@ struct Tile {
                 }
         }
     }
+    // The same with the two products added to each other first: a chain of half as many
+    // roundings (float32 dk and dv of W 64: 0.97 -> 0.90 times as far from 64 bits).
+    __device__ static __forceinline__ void add2(Acc &acc, float a, const Slice &x, float b, const Slice &y) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                if constexpr (kF32) {
+                    acc.c[c][w] += fmaf(a, __uint_as_float(x.c[c][w]), b * __uint_as_float(y.c[c][w]));
+                } else {
+                    f32x4 &d = acc.c[2 * c + (w >> 1)];
+                    const int e = 2 * (w & 1);
+                    d[e] += fmaf(a, bf16_lo(x.c[c][w]), b * bf16_lo(y.c[c][w]));
+                    d[e + 1] += fmaf(a, bf16_hi(x.c[c][w]), b * bf16_hi(y.c[c][w]));
+                }
+            }
+    }
     // acc += a x.
     __device__ static __forceinline__ void axpy(Acc &acc, float a, const Slice &x) {
 #pragma unroll
@@ -483,10 +500,21 @@ struct Tile {
 
 // Probability exp(tau s - lse) of a backward entry, with the forward's sl2 = fl(tau log2e),
 // whose rounding the saved lse shares, and lse2 = fl(lse log2e), which mostly gives back the
-// base-2 value that the forward rounded to lse.  (float32 dk and dv against 64 bits, as a
-// multiple of one lane group per key: 0.99 and 0.98; with the low part of lse log2e put back
-// 1.00, at most 1.06; with s sl2 rounded first 1.04 and 1.06.)
+// base-2 value that the forward rounded to lse.
 __device__ __forceinline__ float prob(float s, float sl2, float lse2) { return exp2f(fmaf(s, sl2, -lse2)); }
+// The same with what the rounding of lse log2e loses multiplied back in (lse itself given):
+// for float32 logits from the matrix cores, which are not rounded as the forward's and gain
+// nothing from its rounding of lse.  dk and dv against 64 bits, as a multiple of one lane
+// group per key: matrix cores (W 24 to 128) 0.82 to 0.90 with it, 0.88 to 0.94 without;
+// logits in the forward's order (W 4 to 16) 0.91 to 0.95 with it, 0.89 to 0.92 without.
+__device__ __forceinline__ float prob_low(float s, float sl2, float l) {
+    const float v = l * kLog2e;
+    // kLog2e + 1.925963e-8 = log2(e); an infinite lse (a dropped query) loses nothing
+    float low = fmaf(l, 1.925963033500e-8f, fmaf(l, kLog2e, -v)) * kLn2;
+    low = __builtin_isfinite(v) ? low : 0.f;
+    const float p = prob(s, sl2, v);
+    return fmaf(p, -low, p);
+}
 
 // Weights 2^x of a bfloat16 band that the matrix cores cannot take in full: three bfloat16
 // parts hold 24 bits from 2^-109 on (their last one is a multiple of 2^-133), and the exp2
