@@ -63,15 +63,15 @@ def parse_args():
 #            --no-learned-alpha --no-integer-offsets --no-rope-on-load --no-configs --copy-probe-mb 256
 # each scaled by what the same counter reads for the plain 256 MiB device copy of that run.
 # They hold only for the kernel sources they were taken on (COUNTER_SOURCES_SHA).
-COUNTER_SOURCES_SHA = "612461e3efd0a46306964bbe254c4bd85df7845e949ab0275b2a017f7c490fbc"
+COUNTER_SOURCES_SHA = "8c275b748ae17c6332314c6dfb070fc0dabbbaa60394e991b4e72861b2815d90"
 COUNTER_WORKLOAD = "layer_60m_fixed_T1024"
 COUNTER_KIB = {  # kernel: (FETCH_SIZE, WRITE_SIZE) mean KiB per dispatch
-    "forward": (12407.9, 16752.5),
-    "bwd_dq": (20801.1, 10426.0),
-    "bwd_dkdv": (18535.9, 16624.2),
-    "rope": (4130.3, 8192.0),
+    "forward": (12407.9, 16754.8),
+    "bwd_dq": (20801.1, 10427.0),
+    "bwd_dkdv": (18526.3, 16619.8),
+    "rope": (4128.8, 8192.0),
 }
-COPY_PROBE_KIB = (262144.0, 131095.0, 262144.0)  # bytes moved each way; FETCH_SIZE; WRITE_SIZE
+COPY_PROBE_KIB = (262144.0, 131094.6, 262144.0)  # bytes moved each way; FETCH_SIZE; WRITE_SIZE
 
 
 def kernel_sources_sha() -> str:

@@ -42,9 +42,10 @@ namespace fibattn {
 //
 // What bounds it: as the forward, the latency of the rung gathers and their VALU work.
 // Against a kernel with one lane group per query, every row read from global memory by
-// every query (us a launch, interpolating): bf16 d 64 B4 H8 T2048 W64 135 -> 22.9; bf16
-// d 128 B2 H16 on 4 T2000 W8 82 -> 37; bf16 d 32 B8 H8 T1024 W10 23.6 -> 15.4 (the R^T of
+// every query (us a launch, interpolating): bf16 d 64 B4 H8 T2048 W64 137 -> 21.7; bf16
+// d 128 B2 H16 on 4 T2000 W8 79 -> 36.5; bf16 d 32 B8 H8 T1024 W10 23.3 -> 14.8 (the R^T of
 // dq, then a launch of its own, not included in the first figure).
+
 // dq and the dalpha parts of query ic, its entries one by one and only those it has, in the
 // order of the float32 kernel (quad layout; nact rungs, the wave's).  The parts are the whole
 // quad's, on its lane 0.
@@ -436,13 +437,14 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_f32_kernel(
 //     are those of the keys four lanes before and on.  For the wave's first and last key
 //     (the edges) they are taken before the loop, 16 rungs at a time.
 //
-// What bounds it: as dq, the latency of the rung gathers and their VALU work; two (NC 4) or
-// four (NC 2) waves per SIMD, as the registers of two query and two dO rows in flight allow.
-// Us a launch: bf16 d 64 B4 H8 T2048 W64 26.3; bf16 d 128 B2 H16 on 4 T2000 W8 51.7; bf16
-// d 32 B8 H8 T1024 W10 17.8; fp32 d 64 B4 H8 T1024 W12 25.6.  With one lane group per key,
-// every query row read from global memory by every key it attends, and the R^T of dk and
-// the dalpha sum as launches of their own, the training step of each took 82, 66, 15 and
-// 38 us more.
+// What bounds it: as dq, the latency of the rung gathers and their VALU work (47 to 54 % of
+// the issue slots in bfloat16); two (NC 4) or four (NC 2) waves per SIMD, as the registers of
+// two query and two dO rows in flight allow.  Us a launch, against one lane group per key,
+// every query row read from global memory by every key it attends (R^T of dk and the dalpha
+// sum then launches of their own, not included): bf16 d 64 B4 H8 T2048 W64 103 -> 28.3; bf16
+// d 128 B2 H16 on 4 T2000 W8 104 -> 53.6; bf16 d 32 B8 H8 T1024 W10 25.6 -> 18.5; fp32 d 64
+// B4 H8 T1024 W12 52 -> 25.6.
+
 // The terms of one query head in dk, dv of key j, its queries one by one and only those that
 // read it (quad layout; nact rungs, the wave's).
 template <typename TL>

@@ -18,12 +18,12 @@
 //     space, their probabilities' weighted values added in the same registers.
 // The whole softmax runs in base 2.
 //
-// What bounds it: the latency of the rung gathers (L2) and their VALU work; the band, on
-// the matrix cores, is a fraction of it at any window.  Against a kernel with one lane
-// group per query, every row read from global memory by every query and no matrix cores
-// (us a launch, interpolating unless noted): bf16 d 64 B4 H8 T1500 W128, integer offsets,
-// 115.8 -> 15.6; bf16 d 64 B4 H8 T2048 W64 76.3 -> 17.2; bf16 d 128 B2 H16 on 4 T2000 W8
-// 62.0 -> 28.3; bf16 d 32 B8 H8 T1024 W10 25.5 -> 11.1.
+// What bounds it: the latency of the rung gathers (L2) and the VALU work (37 to 50 % of the
+// issue slots); the band, on the matrix cores, is a fraction of it at any window.  Us a
+// launch, without and with q rotated on load, against a kernel with one lane group per query,
+// every row read from global memory by every query and no matrix cores: bf16 d 64 B4 H8 T1500
+// W128, integer offsets, 115 -> 15.7 (17.6); bf16 d 64 B4 H8 T2048 W64 75 -> 16.1 (18.5); bf16
+// d 128 B2 H16 on 4 T2000 W8 58 -> 27.7 (32.1); bf16 d 32 B8 H8 T1024 W10 24 -> 10.9 (14.2).
 #include "launch.h"
 #include "tile.h"
 
@@ -73,8 +73,9 @@ __device__ __forceinline__ void forward_by_entry(const typename TL::Slice &qq, c
 // taken together.  DEV: the rung table is the one at rtp, built on the device (rt_arg
 // unused).  rf.on: q holds unrotated rows; each is rotated where it is loaded (a query row
 // is used by one query only, so qrot may be q itself: no restrict on q) and written to qrot,
-// placed by lay.dq, for the backward: 3 to 5 us more here against 5 to 7 us for a launch of
-// its own.
+// placed by lay.dq, for the backward: d 128 B4 H8 T1024 3.7 us more here against 5.5 us for a
+// launch of its own, T4096 7.4 against 14.8; d 64 W24 T4096 3.7 against 7.1; d 32 B16 H8
+// T4096, where the chip is full of angles, 16 against 13.
 template <int D, bool INTERP, bool DEV>
 __global__ __launch_bounds__(256, (fwd_waves<D>)) void fwd_tile_kernel(
     const uint16_t *q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, uint16_t *__restrict__ o,
