@@ -20,6 +20,7 @@ LIB_PATH = os.path.join(_HERE, "libfibattn.so")
 FIBATTN_FP32, FIBATTN_BF16 = 0, 1
 MAX_RUNGS = 32
 MAX_WINDOW = 128
+# "dalpha_reduce" names no launch: the dk/dv launch sums dalpha
 KERNEL_IDS = {"rope": 0, "forward": 1, "bwd_dq": 2, "bwd_dkdv": 3, "dalpha_reduce": 4, "alpha": 5}
 EXPORTED = ("fibattn_rung_table", "fibattn_forward", "fibattn_backward_workspace_bytes",
             "fibattn_backward", "fibattn_forward_gqa", "fibattn_backward_gqa",
